@@ -217,7 +217,10 @@ typedef struct {
                            /* or STDG_CG at p_gamma = 0) for p = 1, 2, 3: M is  */
                            /* each element's own diagonal block of B (its      */
                            /* class's, inverted once per class), used when     */
-                           /* every such block is SPD; other solves ignore it */
+                           /* every such block is SPD, and on meshes of more   */
+                           /* than a few hundred elements that fill their      */
+                           /* bounding box a second level for the smooth part  */
+                           /* of the error; other solves ignore it             */
 } stdg_solve_opts;
 
 typedef struct {
@@ -228,9 +231,9 @@ typedef struct {
     double rel_residual;   /* ||b_a - S_a x|| / ||b_a|| in FP64 at exit        */
     double seconds;        /* wall time of the call                            */
     double initial_rel_residual;  /* the same for the initial guess            */
-    double fused_iter_us;  /* device time per iteration of the one-kernel FP32 */
-                           /* CG (HIP events around its back-to-back launches;  */
-                           /* 0 when that kernel did not run)                  */
+    double fused_iter_us;  /* device time per iteration of the preconditioned  */
+                           /* FP32 CG (HIP events around its back-to-back      */
+                           /* launches; 0 when it did not run)                 */
 } stdg_solve_report;
 
 /* y = (B (x) I) x in FP32: the spatial Schur operator B = dt^2 S^sp of

@@ -1,0 +1,544 @@
+// Two-level preconditioner of the FP32 inner CG on B (x) I (eq. CS_19 on every
+// time node).  With the block-Jacobi step alone the iterations grow with the
+// number of elements across the domain: nothing carries the smooth part of
+// the error further than one element per iteration.  The second level does,
+// in one additive step:
+//   M^-1 r = c^-1 (B_e^-1 r + P K P^T r),
+// P the continuous piecewise linear functions on a tensor grid of vertices,
+// sampled at the element nodes (corner values by `corner` or `tri`, node
+// values by the barycentric weights), K the inverse of dt^2 times the
+// Laplacian of that grid (linear elements, lumped mass, its constant mode
+// left out), which is spectrally equivalent to P^T B P: on structured cubes
+// 34..38 iterations per 1e-5 at p = 2, 3 whatever the size, as many as with
+// the exact P^T B P, against 103 (8^3), 150 (12^3) and about 420 (48^3) with
+// block Jacobi alone (CPU emulation; GPU times at launch_two_level).
+//
+// K is applied exactly, by fast diagonalisation: with the generalised
+// eigenvectors V_d of the one-dimensional stiffness and lumped mass matrices
+// K = (V_z (x) V_y (x) V_x) (l_x + l_y + l_z)^-1 (V_z (x) V_y (x) V_x)^T,
+// six small matrix products (48 x 48 per plane at 48^3) on
+// v_mfma_f32_16x16x4f32 in three kernels: the planes forward, the columns
+// there and back around the division, the planes backward.  What bounds them
+// is latency (48 workgroups per time node at 48^3, 64 MFLOP in all), so the
+// work per launch is one whole plane or column tile held in LDS.
+//
+// The grid: the vertices' own coordinate lines when the vertices are a tensor
+// grid (then a corner is a grid node), otherwise uniform lines with as many
+// cells as hexahedra of six elements fill the box, corners interpolated
+// trilinearly.  It needs a mesh that fills its bounding box (the elements'
+// volumes add up to it); other meshes keep the block-Jacobi step.
+
+#include <algorithm>
+#include <cmath>
+#include <map>
+#include <numeric>
+#include <vector>
+
+#include "internal.hpp"
+#include "kernels.hpp"
+#include "two_level.hpp"
+
+namespace stdg {
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int MAXN = 80;        // grid lines per direction (two padded planes in 64 KB of LDS)
+constexpr int PT = 512;         // threads of the plane kernel
+constexpr int CT = 256;         // threads of the column kernel
+constexpr int CC = 32;          // columns per workgroup of the column kernel
+// lanes per grid node of the restriction: a node of a tensor grid is reached
+// by about 24 corners, one of a grid between scattered vertices by about 190
+// (4,374 scattered elements: 14.6 us with 8 lanes per node, 5.0 with 64)
+constexpr int RL1 = 8, RLW = 64;
+
+inline int pad16(int n) { return (n + 15) / 16 * 16; }
+
+// g[a][node] = sum over the corners that reach the node, RL lanes per node,
+// entries of a node contiguous (padded with slot -1), summed in a fixed order
+template <bool HASW>
+__global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ slot, const float* __restrict__ w, int K,
+                                                  const float* __restrict__ e4, int64_t estr, float* __restrict__ g,
+                                                  int nodes, const double* __restrict__ scal, int it) {
+    if (tl_done(scal, it)) return;
+    constexpr int RL = HASW ? RLW : RL1;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t j = t / RL;
+    const int a = blockIdx.y, l = (int)(t % RL);
+    float s = 0.0f;
+    if (j < nodes) {
+        const float* ea = e4 + a * estr;
+        for (int k = l; k < K; k += RL) {
+            const int c = slot[j * K + k];
+            const float v = c >= 0 ? ea[c] : 0.0f;
+            s += HASW ? w[j * K + k] * v : v;
+        }
+    }
+#pragma unroll
+    for (int o = RL / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, RL);
+    if (l == 0 && j < nodes) g[(int64_t)a * nodes + j] = s;
+}
+
+// one plane z = const: out = My^T in Mx, in and out [ny][nx] (Mx, My padded
+// to multiples of 16 with zeros; V forward, V^T backward)
+__global__ void __launch_bounds__(PT) k_plane(const float* __restrict__ in, float* __restrict__ out,
+                                              const float* __restrict__ Mx, const float* __restrict__ My, int nx,
+                                              int ny, const double* __restrict__ scal, int it) {
+    extern __shared__ float sh[];
+    if (tl_done(scal, it)) return;
+    const int px = (nx + 15) / 16 * 16, py = (ny + 15) / 16 * 16, sx = px + 1;
+    float* X = sh;                   // [py][sx]
+    float* U = sh + py * sx;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
+    const float* src = in + (int64_t)blockIdx.x * nx * ny;
+    for (int t = tid; t < py * px; t += PT) {
+        const int i = t / px, j = t - i * px;
+        X[i * sx + j] = (i < ny && j < nx) ? src[i * nx + j] : 0.0f;
+    }
+    __syncthreads();
+    const int tx = px / 16, tiles = (py / 16) * tx;
+    for (int t = wave; t < tiles; t += PT / 64) {
+        const int r0 = t / tx * 16, c0 = t % tx * 16;
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k1 = 0; k1 < px; k1 += 16)
+#pragma unroll
+            for (int k = k1; k < k1 + 16; k += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[(r0 + lo) * sx + k + hi], Mx[(k + hi) * px + c0 + lo], acc, 0,
+                                                       0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) U[(r0 + 4 * hi + r) * sx + c0 + lo] = acc[r];
+    }
+    __syncthreads();
+    float* dst = out + (int64_t)blockIdx.x * nx * ny;
+    for (int t = wave; t < tiles; t += PT / 64) {
+        const int r0 = t / tx * 16, c0 = t % tx * 16;
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k1 = 0; k1 < py; k1 += 16)
+#pragma unroll
+            for (int k = k1; k < k1 + 16; k += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(My[(k + hi) * py + r0 + lo], U[(k + hi) * sx + c0 + lo], acc, 0,
+                                                       0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (r0 + 4 * hi + r < ny && c0 + lo < nx) dst[(r0 + 4 * hi + r) * nx + c0 + lo] = acc[r];
+    }
+}
+
+// CC columns of one time node: forward in z, times scale / (l_x + l_y + l_z)
+// (0 for the constant mode), backward in z, in place; the workgroup's share
+// of the sum of (transformed value)^2 times that factor, i.e. of (P^T r) . K (P^T r)
+__global__ void __launch_bounds__(CT) k_columns(float* __restrict__ t, const float* __restrict__ Vz,
+                                                const float* __restrict__ VzT, const float* __restrict__ lam, int nx,
+                                                int ny, int nz, float scale, float cut, double* __restrict__ part,
+                                                const double* __restrict__ scal, int it) {
+    extern __shared__ float sh[];
+    __shared__ double red[CT / 64];
+    if (tl_done(scal, it)) return;
+    constexpr int S = CC + 1;
+    const int pz = (nz + 15) / 16 * 16, cols = nx * ny;
+    float* X = sh;                   // [pz][S]
+    float* U = sh + pz * S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
+    const int c0 = blockIdx.x * CC;
+    float* ta = t + (int64_t)blockIdx.y * nz * cols;
+    for (int q = tid; q < pz * CC; q += CT) {
+        const int i = q / CC, j = q - i * CC;
+        X[i * S + j] = (i < nz && c0 + j < cols) ? ta[(int64_t)i * cols + c0 + j] : 0.0f;
+    }
+    __syncthreads();
+    const float* lx = lam;
+    const float* ly = lam + nx;
+    const float* lz = lam + nx + ny;
+    const int tiles = pz / 16 * (CC / 16);
+    double d = 0.0;
+    for (int q = wave; q < tiles; q += CT / 64) {
+        const int r0 = q / (CC / 16) * 16, b0 = q % (CC / 16) * 16;
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k1 = 0; k1 < pz; k1 += 16)
+#pragma unroll
+            for (int k = k1; k < k1 + 16; k += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Vz[(k + hi) * pz + r0 + lo], X[(k + hi) * S + b0 + lo], acc, 0,
+                                                       0, 0);
+        const int col = c0 + b0 + lo;
+        const float lxy = col < cols ? lx[col % nx] + ly[col / nx] : 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int kz = r0 + 4 * hi + r;
+            const float l = kz < nz ? lxy + lz[kz] : 0.0f;
+            const float f = l > cut ? scale / l : 0.0f;
+            d += (double)acc[r] * (double)acc[r] * (double)f;
+            U[kz * S + b0 + lo] = f * acc[r];
+        }
+    }
+    __syncthreads();
+    for (int q = wave; q < tiles; q += CT / 64) {
+        const int r0 = q / (CC / 16) * 16, b0 = q % (CC / 16) * 16;
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k1 = 0; k1 < pz; k1 += 16)
+#pragma unroll
+            for (int k = k1; k < k1 + 16; k += 4)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(VzT[(k + hi) * pz + r0 + lo], U[(k + hi) * S + b0 + lo], acc, 0,
+                                                       0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int iz = r0 + 4 * hi + r;
+            if (iz < nz && c0 + b0 + lo < cols) ta[(int64_t)iz * cols + c0 + b0 + lo] = acc[r];
+        }
+    }
+    const double s = tl_reduce<CT>(d, red);
+    if (tid == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+
+// corner values of every element by trilinear interpolation (grids that do
+// not pass through the vertices): tri = cell indices packed 10 bits each and
+// the three fractions
+struct TriCorner { int32_t cell; float f[3]; };
+__global__ void __launch_bounds__(256) k_corners(const TriCorner* __restrict__ tri, const float* __restrict__ y,
+                                                 float* __restrict__ yc, int64_t n, int64_t estr, int nx, int ny,
+                                                 int nz, int wrap, const double* __restrict__ scal, int it) {
+    if (tl_done(scal, it)) return;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= n) return;
+    const TriCorner c = tri[t];
+    const float* ya = y + (int64_t)blockIdx.y * nx * ny * nz;
+    const int i0 = c.cell & 1023, j0 = (c.cell >> 10) & 1023, k0 = c.cell >> 20;
+    const int i1 = wrap && i0 + 1 == nx ? 0 : i0 + 1, j1 = wrap && j0 + 1 == ny ? 0 : j0 + 1,
+              k1 = wrap && k0 + 1 == nz ? 0 : k0 + 1;
+    auto at = [&](int i, int j, int k) { return ya[((int64_t)k * ny + j) * nx + i]; };
+    auto line = [&](int j, int k) { return (1.0f - c.f[0]) * at(i0, j, k) + c.f[0] * at(i1, j, k); };
+    auto face = [&](int k) { return (1.0f - c.f[1]) * line(j0, k) + c.f[1] * line(j1, k); };
+    yc[blockIdx.y * estr + t] = (1.0f - c.f[2]) * face(k0) + c.f[2] * face(k1);
+}
+
+// ------------------------------------------------------------ host tables
+// One-dimensional problem on the lines x (periodic with period L): eigenvalues
+// l and M-orthonormal eigenvectors V [n][n] of the linear-element stiffness
+// against the lumped mass, by cyclic Jacobi rotations.
+void line_eigen(const std::vector<double>& x, bool periodic, double L, std::vector<double>& l,
+                std::vector<double>& V) {
+    const int n = (int)x.size();
+    std::vector<double> A((size_t)n * n, 0.0), M(n, 0.0);
+    const int cells = periodic ? n : n - 1;
+    for (int i = 0; i < cells; ++i) {
+        const int j = (i + 1) % n;
+        const double h = i + 1 < n ? x[i + 1] - x[i] : x[0] + L - x[i];
+        M[i] += 0.5 * h;
+        M[j] += 0.5 * h;
+        A[i * n + i] += 1.0 / h;
+        A[j * n + j] += 1.0 / h;
+        A[i * n + j] -= 1.0 / h;
+        A[j * n + i] -= 1.0 / h;
+    }
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j) A[i * n + j] /= std::sqrt(M[i] * M[j]);
+    V.assign((size_t)n * n, 0.0);     // rows are eigenvectors while rotating
+    for (int i = 0; i < n; ++i) V[i * n + i] = 1.0;
+    for (int sweep = 0; sweep < 30; ++sweep) {
+        double off = 0.0, diag = 0.0;
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j) (i == j ? diag : off) += A[i * n + j] * A[i * n + j];
+        if (off <= 1e-24 * (diag + off)) break;
+        for (int p = 0; p < n; ++p)
+            for (int q = p + 1; q < n; ++q) {
+                const double apq = A[p * n + q];
+                if (apq == 0.0) continue;
+                const double th = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
+                const double t = (th >= 0.0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
+                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
+                for (int k = 0; k < n; ++k) {
+                    const double u = A[p * n + k], v = A[q * n + k];
+                    A[p * n + k] = c * u - s * v;
+                    A[q * n + k] = s * u + c * v;
+                }
+                for (int k = 0; k < n; ++k) {
+                    const double u = A[k * n + p], v = A[k * n + q];
+                    A[k * n + p] = c * u - s * v;
+                    A[k * n + q] = s * u + c * v;
+                }
+                for (int k = 0; k < n; ++k) {
+                    const double u = V[p * n + k], v = V[q * n + k];
+                    V[p * n + k] = c * u - s * v;
+                    V[q * n + k] = s * u + c * v;
+                }
+            }
+    }
+    l.resize(n);
+    std::vector<double> W((size_t)n * n);
+    for (int k = 0; k < n; ++k) {
+        l[k] = std::max(A[k * n + k], 0.0);
+        for (int i = 0; i < n; ++i) W[i * n + k] = V[k * n + i] / std::sqrt(M[i]);
+    }
+    V.swap(W);
+}
+
+// the distinct values of coordinate d of the element corners (within tol;
+// with a period, hi is identified with lo), empty past MAXN of them
+std::vector<double> lines_of(const stdg_mesh* m, int d, double lo, double hi, bool periodic, double tol) {
+    std::vector<double> x;
+    bool many = false;
+    auto insert = [tol](std::vector<double>& l, double v) {
+        const auto it = std::lower_bound(l.begin(), l.end(), v - tol);
+        if (it == l.end() || std::fabs(*it - v) > tol) l.insert(it, v);
+    };
+#pragma omp parallel
+    {
+        std::vector<double> own;
+#pragma omp for schedule(static)
+        for (int64_t t = 0; t < m->E; ++t)
+            for (int k = 0; k < 4 && (int)own.size() <= MAXN; ++k) {
+                const double v = (double)m->vert[t][k][d];
+                insert(own, periodic && std::fabs(v - hi) < tol ? lo : v);
+            }
+#pragma omp critical
+        {
+            many = many || (int)own.size() > MAXN;
+            for (size_t i = 0; i < own.size() && !many; ++i) {
+                insert(x, own[i]);
+                many = (int)x.size() > MAXN;
+            }
+        }
+    }
+    if (many) x.clear();
+    return x;
+}
+
+// the host tables packed into one buffer, so that a mesh makes one
+// allocation and one copy for them (pieces at 256-byte boundaries)
+struct Pack {
+    std::vector<char> host;
+    template <typename T> size_t add(const std::vector<T>& v) {
+        const size_t at = reserve(v.size() * sizeof(T));
+        std::copy((const char*)v.data(), (const char*)(v.data() + v.size()), host.begin() + at);
+        return at;
+    }
+    size_t reserve(size_t bytes) {
+        const size_t at = host.size();
+        host.resize(at + (bytes + 255) / 256 * 256);
+        return at;
+    }
+};
+
+}  // namespace
+
+bool coarse_supported(const stdg_mesh* m) { return m->d.coarse.nodes > 0; }
+
+// Grid, eigenvectors and the transfer tables of the second level (see the
+// head of this file); nothing is built where the rule does not hold.
+int upload_coarse(stdg_mesh* m) {
+    CoarseTables& c = m->d.coarse;
+    const int64_t E = m->E;
+    double lo[3], hi[3], vol = 0.0;
+    for (int d = 0; d < 3; ++d) { lo[d] = 1e300; hi[d] = -1e300; }
+#pragma omp parallel for schedule(static) reduction(+ : vol) reduction(min : lo[:3]) reduction(max : hi[:3])
+    for (int64_t t = 0; t < E; ++t) {
+        const auto& v = m->vert[t];
+        for (int k = 0; k < 4; ++k)
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = std::min(lo[d], (double)v[k][d]);
+                hi[d] = std::max(hi[d], (double)v[k][d]);
+            }
+        vol += std::fabs((double)det3(sub(v[1], v[0]), sub(v[2], v[0]), sub(v[3], v[0]))) / 6.0;
+    }
+    double L[3], box = 1.0;
+    for (int d = 0; d < 3; ++d) box *= L[d] = hi[d] - lo[d];
+    if (!(std::fabs(vol - box) <= 1e-9 * box)) return STDG_OK;
+    const bool per = m->cfg.periodic != 0;
+    const double h = std::cbrt(6.0 * vol / (double)E);
+    std::vector<double> x[3];
+    double tol[3];
+    bool tensor = true;
+    size_t nodes = 1;
+    for (int d = 0; d < 3; ++d) {
+        tol[d] = 1e-6 * std::min(h, L[d]);
+        if (tensor) x[d] = lines_of(m, d, lo[d], hi[d], per, tol[d]);
+        tensor = tensor && !x[d].empty();
+        nodes *= x[d].size();
+    }
+    // a tensor grid of vertices holds about one node per six elements; far
+    // more lines than that belong to scattered vertices
+    if (tensor && nodes > (size_t)E) tensor = false;
+    for (int d = 0; d < 3; ++d) {
+        if (!tensor) {
+            const int cells = std::min(std::max(1, (int)std::llround(L[d] / h)), MAXN - 1);
+            x[d].resize(per ? cells : cells + 1);
+            for (size_t i = 0; i < x[d].size(); ++i) x[d][i] = lo[d] + L[d] * (double)i / cells;
+        }
+        if (x[d].size() < 2) return STDG_OK;
+    }
+    const int n[3] = {(int)x[0].size(), (int)x[1].size(), (int)x[2].size()};
+    const int G = m->G;
+    const int64_t epad = (E + 63) / 64 * 64;
+    // position of every corner
+    std::vector<int32_t> corner(tensor ? 4 * epad : 0, 0);
+    std::vector<TriCorner> tri(tensor ? 0 : 4 * epad);
+    const int N3 = n[0] * n[1] * n[2];
+    std::vector<int32_t> count(N3, 0);
+    auto node = [&](int i, int j, int k) { return (k * n[1] + j) * n[0] + i; };
+    auto visit = [&](int64_t c4, auto&& f) {
+        if (tensor) { f(corner[c4], 1.0f); return; }
+        const TriCorner& q = tri[c4];
+        const int i0[3] = {q.cell & 1023, (q.cell >> 10) & 1023, q.cell >> 20};
+        for (int s = 0; s < 8; ++s) {
+            float w = 1.0f;
+            int i[3];
+            for (int d = 0; d < 3; ++d) {
+                const int up1 = (s >> d) & 1;
+                w *= up1 ? q.f[d] : 1.0f - q.f[d];
+                i[d] = i0[d] + up1;
+                if (per && i[d] == n[d]) i[d] = 0;
+            }
+            if (w != 0.0f) f(node(i[0], i[1], i[2]), w);
+        }
+    };
+#pragma omp parallel for schedule(static)
+    for (int64_t t = 0; t < E; ++t)
+        for (int k = 0; k < 4; ++k) {
+            int i0[3];
+            float f[3];
+            for (int d = 0; d < 3; ++d) {
+                double v = (double)m->vert[t][k][d];
+                if (tensor) {
+                    if (per && std::fabs(v - hi[d]) < tol[d]) v = lo[d];
+                    i0[d] = (int)(std::lower_bound(x[d].begin(), x[d].end(), v - tol[d]) - x[d].begin());
+                } else {
+                    const int cells = per ? n[d] : n[d] - 1;
+                    const double s = (v - lo[d]) / L[d] * cells;
+                    i0[d] = std::min(std::max((int)std::floor(s), 0), cells - 1);
+                    f[d] = (float)std::min(std::max(s - i0[d], 0.0), 1.0);
+                }
+            }
+            if (tensor) corner[4 * t + k] = node(i0[0], i0[1], i0[2]);
+            else tri[4 * t + k] = TriCorner{i0[0] | (i0[1] << 10) | (i0[2] << 20), {f[0], f[1], f[2]}};
+        }
+    for (int64_t c4 = 0; c4 < 4 * E; ++c4) visit(c4, [&](int j, float) { ++count[j]; });
+    const int RL = tensor ? RL1 : RLW;
+    const int K = (*std::max_element(count.begin(), count.end()) + RL - 1) / RL * RL;
+    if ((int64_t)K * N3 > ((int64_t)1 << 28)) return STDG_OK;     // a few nodes that every corner reaches
+    std::vector<int32_t> slot((size_t)N3 * K, -1);
+    std::vector<float> wgt(tensor ? 0 : (size_t)N3 * K, 0.0f);
+    std::fill(count.begin(), count.end(), 0);
+    for (int64_t c4 = 0; c4 < 4 * E; ++c4)
+        visit(c4, [&](int j, float w) {
+            slot[(size_t)j * K + count[j]] = (int32_t)c4;
+            if (!tensor) wgt[(size_t)j * K + count[j]] = w;
+            ++count[j];
+        });
+    // one-dimensional eigenproblems (equal lines share one)
+    std::vector<double> l[3], V[3];
+    std::vector<float> lam, mats[3], matsT[3];
+    double top = 0.0;
+    for (int d = 0; d < 3; ++d) {
+        int same = -1;
+        for (int o = 0; o < d; ++o) {
+            bool eq = n[o] == n[d];
+            for (int i = 0; eq && i < n[d]; ++i) eq = std::fabs((x[d][i] - lo[d]) - (x[o][i] - lo[o])) <= tol[d];
+            if (eq && std::fabs(L[o] - L[d]) <= tol[d]) same = o;
+        }
+        if (same >= 0) { l[d] = l[same]; V[d] = V[same]; }
+        else line_eigen(x[d], per, L[d], l[d], V[d]);
+        const int pd = pad16(n[d]);
+        mats[d].assign((size_t)pd * pd, 0.0f);
+        matsT[d].assign((size_t)pd * pd, 0.0f);
+        for (int i = 0; i < n[d]; ++i)
+            for (int k = 0; k < n[d]; ++k) {
+                mats[d][i * pd + k] = (float)V[d][i * n[d] + k];
+                matsT[d][k * pd + i] = (float)V[d][i * n[d] + k];
+            }
+        double mx = 0.0;
+        for (double v : l[d]) { lam.push_back((float)v); mx = std::max(mx, v); }
+        top += mx;
+    }
+    double low = top;       // smallest non-zero eigenvalue; half of it separates the constant mode
+    for (int d = 0; d < 3; ++d)
+        for (double v : l[d])
+            if (v > 1e-8 * top) low = std::min(low, v);
+    c.cut = (float)(0.5 * low);
+    c.scale = (float)(1.0 / (m->cfg.dt * m->cfg.dt));
+    c.n[0] = n[0]; c.n[1] = n[1]; c.n[2] = n[2];
+    c.per = per ? 1 : 0;
+    c.K = K;
+    c.epad = epad;
+    Pack pk;
+    size_t at[14];
+    for (int d = 0; d < 3; ++d) {
+        at[d] = pk.add(mats[d]);
+        at[3 + d] = pk.add(matsT[d]);
+    }
+    at[6] = pk.add(lam);
+    at[7] = pk.add(slot);
+    at[8] = tensor ? pk.add(corner) : pk.add(tri);
+    at[9] = tensor ? 0 : pk.add(wgt);
+    const size_t copied = pk.host.size();
+    // work vectors after the tables
+    size_t end = copied;
+    auto room = [&](size_t bytes) {
+        const size_t o = end;
+        end += (bytes + 255) / 256 * 256;
+        return o;
+    };
+    at[10] = room(sizeof(float) * 4 * epad * G);
+    at[11] = room(sizeof(float) * (size_t)N3 * G);
+    at[12] = room(sizeof(float) * (size_t)N3 * G);
+    at[13] = room(sizeof(double) * (size_t)((n[0] * n[1] + CC - 1) / CC) * G);
+    const size_t yc = room(tensor ? 0 : sizeof(float) * 4 * epad * G);
+    STDG_HIP(hipMalloc(&c.base, end));
+    STDG_HIP(hipMemcpy(c.base, pk.host.data(), copied, hipMemcpyHostToDevice));
+    char* base = (char*)c.base;
+    for (int d = 0; d < 3; ++d) {
+        c.V[d] = (float*)(base + at[d]);
+        c.VT[d] = (float*)(base + at[3 + d]);
+    }
+    c.lam = (float*)(base + at[6]);
+    c.slot = (int32_t*)(base + at[7]);
+    if (tensor) {
+        c.corner = (int32_t*)(base + at[8]);
+    } else {
+        c.tri = base + at[8];
+        c.wgt = (float*)(base + at[9]);
+        c.yc = (float*)(base + yc);
+    }
+    c.e4 = (float*)(base + at[10]);
+    c.g = (float*)(base + at[11]);
+    c.t = (float*)(base + at[12]);
+    c.part = (double*)(base + at[13]);
+    c.nodes = N3;
+    return STDG_OK;
+}
+
+void free_coarse(stdg_mesh* m) {
+    CoarseTables& c = m->d.coarse;
+    if (c.base) (void)hipFree(c.base);
+    c = CoarseTables();
+}
+
+int coarse_partials(const stdg_mesh* m) {
+    const CoarseTables& c = m->d.coarse;
+    return (c.n[0] * c.n[1] + CC - 1) / CC * m->G;
+}
+
+// corner sums c.e4 -> K P^T r on the grid (c.g) and, off the grid, at the
+// corners (c.yc); the dot (P^T r) . K (P^T r) in c.part
+hipError_t coarse_solve(const stdg_mesh* m, const double* scal, int it, hipStream_t s) {
+    const CoarseTables& c = m->d.coarse;
+    const int G = m->G, nx = c.n[0], ny = c.n[1], nz = c.n[2];
+    const int64_t estr = 4 * c.epad;
+    const dim3 rgrid((unsigned)(((int64_t)c.nodes * (c.wgt ? RLW : RL1) + 255) / 256), G);
+    if (c.wgt)
+        hipLaunchKernelGGL(k_restrict<true>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
+                           scal, it);
+    else
+        hipLaunchKernelGGL(k_restrict<false>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
+                           scal, it);
+    const size_t plds = (size_t)2 * pad16(ny) * (pad16(nx) + 1) * sizeof(float);
+    hipLaunchKernelGGL(k_plane, dim3(nz * G), dim3(PT), plds, s, c.g, c.t, c.V[0], c.V[1], nx, ny, scal, it);
+    const size_t clds = (size_t)2 * pad16(nz) * (CC + 1) * sizeof(float);
+    hipLaunchKernelGGL(k_columns, dim3((nx * ny + CC - 1) / CC, G), dim3(CT), clds, s, c.t, c.V[2], c.VT[2], c.lam, nx,
+                       ny, nz, c.scale, c.cut, c.part, scal, it);
+    hipLaunchKernelGGL(k_plane, dim3(nz * G), dim3(PT), plds, s, c.t, c.g, c.VT[0], c.VT[1], nx, ny, scal, it);
+    if (c.tri)
+        hipLaunchKernelGGL(k_corners, dim3((unsigned)((4 * m->E + 255) / 256), G), dim3(256), 0, s,
+                           (const TriCorner*)c.tri, c.g, c.yc, 4 * m->E, estr, nx, ny, nz, c.per, scal, it);
+    return hipGetLastError();
+}
+
+}  // namespace stdg

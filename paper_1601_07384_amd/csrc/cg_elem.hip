@@ -30,6 +30,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "two_level.hpp"
 
 namespace stdg {
 namespace {
@@ -307,27 +308,33 @@ __global__ void __launch_bounds__(64 * EWPB) k_elem_iter(
 
 // y = cscale (B (x) I) x on the same per-element tables (the operator of the
 // inner solve's residual and of stdg_pressure_apply_spatial_f32): the own
-// and four neighbour blocks against the rows of x, all time nodes per
-// wavefront, each lane storing its row slice.
-template <int N, int G>
+// and four neighbour blocks against the rows of x, all time nodes
+// per wavefront, each lane storing its row slice.  With DOT it is the
+// operator of iteration `it` of the two-level CG and leaves the workgroup's
+// share of x.y.
+template <int N, int G, bool DOT>
 __global__ void __launch_bounds__(64 * EWPB) k_elem_op(const float* __restrict__ table,
                                                        const int32_t* __restrict__ nbr, const float* x, float* y,
-                                                       float cscale, int32_t E, uint32_t n_waves, uint32_t vbytes) {
+                                                       float cscale, int32_t E, uint32_t n_waves, uint32_t vbytes,
+                                                       const double* __restrict__ scal, int it,
+                                                       double* __restrict__ part_out) {
+    if (DOT && tl_done(scal, it)) return;
     typedef ElemShape<N> S;
     constexpr int L = S::L, RPL = S::RPL, EPW = S::EPW, NC4 = S::NC4;
     constexpr uint32_t ROWB = 4u * N;
     constexpr size_t BSZ = (size_t)RPL * NC4 * 64;
     const uint32_t lblock = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     const uint32_t wid = lblock * EWPB + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wid >= n_waves) return;
+    if (!DOT && wid >= n_waves) return;
+    double d = 0.0;
     const int lane = threadIdx.x & 63, q = lane % L, r0 = q * RPL;
     const int32_t e = (int32_t)(wid * EPW) + lane / L;
-    const bool valid = e < E;
+    const bool valid = wid < n_waves && e < E;
     const Rsrc rn = make_rsrc(nbr, 16u * (uint32_t)E);
     const i4v nb =
         __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(rn, (int)(valid ? 16u * e : OOB), 0, 0));
     const Rsrc rx = make_rsrc(x, vbytes);
-    const f4* tb = (const f4*)table + (size_t)wid * 6 * BSZ + lane;
+    const f4* tb = (const f4*)table + (size_t)(wid < n_waves ? wid : 0) * 6 * BSZ + lane;
     float acc[1][G][RPL];
 #pragma unroll
     for (int a = 0; a < G; ++a)
@@ -352,6 +359,17 @@ __global__ void __launch_bounds__(64 * EWPB) k_elem_op(const float* __restrict__
 #pragma unroll
         for (int i = 0; i < RPL; ++i) o[i] = cscale * acc[0][a][i];
         eslice_store<N>(ry, own == OOB ? OOB : own + a * ROWB, r0, o);
+        if (DOT) {
+            float xs[RPL];
+            eslice_load<N>(rx, own == OOB ? OOB : own + a * ROWB, r0, xs);
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) d += (double)xs[i] * (double)o[i];
+        }
+    }
+    if (DOT) {
+        __shared__ double sh[EWPB];
+        const double t = tl_reduce<64 * EWPB>(d, sh);
+        if (threadIdx.x == 0) part_out[blockIdx.x] = t;
     }
 }
 
@@ -436,6 +454,181 @@ __global__ void __launch_bounds__(64 * EWPB) k_elem_apply64(const double* __rest
                 for (int b = 0; b < G; ++b) s += Cm[a][b] * acc[b][i];
                 y[((int64_t)e * G + a) * N + r0 + i] = s;
             }
+}
+
+// ------------------------------------------------- two-level CG iteration
+// Residual and direction kernels of the two-level CG (cg_coarse.hip) for
+// element-major vectors [E][G][N]; the same steps as k_lane_update and
+// k_lane_direction.  A wavefront takes EPW elements, L lanes each, lane q its
+// rows q RPL ..; the lane's RPL rows of the inverse own block are loaded once
+// and serve every time node.  With PER they come from the per-element table
+// (block 5, coalesced), otherwise from a table per class (own_inv, entry
+// (((c RPL + rr) NC4 + c4) L + q) 4 + j), which a wavefront of few classes
+// reads from the cache.
+template <int N, bool PER>
+__device__ inline void load_inv_slice(const float* __restrict__ table, uint32_t group, int c,
+                                      float (&w)[ElemShape<N>::RPL][4 * ElemShape<N>::NC4]) {
+    typedef ElemShape<N> S;
+    constexpr int L = S::L, RPL = S::RPL, NC4 = S::NC4;
+    constexpr size_t BSZ = (size_t)RPL * NC4 * 64;
+    const int lane = threadIdx.x & 63;
+    const f4* tb = PER ? (const f4*)table + ((size_t)group * 6 + 5) * BSZ + lane
+                       : (const f4*)table + (size_t)c * RPL * NC4 * L + lane % L;
+    constexpr int ST = PER ? 64 : L;
+#pragma unroll
+    for (int rr = 0; rr < RPL; ++rr)
+#pragma unroll
+        for (int c4 = 0; c4 < NC4; ++c4) {
+            const f4 t = tb[ST * (rr * NC4 + c4)];
+            w[rr][4 * c4] = t.x; w[rr][4 * c4 + 1] = t.y; w[rr][4 * c4 + 2] = t.z; w[rr][4 * c4 + 3] = t.w;
+        }
+}
+
+struct ElemItems { uint32_t first, end, step; };
+__device__ inline ElemItems elem_items(uint32_t n) {
+    const uint32_t per = (n + 7) / 8, lo = (blockIdx.x % 8) * per;
+    ElemItems w;
+    w.first = lo + (blockIdx.x / 8) * EWPB + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.end = lo + per < n ? lo + per : n;
+    w.step = (gridDim.x / 8) * EWPB;
+    return w;
+}
+
+template <int N, bool PER>
+__global__ void __launch_bounds__(64 * EWPB) k_elem_update(
+    const float* __restrict__ table, const int32_t* __restrict__ cls, float* r, const float* q, f4* __restrict__ e4,
+    double* scal, int it, const double* __restrict__ part_pq, int n_pq, float minv, int32_t E, int32_t G,
+    uint32_t n_groups, int64_t epad, uint32_t vbytes, double* __restrict__ part_out) {
+    __shared__ double sh[EWPB];
+    if (tl_done(scal, it)) return;
+    typedef ElemShape<N> S;
+    constexpr int L = S::L, RPL = S::RPL, EPW = S::EPW, NC4 = S::NC4;
+    const double alpha64 = it > 0 ? tl_alpha(scal, tl_sum<64 * EWPB>(part_pq, n_pq, 1, sh), it) : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[TL_ALPHA] = alpha64;
+    const float alpha = (float)alpha64;
+    static constexpr Bary<N> bary;
+    const Rsrc rr = make_rsrc(r, vbytes), rq = make_rsrc(q, vbytes);
+    const int lane = threadIdx.x & 63, ql = lane % L, r0 = ql * RPL;
+    double d0 = 0.0, d1 = 0.0;
+    const ElemItems w = elem_items(n_groups);
+    for (uint32_t i = w.first; i < w.end; i += w.step) {
+        const int32_t e = (int32_t)(i * EPW) + lane / L;
+        const bool valid = e < E;
+        float iv[RPL][4 * NC4];
+        load_inv_slice<N, PER>(table, i, PER ? 0 : cls[valid ? e : E - 1], iv);
+        for (int a = 0; a < G; ++a) {
+            const uint32_t off = valid ? ((uint32_t)e * (uint32_t)G + (uint32_t)a) * (4u * N) : OOB;
+            float rv[N], rs[RPL];
+            erow_load<N>(rr, off, rv);
+            eslice_load<N>(rr, off, r0, rs);
+            if (it > 0) {
+                float qv[N], qs[RPL];
+                erow_load<N>(rq, off, qv);
+                eslice_load<N>(rq, off, r0, qs);
+#pragma unroll
+                for (int k = 0; k < N; ++k) rv[k] -= alpha * qv[k];
+#pragma unroll
+                for (int k = 0; k < RPL; ++k) rs[k] -= alpha * qs[k];
+                eslice_store<N>(rr, off, r0, rs);
+            }
+            f4 c4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (bary.w[k][v] != 0.0f) c4[v] += bary.w[k][v] * rv[k];
+            if (valid && ql == 0) e4[(int64_t)a * epad + e] = c4;
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                float z = 0.0f;
+#pragma unroll
+                for (int c = 0; c < N; ++c) z = __builtin_fmaf(iv[k][c], rv[c], z);
+                d0 += (double)rs[k] * (double)rs[k];
+                d1 += (double)rs[k] * (double)(minv * z);
+            }
+        }
+    }
+    const double s0 = tl_reduce<64 * EWPB>(d0, sh);
+    const double s1 = tl_reduce<64 * EWPB>(d1, sh);
+    if (threadIdx.x == 0) {
+        part_out[2 * blockIdx.x] = s0;
+        part_out[2 * blockIdx.x + 1] = s1;
+    }
+}
+
+template <int N, bool PER>
+__global__ void __launch_bounds__(64 * EWPB) k_elem_direction(
+    const float* __restrict__ table, const int32_t* __restrict__ cls, const float* r, float* p, float* x,
+    const i4v* __restrict__ corner, const float* __restrict__ y, int64_t ystr, double* scal, int it,
+    const double* __restrict__ part_up, int n_up, const double* __restrict__ part_c, int n_c, float minv, double tol2,
+    int32_t E, int32_t G, uint32_t n_groups, uint32_t vbytes) {
+    __shared__ double sh[EWPB];
+    if (tl_done(scal, it)) return;
+    typedef ElemShape<N> S;
+    constexpr int L = S::L, RPL = S::RPL, EPW = S::EPW, NC4 = S::NC4;
+    const TlStep st = tl_step<64 * EWPB>(scal, it, part_up, n_up, part_c, n_c, (double)minv, tol2, sh);
+    if (it == 0 && st.stop) return;
+    const float alpha = (float)st.alpha, beta = (float)st.beta;
+    const Rsrc rr = make_rsrc(r, vbytes), rp = make_rsrc(p, vbytes), rx = make_rsrc(x, vbytes);
+    const int lane = threadIdx.x & 63, r0 = (lane % L) * RPL;
+    // corner weights of the lane's rows
+    static constexpr Bary<N> bary;
+    float bw[RPL][4];
+#pragma unroll
+    for (int k = 0; k < RPL; ++k)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bw[k][v] = r0 + k < N ? bary.w[r0 + k][v] : 0.0f;
+    const ElemItems w = elem_items(n_groups);
+    for (uint32_t i = w.first; i < w.end; i += w.step) {
+        const int32_t e = (int32_t)(i * EPW) + lane / L;
+        const bool valid = e < E;
+        float iv[RPL][4 * NC4];
+        load_inv_slice<N, PER>(table, i, PER ? 0 : cls[valid ? e : E - 1], iv);
+        const i4v ci = corner && valid ? corner[e] : i4v{0, 0, 0, 0};
+        for (int a = 0; a < G; ++a) {
+            const uint32_t off = valid ? ((uint32_t)e * (uint32_t)G + (uint32_t)a) * (4u * N) : OOB;
+            float ps[RPL];
+            if (it > 0) {
+                float xs[RPL];
+                eslice_load<N>(rp, off, r0, ps);
+                eslice_load<N>(rx, off, r0, xs);
+#pragma unroll
+                for (int k = 0; k < RPL; ++k) xs[k] += alpha * ps[k];
+                eslice_store<N>(rx, off, r0, xs);
+                if (st.stop) continue;
+            } else {
+#pragma unroll
+                for (int k = 0; k < RPL; ++k) ps[k] = 0.0f;
+            }
+            float rv[N];
+            erow_load<N>(rr, off, rv);
+            const float* ya = y + (int64_t)a * ystr;
+            const f4 yc = !valid ? f4{0.0f, 0.0f, 0.0f, 0.0f}
+                                 : (corner ? f4{ya[ci.x], ya[ci.y], ya[ci.z], ya[ci.w]} : ((const f4*)ya)[e]);
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                float z = bw[k][0] * yc.x + bw[k][1] * yc.y + bw[k][2] * yc.z + bw[k][3] * yc.w;
+#pragma unroll
+                for (int c = 0; c < N; ++c) z = __builtin_fmaf(iv[k][c], rv[c], z);
+                ps[k] = minv * z + beta * ps[k];
+            }
+            eslice_store<N>(rp, off, r0, ps);
+        }
+    }
+}
+
+template <int N> int own_inverse_table(stdg_mesh* m, const std::vector<double>& inv) {
+    typedef ElemShape<N> S;
+    constexpr int L = S::L, RPL = S::RPL, NC4 = S::NC4;
+    std::vector<float> t((size_t)m->n_classes * RPL * NC4 * L * 4, 0.0f);
+    for (int c = 0; c < m->n_classes; ++c)
+        for (int r = 0; r < N; ++r)
+            for (int col = 0; col < N; ++col)
+                t[((((size_t)c * RPL + r % RPL) * NC4 + col / 4) * L + r / RPL) * 4 + col % 4] =
+                    (float)inv[((size_t)c * N + r) * N + col];
+    STDG_HIP(hipMalloc(&m->d.own_inv, t.size() * sizeof(float)));
+    STDG_HIP(hipMemcpy(m->d.own_inv, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice));
+    return STDG_OK;
 }
 
 template <int N> void elem_table64(const stdg_mesh* m, std::vector<double>& out) {
@@ -559,8 +752,8 @@ hipError_t elem_apply_f32(const stdg_mesh* m, const float* x, float* y, float cs
     const uint32_t nw = (uint32_t)elem_waves_n(m);
 #define STDG_NG(n, g)                                                                                           \
     if (m->N == n && m->G == g) {                                                                               \
-        hipLaunchKernelGGL((k_elem_op<n, g>), grid, block, 0, s, m->d.elem_ops, m->d.nbr, x, y, cscale,        \
-                           (int32_t)m->E, nw, vbytes);                                                          \
+        hipLaunchKernelGGL((k_elem_op<n, g, false>), grid, block, 0, s, m->d.elem_ops, m->d.nbr, x, y, cscale, \
+                           (int32_t)m->E, nw, vbytes, (const double*)nullptr, 0, (double*)nullptr);             \
         return hipGetLastError();                                                                               \
     }
     STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(4, 3) STDG_NG(4, 4) STDG_NG(4, 5)
@@ -588,5 +781,77 @@ hipError_t elem_iter_f32(const stdg_mesh* m, float* x, const float* r_in, const 
 #undef STDG_NG
     return hipErrorInvalidValue;
 }
+
+// inverse own blocks per class for the element-major two-level kernels of
+// meshes without per-element tables
+int upload_own_inverse(stdg_mesh* m, const std::vector<double>& inv) {
+    switch (m->N) {
+        case 4: return own_inverse_table<4>(m, inv);
+        case 10: return own_inverse_table<10>(m, inv);
+        case 20: return own_inverse_table<20>(m, inv);
+        default: return STDG_OK;
+    }
+}
+
+int64_t elem_groups(const stdg_mesh* m) { return elem_waves_n(m); }
+
+hipError_t elem_tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * m->E * m->G * m->N);
+    const dim3 grid((unsigned)elem_iter_blocks(m)), block(64 * EWPB);
+    const uint32_t nw = (uint32_t)elem_waves_n(m);
+#define STDG_NG(n, g)                                                                                              \
+    if (m->N == n && m->G == g) {                                                                                  \
+        hipLaunchKernelGGL((k_elem_op<n, g, true>), grid, block, 0, s, m->d.elem_ops, m->d.nbr, t.p, t.q, t.cscale, \
+                           (int32_t)m->E, nw, vbytes, t.scal, it, t.part_pq);                                      \
+        return hipGetLastError();                                                                                  \
+    }
+    STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(4, 3) STDG_NG(4, 4) STDG_NG(4, 5)
+    STDG_NG(10, 1) STDG_NG(10, 2) STDG_NG(10, 3) STDG_NG(10, 4) STDG_NG(10, 5)
+    STDG_NG(20, 1) STDG_NG(20, 2) STDG_NG(20, 3) STDG_NG(20, 4) STDG_NG(20, 5)
+#undef STDG_NG
+    return hipErrorInvalidValue;
+}
+
+#define STDG_TL(CALL)                                                                  \
+    if (m->d.elem_ops) {                                                               \
+        switch (m->N) {                                                                \
+            case 4: CALL(4, true, m->d.elem_ops); break;                               \
+            case 10: CALL(10, true, m->d.elem_ops); break;                             \
+            case 20: CALL(20, true, m->d.elem_ops); break;                             \
+            default: return hipErrorInvalidValue;                                      \
+        }                                                                              \
+    } else {                                                                           \
+        switch (m->N) {                                                                \
+            case 4: CALL(4, false, m->d.own_inv); break;                               \
+            case 10: CALL(10, false, m->d.own_inv); break;                             \
+            case 20: CALL(20, false, m->d.own_inv); break;                             \
+            default: return hipErrorInvalidValue;                                      \
+        }                                                                              \
+    }                                                                                  \
+    return hipGetLastError();
+
+hipError_t elem_tl_update(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * m->E * m->G * m->N);
+#define STDG_CALL(n, per, table)                                                                                    \
+    hipLaunchKernelGGL((k_elem_update<n, per>), dim3(blocks), dim3(64 * EWPB), 0, s, table, m->d.cls, t.r, t.q,      \
+                       (f4*)m->d.coarse.e4, t.scal, it, t.part_pq, tl_op_blocks(m), 1.0f / t.cscale, (int32_t)m->E, \
+                       (int32_t)m->G, (uint32_t)elem_waves_n(m), m->d.coarse.epad, vbytes, t.part_up)
+    STDG_TL(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t elem_tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * m->E * m->G * m->N);
+    const CoarseTables& c = m->d.coarse;
+    const float* y = c.corner ? c.g : c.yc;
+    const int64_t ystr = c.corner ? c.nodes : 4 * c.epad;
+#define STDG_CALL(n, per, table)                                                                                      \
+    hipLaunchKernelGGL((k_elem_direction<n, per>), dim3(blocks), dim3(64 * EWPB), 0, s, table, m->d.cls, t.r, t.p,     \
+                       t.x, (const i4v*)c.corner, y, ystr, t.scal, it, t.part_up, blocks, c.part, coarse_partials(m), \
+                       1.0f / t.cscale, t.tol2, (int32_t)m->E, (int32_t)m->G, (uint32_t)elem_waves_n(m), vbytes)
+    STDG_TL(STDG_CALL)
+#undef STDG_CALL
+}
+#undef STDG_TL
 
 }  // namespace stdg

@@ -51,6 +51,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "two_level.hpp"
 
 namespace stdg {
 
@@ -88,6 +89,16 @@ constexpr int RED_T = 1024;             // threads of the one-block reductions
 constexpr int WPB = 4;                  // wavefronts per workgroup of the operator kernel (8 measured slower)
 constexpr int NPART = 5;                // partial dot products per block ...
 constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
+// elements from which the two-level CG is used.  An iteration costs seven to
+// eight launches instead of two, about 33 us instead of 10..14 where latency
+// is all, and saves as many as the mesh is wide.  Solve to 1e-10, ms, block
+// Jacobi against two-level: run layout (periodic cubes), p = 2: 1,296 elements
+// 2.17 / 2.41, 2,058 2.38 / 2.51, 3,072 2.90 / 2.56, p = 3: 2,058 3.15 / 3.14,
+// 3,072 3.85 / 3.02, 82,944 (p_gamma = 1) 22.7 / 6.3, 663,552 212 / 15.5; the
+// line leaves the even range to the older path.  Walls (tile kernel) 384
+// elements 3.31 / 2.47, 1,296 4.32 / 2.58, 3,072 4.98 / 2.85; scattered
+// vertices 384 4.06 / 3.58, 1,296 5.72 / 4.24.
+constexpr int64_t TL_MIN_E_RUN = 4096, TL_MIN_E = 384;
 
 __device__ inline Rsrc make_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
@@ -257,13 +268,17 @@ __device__ inline TilePos tile_pos(int wave, int32_t E, int32_t G, uint64_t gmul
     return t;
 }
 
-template <int N, bool ITER>
+// With DOT (and not ITER) the plain operator is that of iteration `iter` of the
+// two-level CG: it leaves the workgroup's share of x.y and reads `ab` as its
+// scalar record.
+template <int N, bool ITER, bool DOT = false>
 __global__ void __launch_bounds__(64 * WPB) k_cg_op(const float* __restrict__ A, const int32_t* __restrict__ cls,
                                                const int32_t* __restrict__ nbr, float* x, const float* r_in,
                                                const float* p_in, const float* q_in, float* r_out, float* p_out,
                                                float* q_out, const double* __restrict__ ab, float cscale,
                                                int precond, int32_t E, int32_t G, uint64_t gmul, uint32_t vbytes,
-                                               double* __restrict__ part_out) {
+                                               double* __restrict__ part_out, int iter = 0) {
+    if (DOT && tl_done(ab, iter)) return;
     typedef SliceShape<N> S;
     constexpr int W = S::W, REM = S::REM, KS = S::KS, MT = S::MT, NB = S::NB, NA = S::NA, NI = S::NI,
                   NT = S::NT;
@@ -385,6 +400,13 @@ __global__ void __launch_bounds__(64 * WPB) k_cg_op(const float* __restrict__ A,
     if (!ITER) {
         bstore<W>(rq_out, off[0], o);
         if (REM > 0) bstore<1>(rq_out, offr[0], &o[W]);
+        if (DOT) {
+            double d = 0.0;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) d += (double)bv[0][s] * (double)o[s];
+            const double t = tl_reduce<64 * WPB>(d, sh);
+            if (threadIdx.x == 0) part_out[blockIdx.x] = t;
+        }
         return;
     }
     // w = M^-1 q = B_e^-1 (B p) and r = M z = c B_e z on the own rows
@@ -531,7 +553,15 @@ hipError_t op_n(const stdg_mesh* m, float* x, const float* r_in, const float* p_
     }
     hipLaunchKernelGGL((k_cg_op<N, ITER>), dim3((unsigned)tile_blocks(m)), dim3(64 * WPB), 0, s, m->d.aop32, m->d.cls,
                        m->d.nbr, x, r_in, p_in, q_in, r_out, p_out, q_out, ab, cscale, precond, (int32_t)m->E,
-                       (int32_t)m->G, g_multiplier(m), vbytes, part_out);
+                       (int32_t)m->G, g_multiplier(m), vbytes, part_out, 0);
+    return hipGetLastError();
+}
+
+template <int N> hipError_t tile_tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * m->E * m->G * m->N);
+    hipLaunchKernelGGL((k_cg_op<N, false, true>), dim3((unsigned)tile_blocks(m)), dim3(64 * WPB), 0, s, m->d.aop32,
+                       m->d.cls, m->d.nbr, nullptr, t.p, nullptr, nullptr, nullptr, nullptr, t.q, t.scal, t.cscale, 0,
+                       (int32_t)m->E, (int32_t)m->G, g_multiplier(m), vbytes, t.part_pq, it);
     return hipGetLastError();
 }
 
@@ -608,9 +638,45 @@ int upload_cg_operands(stdg_mesh* m) {
     m->d.cg_precond_ok = spd ? 1 : 0;
     STDG_HIP(hipMalloc(&m->d.aop32, t.size() * sizeof(float)));
     STDG_HIP(hipMemcpy(m->d.aop32, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice));
-    const int e = upload_lane_operands(m, invs);
-    if (e != STDG_OK || lane_supported(m)) return e;
-    return upload_elem_operands(m, invs);
+    int e = upload_lane_operands(m, invs);
+    if (e == STDG_OK && !lane_supported(m)) e = upload_elem_operands(m, invs);
+    // the second level, where the one-kernel iteration (and its workspaces) would serve
+    if (e != STDG_OK || !spd || m->E < (lane_supported(m) ? TL_MIN_E_RUN : TL_MIN_E) || !cg_fused_supported(m)) return e;
+    if ((e = upload_coarse(m))) return e;
+    if (coarse_supported(m) && !lane_supported(m) && !elem_supported(m)) e = upload_own_inverse(m, invs);
+    return e;
+}
+
+int tl_op_blocks(const stdg_mesh* m) {
+    return (int)(lane_supported(m) ? lane_run_blocks(m) : (elem_supported(m) ? elem_iter_blocks(m) : tile_blocks(m)));
+}
+
+// workgroups of the residual and direction kernels: four per CU at most
+// (each sums the partials of the kernel before it), a multiple of the 8 XCDs
+int tl_upd_blocks(const stdg_mesh* m) {
+    const int64_t waves = lane_supported(m) ? (m->E + 63) / 64 * m->G : elem_groups(m);
+    return (int)std::min<int64_t>(1024, ((waves + 3) / 4 + 7) / 8 * 8);
+}
+
+hipError_t tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    if (lane_supported(m)) return lane_tl_op(m, t, it, s);
+    if (elem_supported(m)) return elem_tl_op(m, t, it, s);
+    switch (m->N) {
+        case 4: return tile_tl_op<4>(m, t, it, s);
+        case 10: return tile_tl_op<10>(m, t, it, s);
+        case 20: return tile_tl_op<20>(m, t, it, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t tl_update(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    return lane_supported(m) ? lane_tl_update(m, t, it, tl_upd_blocks(m), s)
+                             : elem_tl_update(m, t, it, tl_upd_blocks(m), s);
+}
+
+hipError_t tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    return lane_supported(m) ? lane_tl_direction(m, t, it, tl_upd_blocks(m), s)
+                             : elem_tl_direction(m, t, it, tl_upd_blocks(m), s);
 }
 
 // workgroups (and partial records) of one CG iteration launch

@@ -43,6 +43,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "two_level.hpp"
 
 namespace stdg {
 namespace {
@@ -192,47 +193,65 @@ template <int N> __device__ inline void load_ops(const float* __restrict__ table
 // then the products with the rows of the other classes' lanes read as zeros.
 // A run of one class takes a single pass.
 // y = cscale B x (cscale = c for p_gamma = 0, 1 for one time node of B (x) I);
-// the five rows of a pass are loaded one block ahead of their products
-template <int N>
+// the five rows of a pass are loaded one block ahead of their products.  With
+// DOT (runs of one class only) the own row comes last, so that it is still
+// in registers for the workgroup's share of x.y, and the kernel belongs to
+// iteration `it` of the two-level CG.
+template <int N, bool DOT>
 __global__ void __launch_bounds__(64 * LWPB) k_lane_op(const float* __restrict__ table, const int32_t* __restrict__ cls,
                                                        const int32_t* __restrict__ nbr, const float* x, float* y,
                                                        float cscale, int32_t E, int32_t G, uint32_t n_waves,
-                                                       uint32_t vbytes) {
+                                                       uint32_t vbytes, const double* __restrict__ scal, int it,
+                                                       double* __restrict__ part_out) {
+    if (DOT && tl_done(scal, it)) return;
     const LanePos lp = lane_pos(E, G, n_waves);
-    if (!lp.wact) return;
-    const int mc = lp.valid ? cls[lp.e] : -1;
-    const Rsrc rn = make_rsrc(nbr, 16u * (uint32_t)E);
-    const i4v nb = __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(rn, (int)(lp.valid ? 16u * lp.e : OOB), 0, 0));
-    const int32_t rows[5] = {lp.e, nb.x, nb.y, nb.z, nb.w};
-    const Rsrc rx = make_rsrc(x, vbytes);
-    f4 acc[LaneShape<N>::NQ];
-    acc_zero<N>(acc);
-    float ops[LaneShape<N>::NV];
-    for (uint64_t todo = __ballot(lp.valid); todo;) {
-        const int c = __builtin_amdgcn_readlane(mc, __builtin_ctzll(todo));
-        const bool mine = lp.valid && mc == c;
-        todo &= ~__ballot(mine);
-        load_ops<N>(table, c, ops);
-        uint32_t off[5];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) off[k] = (mine && rows[k] >= 0) ? run_off<N>(rows[k], lp.a, G) : OOB;
+    if (!DOT && !lp.wact) return;
+    double d = 0.0;
+    if (lp.wact) {
+        const int mc = lp.valid ? cls[lp.e] : -1;
+        const Rsrc rn = make_rsrc(nbr, 16u * (uint32_t)E);
+        const i4v nb =
+            __builtin_bit_cast(i4v, __builtin_amdgcn_raw_buffer_load_b128(rn, (int)(lp.valid ? 16u * lp.e : OOB), 0, 0));
+        const int32_t rows[5] = {lp.e, nb.x, nb.y, nb.z, nb.w};
+        const Rsrc rx = make_rsrc(x, vbytes);
+        f4 acc[LaneShape<N>::NQ];
+        acc_zero<N>(acc);
+        float ops[LaneShape<N>::NV];
         float v[2][N];
-        row_load<N>(rx, off[0], v[0]);
-        auto blk = [&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            if constexpr (k < 4) row_load<N>(rx, off[k + 1], v[(k + 1) & 1]);
-            lane_block<N, k>(ops, v[k & 1], acc);
-        };
-        blk(std::integral_constant<int, 0>{});
-        blk(std::integral_constant<int, 1>{});
-        blk(std::integral_constant<int, 2>{});
-        blk(std::integral_constant<int, 3>{});
-        blk(std::integral_constant<int, 4>{});
+        constexpr int FIRST = DOT ? 1 : 0;
+        for (uint64_t todo = __ballot(lp.valid); todo;) {
+            const int c = __builtin_amdgcn_readlane(mc, __builtin_ctzll(todo));
+            const bool mine = lp.valid && mc == c;
+            todo &= ~__ballot(mine);
+            load_ops<N>(table, c, ops);
+            uint32_t off[5];
+#pragma unroll
+            for (int k = 0; k < 5; ++k) off[k] = (mine && rows[k] >= 0) ? run_off<N>(rows[k], lp.a, G) : OOB;
+            row_load<N>(rx, off[FIRST], v[0]);
+            auto blk = [&](auto kc) {
+                constexpr int k = decltype(kc)::value, cur = (k + FIRST) % 5, nxt = (k + 1 + FIRST) % 5;
+                if constexpr (k < 4) row_load<N>(rx, off[nxt], v[(k + 1) & 1]);
+                lane_block<N, cur>(ops, v[k & 1], acc);
+            };
+            blk(std::integral_constant<int, 0>{});
+            blk(std::integral_constant<int, 1>{});
+            blk(std::integral_constant<int, 2>{});
+            blk(std::integral_constant<int, 3>{});
+            blk(std::integral_constant<int, 4>{});
+        }
+        float o[N];
+        acc_rows<N>(acc, cscale, o);
+        // every lane of the run stores (the slots past the mesh get zeros)
+        row_store<N>(make_rsrc(y, vbytes), run_off<N>(lp.e, lp.a, G), o);
+        if (DOT)
+#pragma unroll
+            for (int r = 0; r < N; ++r) d += (double)v[0][r] * (double)o[r];
     }
-    float o[N];
-    acc_rows<N>(acc, cscale, o);
-    // every lane of the run stores (the slots past the mesh get zeros)
-    row_store<N>(make_rsrc(y, vbytes), run_off<N>(lp.e, lp.a, G), o);
+    if (DOT) {
+        __shared__ double sh[LWPB];
+        const double t = tl_reduce<64 * LWPB>(d, sh);
+        if (threadIdx.x == 0) part_out[blockIdx.x] = t;
+    }
 }
 
 // y = scale B_e^-1 x (block-Jacobi step)
@@ -554,6 +573,163 @@ __global__ void __launch_bounds__(64 * CHW, 2) k_lane_chunk(
     }
 }
 
+// ------------------------------------------------- two-level CG iteration
+// The other two kernels of an iteration of the two-level CG (cg_coarse.hip;
+// the first is k_lane_op<N, true>), each streaming whole rows of the run
+// layout with few registers (the inverse own block is 7 of the class's
+// operand registers at N = 20).  With the preconditioner's second level in
+// between, the recurrences of the one-kernel iteration would have to carry
+// two halves of z and w through every neighbour row; three kernels read and
+// write ten vectors in place of its eight, but each near the copy rate, and
+// the p rows a neighbour needs are read instead of being formed again.
+struct WaveItems { uint32_t first, end, step; };
+// the wavefronts' items 0 .. n - 1: XCD x (workgroups go round-robin) takes
+// a contiguous eighth
+__device__ inline WaveItems wave_items(uint32_t n) {
+    const uint32_t per = (n + 7) / 8, lo = (blockIdx.x % 8) * per;
+    WaveItems w;
+    w.first = lo + (blockIdx.x / 8) * LWPB + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.end = lo + per < n ? lo + per : n;
+    w.step = (gridDim.x / 8) * LWPB;
+    return w;
+}
+
+// the operands of the inverse own block (registers before them stay unset)
+template <int N> __device__ inline void load_inv_ops(const float* __restrict__ table, int c, float (&ops)[LaneShape<N>::NV]) {
+    constexpr int NV = LaneShape<N>::NV, I0 = 5 * LaneShape<N>::NQ * N / 64;
+    const f4* src = (const f4*)table + (size_t)c * (NV / 4) * 64 + (threadIdx.x & 63);
+#pragma unroll
+    for (int i = I0; i < NV / 4; ++i) {
+        const f4 t = src[64 * i];
+        ops[4 * i] = t.x; ops[4 * i + 1] = t.y; ops[4 * i + 2] = t.z; ops[4 * i + 3] = t.w;
+    }
+}
+
+// r -= alpha q (r = b at iteration 0), its corner sums e4 = P^T r, and the
+// workgroup's shares of r.r and r . B_e^-1 r / c
+template <int N>
+__global__ void __launch_bounds__(64 * LWPB) k_lane_update(
+    const float* __restrict__ table, const int32_t* __restrict__ cls, float* r, const float* q, f4* __restrict__ e4,
+    double* scal, int it, const double* __restrict__ part_pq, int n_pq, float minv, int32_t G, uint32_t n_waves,
+    int64_t epad, uint32_t vbytes, double* __restrict__ part_out) {
+    __shared__ double sh[LWPB];
+    if (tl_done(scal, it)) return;
+    const double alpha64 = it > 0 ? tl_alpha(scal, tl_sum<64 * LWPB>(part_pq, n_pq, 1, sh), it) : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[TL_ALPHA] = alpha64;
+    const float alpha = (float)alpha64;
+    static constexpr Bary<N> bary;
+    const Rsrc rr = make_rsrc(r, vbytes), rq = make_rsrc(q, vbytes);
+    const int lane = threadIdx.x & 63;
+    double d0 = 0.0, d1 = 0.0;
+    const WaveItems w = wave_items(n_waves);
+    for (uint32_t i = w.first; i < w.end; i += w.step) {
+        const uint32_t run = i / (uint32_t)G;
+        const int a = (int)(i - run * (uint32_t)G);
+        const int32_t e = (int32_t)(run * 64u) + lane;
+        const uint32_t off = run_off<N>(e, a, G);
+        float rv[N];
+        row_load<N>(rr, off, rv);
+        if (it > 0) {
+            float qv[N];
+            row_load<N>(rq, off, qv);
+#pragma unroll
+            for (int k = 0; k < N; ++k) rv[k] -= alpha * qv[k];
+            row_store<N>(rr, off, rv);
+        }
+        float ops[LaneShape<N>::NV];
+        load_inv_ops<N>(table, __builtin_amdgcn_readfirstlane(cls[run * 64u]), ops);
+        f4 c4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (bary.w[k][v] != 0.0f) c4[v] += bary.w[k][v] * rv[k];
+        e4[(int64_t)a * epad + e] = c4;
+        f4 acc[LaneShape<N>::NQ];
+        acc_zero<N>(acc);
+        lane_block<N, 5>(ops, rv, acc);
+        float z[N];
+        acc_rows<N>(acc, minv, z);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            d0 += (double)rv[k] * (double)rv[k];
+            d1 += (double)rv[k] * (double)z[k];
+        }
+    }
+    const double s0 = tl_reduce<64 * LWPB>(d0, sh);
+    const double s1 = tl_reduce<64 * LWPB>(d1, sh);
+    if (threadIdx.x == 0) {
+        part_out[2 * blockIdx.x] = s0;
+        part_out[2 * blockIdx.x + 1] = s1;
+    }
+}
+
+// x += alpha p, then p = z + beta p with z = (B_e^-1 r + P y) / c formed here
+// (cheaper than storing and reading it), y the second level's corner values
+// (through `corner`, or per element when it is null)
+template <int N>
+__global__ void __launch_bounds__(64 * LWPB) k_lane_direction(
+    const float* __restrict__ table, const int32_t* __restrict__ cls, const float* r, float* p, float* x,
+    const i4v* __restrict__ corner, const float* __restrict__ y, int64_t ystr, double* scal, int it,
+    const double* __restrict__ part_up, int n_up, const double* __restrict__ part_c, int n_c, float minv, double tol2,
+    int32_t E, int32_t G, uint32_t n_waves, uint32_t vbytes) {
+    __shared__ double sh[LWPB];
+    if (tl_done(scal, it)) return;
+    const TlStep st = tl_step<64 * LWPB>(scal, it, part_up, n_up, part_c, n_c, (double)minv, tol2, sh);
+    if (it == 0 && st.stop) return;
+    const float alpha = (float)st.alpha, beta = (float)st.beta;
+    static constexpr Bary<N> bary;
+    const Rsrc rr = make_rsrc(r, vbytes), rp = make_rsrc(p, vbytes), rx = make_rsrc(x, vbytes);
+    const int lane = threadIdx.x & 63;
+    const WaveItems w = wave_items(n_waves);
+    for (uint32_t i = w.first; i < w.end; i += w.step) {
+        const uint32_t run = i / (uint32_t)G;
+        const int a = (int)(i - run * (uint32_t)G);
+        const int32_t e = (int32_t)(run * 64u) + lane;
+        const uint32_t off = run_off<N>(e, a, G);
+        float pv[N];
+        if (it > 0) {
+            float xv[N];
+            row_load<N>(rp, off, pv);
+            row_load<N>(rx, off, xv);
+#pragma unroll
+            for (int k = 0; k < N; ++k) xv[k] += alpha * pv[k];
+            row_store<N>(rx, off, xv);
+            if (st.stop) continue;
+        } else {
+#pragma unroll
+            for (int k = 0; k < N; ++k) pv[k] = 0.0f;
+        }
+        float rv[N];
+        row_load<N>(rr, off, rv);
+        float ops[LaneShape<N>::NV];
+        load_inv_ops<N>(table, __builtin_amdgcn_readfirstlane(cls[run * 64u]), ops);
+        const float* ya = y + (int64_t)a * ystr;
+        f4 yc = {0.0f, 0.0f, 0.0f, 0.0f};     // (the slots past the mesh keep zeros)
+        if (e >= E) {
+        } else if (corner) {
+            const i4v ci = corner[e];
+            yc = f4{ya[ci.x], ya[ci.y], ya[ci.z], ya[ci.w]};
+        } else {
+            yc = ((const f4*)ya)[e];
+        }
+        f4 acc[LaneShape<N>::NQ];
+        acc_zero<N>(acc);
+        lane_block<N, 5>(ops, rv, acc);
+        float z[N];
+        acc_rows<N>(acc, 1.0f, z);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            float c = 0.0f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (bary.w[k][v] != 0.0f) c += bary.w[k][v] * yc[v];
+            pv[k] = minv * (z[k] + c) + beta * pv[k];
+        }
+        row_store<N>(rp, off, pv);
+    }
+}
+
 // ------------------------------------------------------------ layout moves
 // y (run layout) = (float)(scale x), x in [E][G][N]; zeros past the mesh
 template <int RW>
@@ -744,14 +920,57 @@ hipError_t lane_apply_f32(const stdg_mesh* m, const float* x, float* y, float cs
     const dim3 grid((unsigned)lane_run_blocks(m)), block(64 * LWPB);
 #define STDG_N(n)                                                                                                  \
     case n:                                                                                                        \
-        hipLaunchKernelGGL(k_lane_op<n>, grid, block, 0, s, m->d.lane_ops, m->d.cls, m->d.nbr, x, y, cscale,       \
-                           (int32_t)m->E, (int32_t)m->G, lane_waves(m), vbytes);                                   \
+        hipLaunchKernelGGL((k_lane_op<n, false>), grid, block, 0, s, m->d.lane_ops, m->d.cls, m->d.nbr, x, y,      \
+                           cscale, (int32_t)m->E, (int32_t)m->G, lane_waves(m), vbytes, (const double*)nullptr, 0, \
+                           (double*)nullptr);                                                                      \
         return hipGetLastError();
     switch (m->N) {
         STDG_N(4) STDG_N(10) STDG_N(20) STDG_N(35)
         default: return hipErrorInvalidValue;
     }
 #undef STDG_N
+}
+
+#define STDG_TL(CALL)                          \
+    switch (m->N) {                            \
+        case 4: CALL(4); break;                \
+        case 10: CALL(10); break;              \
+        case 20: CALL(20); break;              \
+        default: return hipErrorInvalidValue;  \
+    }                                          \
+    return hipGetLastError();
+
+hipError_t lane_tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * lane_len(m));
+#define STDG_CALL(n)                                                                                                 \
+    hipLaunchKernelGGL((k_lane_op<n, true>), dim3((unsigned)lane_run_blocks(m)), dim3(64 * LWPB), 0, s, m->d.lane_ops, \
+                       m->d.cls, m->d.nbr, t.p, t.q, t.cscale, (int32_t)m->E, (int32_t)m->G, lane_waves(m), vbytes,  \
+                       t.scal, it, t.part_pq)
+    STDG_TL(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t lane_tl_update(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * lane_len(m));
+#define STDG_CALL(n)                                                                                               \
+    hipLaunchKernelGGL(k_lane_update<n>, dim3(blocks), dim3(64 * LWPB), 0, s, m->d.lane_ops, m->d.cls, t.r, t.q,    \
+                       (f4*)m->d.coarse.e4, t.scal, it, t.part_pq, tl_op_blocks(m), 1.0f / t.cscale, (int32_t)m->G, \
+                       lane_waves(m), m->d.coarse.epad, vbytes, t.part_up)
+    STDG_TL(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t lane_tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s) {
+    const uint32_t vbytes = (uint32_t)(4 * lane_len(m));
+    const CoarseTables& c = m->d.coarse;
+    const float* y = c.corner ? c.g : c.yc;
+    const int64_t ystr = c.corner ? c.nodes : 4 * c.epad;
+#define STDG_CALL(n)                                                                                             \
+    hipLaunchKernelGGL(k_lane_direction<n>, dim3(blocks), dim3(64 * LWPB), 0, s, m->d.lane_ops, m->d.cls, t.r, t.p, \
+                       t.x, (const i4v*)c.corner, y, ystr, t.scal, it, t.part_up, blocks, c.part, coarse_partials(m), \
+                       1.0f / t.cscale, t.tol2, (int32_t)m->E, (int32_t)m->G, lane_waves(m), vbytes)
+    STDG_TL(STDG_CALL)
+#undef STDG_CALL
 }
 
 hipError_t lane_prec_f32(const stdg_mesh* m, const float* x, float* y, float scale, hipStream_t s) {

@@ -29,8 +29,35 @@ struct Face {
     V3 shift;                // right element's coordinates + shift = adjacent to left
 };
 
+// Second level of the inner CG's preconditioner (cg_coarse.hip): a tensor
+// grid, the eigenvectors of its one-dimensional problems, the transfer
+// between grid nodes and element corners, and the work vectors of one solve.
+struct CoarseTables {
+    int nodes = 0;                // grid nodes (0: not used for this mesh)
+    int n[3] = {0, 0, 0};         // nodes per direction
+    int per = 0;                  // periodic in all directions
+    float cut = 0.0f;             // eigenvalue sums below it belong to the constant mode
+    float scale = 0.0f;           // 1 / dt^2
+    void* base = nullptr;         // the one allocation that holds all of the following
+    int K = 0;                    // restriction entries per node
+    int64_t epad = 0;             // elements, padded to whole 64-element runs
+    float* V[3] = {nullptr, nullptr, nullptr};    // [n][n] eigenvectors, padded to multiples of 16
+    float* VT[3] = {nullptr, nullptr, nullptr};   // transposed
+    float* lam = nullptr;         // eigenvalues, x then y then z
+    int32_t* slot = nullptr;      // [nodes][K] corner (4 element + corner) reaching the node, -1 padding
+    float* wgt = nullptr;         // its weight (null: all one)
+    int32_t* corner = nullptr;    // [epad][4] grid node of each corner (null: interpolated)
+    void* tri = nullptr;          // [epad][4] trilinear position of each corner
+    float* yc = nullptr;          // [G][epad][4] interpolated corner values
+    float* e4 = nullptr;          // [G][epad][4] corner sums of an element-wise vector
+    float* g = nullptr;           // [G][nodes] grid values
+    float* t = nullptr;           // [G][nodes] transformed
+    double* part = nullptr;       // dot partials of the column kernel
+};
+
 // Device buffers owned by the handle (freed with it).
 struct DeviceTables {
+    CoarseTables coarse;
     double* blocks = nullptr;     // [n_classes][5][N][N]  dt^2 S^sp blocks
     float* blocks32 = nullptr;    // same, FP32
     float* aop32 = nullptr;       // FP32 blocks per lane in MFMA operand order (fused CG kernel)
@@ -43,6 +70,7 @@ struct DeviceTables {
     int64_t chunk_chunks = 0;
     float* elem_ops = nullptr;    // per-element FP32 blocks of the per-element PCG iteration (null: not used)
     double* elem_ops64 = nullptr; // per-element FP64 operator blocks of the FP64 apply on such meshes
+    float* own_inv = nullptr;     // inverse own blocks per class for the element-major two-level kernels
     float* lane_ops = nullptr;    // class operands of the element-per-lane kernels (null: a run mixes classes)
     int runs_uniform = 0;         // every 64-element run of the element order holds one class
     int32_t* run_cls = nullptr;   // [runs] class of a one-class 64-element run, -1 for a run of several

@@ -50,6 +50,35 @@ int64_t lane_len(const stdg_mesh* m);   // floats of a run-layout vector
 hipError_t lane_pack(const stdg_mesh* m, const double* x, double scale, float* y, hipStream_t s);
 hipError_t lane_unpack(const stdg_mesh* m, const float* y, const double* M, double scale, bool add, double* x,
                        hipStream_t s);
+bool coarse_supported(const stdg_mesh* m);
+int upload_coarse(stdg_mesh* m);
+void free_coarse(stdg_mesh* m);
+int coarse_partials(const stdg_mesh* m);
+hipError_t coarse_solve(const stdg_mesh* m, const double* scal, int it, hipStream_t s);
+// one iteration's operator, residual and direction kernels of the two-level
+// PCG (lane_*: run layout, elem_*: element-major)
+struct TwoLevel {
+    float *r, *p, *q, *x;
+    double* part_pq;          // partials of p.q (tl_op_blocks)
+    double* part_up;          // partials of r.r and r.z, interleaved (tl_upd_blocks)
+    double* scal;             // TL_COUNT scalars
+    float cscale;
+    double tol2;
+};
+int tl_op_blocks(const stdg_mesh* m);
+int tl_upd_blocks(const stdg_mesh* m);
+hipError_t tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s);
+hipError_t tl_update(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s);
+hipError_t tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s);
+hipError_t lane_tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s);
+hipError_t lane_tl_update(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s);
+hipError_t lane_tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s);
+int64_t lane_run_blocks(const stdg_mesh* m);
+hipError_t elem_tl_op(const stdg_mesh* m, const TwoLevel& t, int it, hipStream_t s);
+hipError_t elem_tl_update(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s);
+hipError_t elem_tl_direction(const stdg_mesh* m, const TwoLevel& t, int it, int blocks, hipStream_t s);
+int64_t elem_groups(const stdg_mesh* m);
+int upload_own_inverse(stdg_mesh* m, const std::vector<double>& inv);
 hipError_t launch_cg_check_f32(const double* part, int64_t n_part, double* scal, int slot, hipStream_t s);
 hipError_t time_mix_f64(const stdg_mesh* m, const double* M, const double* x, double* y, hipStream_t s);
 hipError_t time_mix_f32(const stdg_mesh* m, const float* M, const float* x, float* y, hipStream_t s);

@@ -29,6 +29,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "two_level.hpp"
 
 namespace stdg {
 
@@ -51,7 +52,8 @@ enum Slot {
     S_BALPHA = 69,
     S_BOMEGA = 70,
     S_BSIG = 71,
-    S_COUNT = 72
+    S_TL = 72,          // TL_COUNT scalars of the two-level CG
+    S_COUNT = 80
 };
 
 __device__ inline double wave_sum(double v) {
@@ -507,6 +509,78 @@ int cg_fused(Ctx& c, const float* b, float* x, float* r, float* p, float* q, dou
     return status;
 }
 
+// Two-level preconditioned CG (cg_coarse.hip) from x = 0: b is overwritten by
+// the residual.  Per iteration the operator, the residual update, the second
+// level and the direction update; alpha, beta and the convergence test are
+// formed on the device, and once the test holds the kernels still queued
+// return at once, so the host polls without draining the queue.  iters is
+// the iteration that met the tolerance.
+bool cg_two_level(const Ctx& c) {
+    return c.precond && (c.op == 2 || (c.op == 0 && c.m->G == 1)) && coarse_supported(c.m) && c.m->ws.ev[0] &&
+           tl_op_blocks(c.m) + 2 * tl_upd_blocks(c.m) <= NBLK * 208;
+}
+
+int cg_two_level_solve(Ctx& c, float* b, float* x, float* p, float* q, double tol_abs, int max_it, int check_every,
+                       int& iters, double& res_out) {
+    const stdg_mesh* m = c.m;
+    TwoLevel t;
+    t.r = b; t.p = p; t.q = q; t.x = x;
+    t.part_pq = c.partial;
+    t.part_up = c.partial + tl_op_blocks(m);
+    t.scal = c.scal + S_TL;
+    t.cscale = c.op == 2 ? 1.0f : (float)m->Ctime[0];
+    t.tol2 = tol_abs * tol_abs;
+    hipLaunchKernelGGL(k_fill<double>, dim3(1), dim3(256), 0, c.s, t.scal, 0.0, (int64_t)TL_COUNT);
+    // polls one interval behind the queue, every fourth iteration at most (an
+    // iteration is several kernels long)
+    const int every = std::min(check_every, 4);
+    hipEvent_t const* ev = m->ws.ev;
+    CK(hipEventRecord(ev[2], c.s));
+    int it = 0, slot = 0, pending = -1;
+    bool done = false;
+    double rec[TL_COUNT] = {0.0};
+    auto read = [&](int sl) -> int {
+        CK(hipEventSynchronize(ev[sl]));
+        for (int k = 0; k < TL_COUNT; ++k) rec[k] = c.hscal[8 + TL_COUNT * sl + k];
+        if (!std::isfinite(rec[TL_RR]) || !std::isfinite(rec[TL_RZ]) || !std::isfinite(rec[TL_RZ + 1])) {
+            set_error("non-finite residual in CG");
+            return STDG_ERR_NUMERIC;
+        }
+        done = rec[TL_DONE] != 0.0;
+        return STDG_OK;
+    };
+    for (;; ++it) {
+        if (it > 0) { CK(tl_op(m, t, it, c.s)); }
+        CK(tl_update(m, t, it, c.s));
+        CK(coarse_solve(m, t.scal, it, c.s));
+        CK(tl_direction(m, t, it, c.s));
+        if ((it > 0 && it % every == 0) || it == max_it) {
+            CK(hipMemcpyAsync(c.hscal + 8 + TL_COUNT * slot, t.scal, sizeof(double) * TL_COUNT, hipMemcpyDeviceToHost,
+                              c.s));
+            CK(hipEventRecord(ev[slot], c.s));
+            if (pending >= 0) {
+                if (int e = read(slot ^ 1)) return e;
+                if (done) break;
+            }
+            pending = it;
+            slot ^= 1;
+            if (it == max_it) break;
+        }
+    }
+    CK(hipEventRecord(ev[3], c.s));
+    if (!done)
+        if (int e = read(slot ^ 1)) return e;
+    iters = (int)rec[TL_ITERS];
+    c.applies += iters;
+    res_out = std::sqrt(rec[TL_RR]);
+    float ms = 0.0f;
+    CK(hipEventSynchronize(ev[3]));
+    CK(hipEventElapsedTime(&ms, ev[2], ev[3]));
+    c.loop_ms += ms;
+    c.loop_iters += iters;
+    return res_out <= tol_abs ? STDG_OK : STDG_NOT_CONVERGED;
+}
+
 // CG on S x = b (consistent); x, b, work vectors of type T.  Stops when the
 // recursive residual norm <= tol_abs or after max_it iterations.
 template <typename T>
@@ -797,7 +871,7 @@ int ensure_workspace(stdg_mesh* m, int mres, bool need32) {
         STDG_HIP(hipMalloc(&w.z, n * sizeof(double)));
         STDG_HIP(hipMalloc(&w.partial, sizeof(double) * NBLK * 208));
         STDG_HIP(hipMalloc(&w.scal, sizeof(double) * (S_COUNT + 4 * 256 + 208 * 208)));
-        STDG_HIP(hipHostMalloc(&w.hscal, sizeof(double) * 8));
+        STDG_HIP(hipHostMalloc(&w.hscal, sizeof(double) * (8 + 2 * TL_COUNT)));
     }
     if (need32) {
         // long enough for the run layout as well (padded to whole 64-element runs)
@@ -1088,8 +1162,11 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
                 c.n = n32;
                 c.run_layout = true;
                 c.op = o.method == STDG_CG ? 0 : 2;
-                status = cg<float>(c, w.b32, w.x32, w.r32, w.p32, w.q32, inner_abs / rn, o.max_iter - inner_total,
-                                   o.check_every, it, res);
+                status = cg_two_level(c)
+                             ? cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, inner_abs / rn,
+                                                  o.max_iter - inner_total, o.check_every, it, res)
+                             : cg<float>(c, w.b32, w.x32, w.r32, w.p32, w.q32, inner_abs / rn,
+                                         o.max_iter - inner_total, o.check_every, it, res);
                 c.n = n;
                 c.run_layout = false;
                 c.op = 0;
@@ -1099,8 +1176,21 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
             } else {
                 hipLaunchKernelGGL(k_d2f_scaled, dim3(gb), dim3(256), 0, c.s, w.r, w.b32, 1.0 / rn, n);
                 hipLaunchKernelGGL(k_fill<float>, dim3(gb), dim3(256), 0, c.s, w.x32, 0.0f, n);
-                status = run_krylov<float>(c, o.method, w.b32, w.x32, w.r32, w.p32, w.q32, w.V32, mres,
-                                           inner_abs / rn, o.max_iter - inner_total, o.check_every, it, res);
+                const bool time = o.method == STDG_CG_TIME;
+                if (time) c.op = 2;
+                const bool two = (time || o.method == STDG_CG) && cg_two_level(c);
+                if (two)
+                    status = cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, inner_abs / rn,
+                                                o.max_iter - inner_total, o.check_every, it, res);
+                c.op = 0;
+                if (two && time && status >= 0) {
+                    // correction (I (x) C^-1) w
+                    CK(time_mix_f32(m, m->d.Cinv32, w.x32, w.q32, c.s));
+                    hipLaunchKernelGGL(k_copy<float>, dim3(gb), dim3(256), 0, c.s, w.q32, w.x32, n);
+                }
+                if (!two)
+                    status = run_krylov<float>(c, o.method, w.b32, w.x32, w.r32, w.p32, w.q32, w.V32, mres,
+                                               inner_abs / rn, o.max_iter - inner_total, o.check_every, it, res);
                 inner_total += it;
                 if (status < 0) return status;
                 hipLaunchKernelGGL(k_add_f32, dim3(gb), dim3(256), 0, c.s, x, w.x32, rn, n);
