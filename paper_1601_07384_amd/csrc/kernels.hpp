@@ -82,6 +82,10 @@ int upload_own_inverse(stdg_mesh* m, const std::vector<double>& inv);
 hipError_t launch_cg_check_f32(const double* part, int64_t n_part, double* scal, int slot, hipStream_t s);
 hipError_t time_mix_f64(const stdg_mesh* m, const double* M, const double* x, double* y, hipStream_t s);
 hipError_t time_mix_f32(const stdg_mesh* m, const float* M, const float* x, float* y, hipStream_t s);
+int64_t visc_mfma_blocks(const stdg_mesh* m);
+bool visc_mfma_supported(const stdg_mesh* m);
+hipError_t visc_mfma(const stdg_mesh* m, bool pre, int dots, const double* x, double* y, const double* w, double* part,
+                     hipStream_t s);
 hipError_t launch_visc_apply(const stdg_mesh* m, const double* x, double* y, hipStream_t s);
 int model_predict(stdg_model* md, const stdg_mesh* m, const double* P, const double* Pm, const double* B,
                   double* x0, hipStream_t s, bool correction_only);

@@ -369,6 +369,7 @@ template <> struct Apply<double> {
     static hipError_t run(const Ctx& c, const double* x, double* y) {
         if (c.op == 0) return launch_apply_f64(c.m, x, y, c.s);
         if (c.op == 2) return launch_apply_f64_c(c.m, c.m->d.Cid, x, y, c.s);
+        if (c.op == 3 && visc_mfma_supported(c.m)) return visc_mfma(c.m, true, 0, x, y, nullptr, nullptr, c.s);
         if (c.op == 3) {
             const hipError_t e = launch_visc_apply(c.m, x, c.tmp, c.s);
             return e != hipSuccess ? e : launch_visc_precond(c.m, c.tmp, y, c.s);
@@ -833,16 +834,33 @@ int bicgstab(Ctx& c, const T* b, T* x, T* r, T* rh, T* p, T* v, T* s, T* t, doub
     res_out = std::sqrt(rr);
     if (!std::isfinite(res_out)) { set_error("non-finite residual in BiCGStab"); return STDG_ERR_NUMERIC; }
     if (res_out <= tol_abs) return STDG_OK;
+    // the preconditioned viscous operator on the matrix cores leaves the dot
+    // products of its result with it
+    const bool dots = std::is_same<T, double>::value && c.op == 3 && visc_mfma_supported(c.m) &&
+                      2 * visc_mfma_blocks(c.m) <= NBLK * 208;
+    const int nd = dots ? (int)visc_mfma_blocks(c.m) : NBLK;
     while (iters < max_it) {
         hipLaunchKernelGGL(k_bcg_p<T>, dim3(gb), dim3(256), 0, c.s, p, r, v, c.scal, n);
-        CK(Apply<T>::run(c, p, v)); c.applies++;
-        hipLaunchKernelGGL((k_dot<T, T>), dim3(NBLK), dim3(RT), 0, c.s, rh, v, n, c.partial);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, (int)S_BSIG,
+        if constexpr (std::is_same<T, double>::value) {
+            if (dots) CK(visc_mfma(c.m, true, 1, p, v, rh, c.partial, c.s));
+        }
+        if (!dots) {
+            CK(Apply<T>::run(c, p, v));
+            hipLaunchKernelGGL((k_dot<T, T>), dim3(NBLK), dim3(RT), 0, c.s, rh, v, n, c.partial);
+        }
+        c.applies++;
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, nd, c.scal, (int)S_BSIG,
                            (int)FIN_STORE);
         hipLaunchKernelGGL(k_bcg_s<T>, dim3(gb), dim3(256), 0, c.s, s, r, v, c.scal, n);
-        CK(Apply<T>::run(c, s, t)); c.applies++;
-        hipLaunchKernelGGL(k_dot2<T>, dim3(NBLK), dim3(RT), 0, c.s, t, s, n, c.partial);
-        hipLaunchKernelGGL(k_fin_multi, dim3(2), dim3(RT), 0, c.s, c.partial, NBLK, c.scal + S_BTS,
+        if constexpr (std::is_same<T, double>::value) {
+            if (dots) CK(visc_mfma(c.m, true, 2, s, t, nullptr, c.partial, c.s));
+        }
+        if (!dots) {
+            CK(Apply<T>::run(c, s, t));
+            hipLaunchKernelGGL(k_dot2<T>, dim3(NBLK), dim3(RT), 0, c.s, t, s, n, c.partial);
+        }
+        c.applies++;
+        hipLaunchKernelGGL(k_fin_multi, dim3(2), dim3(RT), 0, c.s, c.partial, nd, c.scal + S_BTS,
                            (double*)nullptr, 0.0);
         hipLaunchKernelGGL(k_bcg_xr<T>, dim3(NBLK), dim3(RT), 0, c.s, x, r, p, s, t, rh, c.scal, n, c.partial);
         hipLaunchKernelGGL(k_fin_multi, dim3(2), dim3(RT), 0, c.s, c.partial, NBLK, c.scal + S_BRHO,

@@ -638,6 +638,7 @@ static hipError_t launch_visc_ng(const stdg_mesh* m, const double* x, double* y,
 }
 
 hipError_t launch_visc_apply(const stdg_mesh* m, const double* x, double* y, hipStream_t s) {
+    if (visc_mfma_supported(m)) return visc_mfma(m, false, 0, x, y, nullptr, nullptr, s);
 #define STDG_VN(n, g) \
     if (m->N == n && m->G == g) return launch_visc_ng<n, g>(m, x, y, s);
     STDG_VN(4, 1) STDG_VN(4, 2) STDG_VN(4, 3) STDG_VN(4, 4) STDG_VN(4, 5)
