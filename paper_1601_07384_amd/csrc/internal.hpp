@@ -134,6 +134,7 @@ struct PicardDevice {
     int64_t* fr = nullptr;           // [F] right element (-1 boundary)
     int32_t* flf = nullptr;          // [F] left local face
     int32_t* frf = nullptr;          // [F] right local face
+    int32_t* face_groups = nullptr;  // [ceil(F / 64)][4] groups of 64 faces (rows_mfma.hip)
     double* work = nullptr;          // step workspace
     size_t work_len = 0;
     double* conv_tmp = nullptr;      // convection sums per time point [qt][3][E][N]

@@ -91,6 +91,14 @@ int model_predict(stdg_model* md, const stdg_mesh* m, const double* P, const dou
                   double* x0, hipStream_t s, bool correction_only);
 int device_dots(stdg_mesh* m, int k, const double* const* a, const double* const* b, int64_t n, hipStream_t s,
                 double* out);
+bool rows_mfma_supported(const stdg_mesh* m);
+hipError_t rows_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s);
+hipError_t rows_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0, int64_t f1,
+                       hipStream_t s);
+hipError_t rows_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s);
+hipError_t rows_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, double* b, hipStream_t s);
+hipError_t rows_visc_rhs(const stdg_mesh* m, const double* vprev, const double* ups, const double* lam,
+                         const double* vbc, double* rhs, hipStream_t s);
 bool fast_rows_supported(const stdg_mesh* m);
 hipError_t fast_convection(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s);
 hipError_t fast_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s);

@@ -85,4 +85,42 @@ template <int N, int T> __device__ inline void m64_stage(const double* __restric
     }
 }
 
+// Results of 16 consecutive entities (columns) back to memory: the wavefront's
+// rows [entity][time node][N] of one component are contiguous, so they pass
+// through its own LDS slice `buf` (16 G N doubles) and leave as 16-byte
+// stores of consecutive lanes; straight from the accumulators every store
+// instruction would touch 16 rows, 32 bytes each (goback, 663,552 elements,
+// p = 3: 465 -> 445 us, the preconditioned viscous operator 340 -> 317).  value(rg, a) is the lane's result row 4 rg + hi at
+// time node a; out(i, v) takes the two values at offset i of the component
+// (relative to the first entity), of which those below `count` exist.
+typedef double m64_d2u __attribute__((ext_vector_type(2), aligned(8)));   // rows start at any multiple of 8 bytes
+template <int N, int G, typename V, typename O>
+__device__ __forceinline__ void m64_flush(double* buf, int lane, int hi, int count, V&& value, O&& out) {
+    constexpr int NQ = M64<N>::NQ, TOT = 16 * G * N;
+    // (lanes of absent entities write too; their values are not read)
+    double* row = buf + (lane & 15) * (G * N);
+#pragma unroll
+    for (int a = 0; a < G; ++a)
+#pragma unroll
+        for (int rg = 0; rg < NQ; ++rg)
+            if (4 * rg + hi < N) row[a * N + 4 * rg + hi] = value(rg, a);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i0 = 0; i0 < TOT; i0 += 128) {
+        const int i = i0 + 2 * lane;
+        if (i < count) out(i, m64_d2u{buf[i], buf[i + 1 < TOT ? i + 1 : i]});
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// store of m64_flush's pair at y + i
+__device__ __forceinline__ void m64_put(double* y, int i, int count, m64_d2u v) {
+    if (i + 1 < count) *reinterpret_cast<m64_d2u*>(y + i) = v;
+    else y[i] = v.x;
+}
+
 }  // namespace stdg

@@ -1,0 +1,522 @@
+// Block-row kernels of the Picard step on the FP64 matrix cores (Sec. 2.6,
+// steps 1, 3, 4, 5, 6; eqs. average, goback, prevpress / A3_mod, A1_mod,
+// A2_mod): every output row of N coefficients is a sum of small N x N blocks
+// times gathered rows, the blocks shared by a geometry class (and local face).
+//
+// One workgroup takes 64 consecutive entities (elements, or faces, which are
+// sorted by the classes and local faces of their two sides).  When all 64
+// share their blocks, these are staged in LDS and four wavefronts take 16
+// entities each, their components and time nodes as further columns, so an
+// operand read from LDS feeds several matrix instructions and a row is read
+// with 16-byte loads (mfma64.hpp); otherwise (the groups where the class
+// changes, a few per class) the threads take one output value each.  They
+// replace, on meshes of mostly uniform groups, kernels with one output row
+// per thread, which read every row with a stride of N doubles between lanes.
+// What bounds them is the row traffic.  82,944 elements, p = 3, p_gamma = 1:
+// average 275 -> 76 us, goback 383 -> 170, right-hand side 266 -> 67;
+// 663,552 elements, p_gamma = 0: average 976 -> 291 us (0.96 GB), goback
+// 1,437 -> 357, gradient 912 -> 299, right-hand side 1,068 -> 273.
+
+#include "internal.hpp"
+#include "kernels.hpp"
+#include "mfma64.hpp"
+
+namespace stdg {
+namespace {
+
+constexpr int RT = 256;
+
+// wavefronts per SIMD to leave registers for: the kernels wait on rows, so
+// four where the accumulators allow it (663,552 elements, p = 3: goback 441 ->
+// 357 us, gradient 417 -> 299 together with the group records below; average,
+// whose four row sets fill more registers, 291 -> 309: it keeps two)
+template <int N, int G> constexpr int waves() {
+    return M64<N>::NQ * 3 * G <= 18 ? 4 : (M64<N>::NQ * G <= 25 ? 2 : 1);
+}
+
+// components (or directions) of one workgroup: all three while their
+// accumulators leave room for two wavefronts per SIMD
+template <int N, int G> constexpr int comps() { return M64<N>::NQ * 3 * G <= 48 ? 3 : 1; }
+
+template <int R, int C> __device__ inline void zero(double (&a)[R][C]) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < C; ++j) a[i][j] = 0.0;
+}
+
+// doubles of LDS: the staged blocks, and afterwards the four wavefronts'
+// output rows
+template <int N, int G, int BLOCKS> constexpr int lds_size() {
+    return BLOCKS * N * M64<N>::NP > 4 * 16 * G * N ? BLOCKS * N * M64<N>::NP : 4 * 16 * G * N;
+}
+
+// acc[rg][col0 + a] of the wavefront's entities first .. (those below end) to
+// the rows of y ([entity][G][N]) times scale(a); all wavefronts have passed a
+// barrier since they last read the blocks in `lds`
+template <int N, int G, int NC, typename S>
+__device__ __forceinline__ void put_rows(double* lds, int wave, int lane, int hi, double* __restrict__ y, int64_t first,
+                                         int64_t end, const double (&acc)[M64<N>::NQ][NC], int col0, S&& scale) {
+    const int64_t left = end - first;
+    if (left <= 0) return;
+    const int count = (int)(left < 16 ? left : 16) * G * N;
+    double* dst = y + first * G * N;
+    m64_flush<N, G>(lds + wave * 16 * G * N, lane, hi, count,
+                    [&](int rg, int a) { return scale(a) * acc[rg][col0 + a]; },
+                    [&](int i, m64_d2u v) { m64_put(dst, i, count, v); });
+}
+
+template <int N> __device__ inline double row_dot(const double* __restrict__ Bt, const double* __restrict__ x, int r) {
+    double s = 0.0;
+    for (int m = 0; m < N; ++m) s += Bt[m * N + r] * x[m];
+    return s;
+}
+
+// workgroup -> group, consecutive ones on one XCD
+__device__ inline uint32_t group_of() { return (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; }
+
+// Group of 64 faces (sorted by their sides): the block of the left and of the
+// right side (class 4 + local face; right -1 on the boundary), left -1 when
+// the group holds several.  One record instead of the chain face -> element ->
+// class at the head of every workgroup; the records are in the order of
+// their first left element, so that neighbouring groups of different sides
+// share their elements' rows while they are cached.
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+struct Lane {
+    int lane, wave, hi, lo;
+    __device__ Lane() {
+        lane = threadIdx.x & 63;
+        wave = threadIdx.x >> 6;
+        hi = lane >> 4;
+        lo = lane & 3;
+    }
+};
+
+// eq. average: vbar[c][i][a] = sum_f A_{i,f} vhat[c][face(i,f)][a]
+template <int N, int G>
+__global__ void __launch_bounds__(RT) kr_average(const double* __restrict__ At, const int32_t* __restrict__ cls,
+                                                 const int32_t* __restrict__ run_cls,
+                                                 const int64_t* __restrict__ tet_face, const double* __restrict__ vhat,
+                                                 double* __restrict__ vbar, int64_t E, int64_t F, uint32_t n_groups) {
+    constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
+    __shared__ double A[lds_size<N, G, 4>()];
+    const uint32_t g = group_of();
+    if (g >= n_groups) return;
+    const int c0 = blockIdx.y * CP, c = run_cls[g];
+    const int64_t e0 = (int64_t)g * 64;
+    if (c < 0) {
+        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
+            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
+            const int64_t i = e0 + t / (N * G * CP);
+            if (i >= E) break;
+            double s = 0.0;
+            for (int f = 0; f < 4; ++f)
+                s += row_dot<N>(At + ((int64_t)cls[i] * 4 + f) * N * N, vhat + ((cc * F + tet_face[4 * i + f]) * G + a) * N, r);
+            vbar[((cc * E + i) * G + a) * N + r] = s;
+        }
+        return;
+    }
+    m64_stage<N, RT>(At + (int64_t)c * 4 * N * N, A, 4);
+    __syncthreads();
+    const Lane l;
+    const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
+    const bool valid = i < E;
+    __amdgpu_buffer_rsrc_t rv[CP];
+#pragma unroll
+    for (int k = 0; k < CP; ++k) rv[k] = m64_rsrc(vhat + (c0 + k) * F * G * N, (uint32_t)(8 * F * G * N));
+    double acc[NQ][CP * G];
+    zero(acc);
+    int64_t face[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) face[f] = valid ? tet_face[4 * i + f] : -1;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        double b[CP * G][NQ];
+#pragma unroll
+        for (int k = 0; k < CP; ++k)
+#pragma unroll
+            for (int a = 0; a < G; ++a)
+                m64_load<N>(rv[k], valid ? (uint32_t)((face[f] * G + a) * N * 8) : M64_OOB, l.hi, b[k * G + a]);
+        m64_block<N, CP * G>(A + f * N * NP, b, l.lo, l.hi, acc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CP; ++k)
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, vbar + (c0 + k) * E * G * N, e0 + 16 * l.wave, E, acc, k * G,
+                       [](int) { return 1.0; });
+}
+
+// eq. goback on faces 0 .. f1: out[c][j][a] = GB_l vbar_l[a] + GB_r vbar_r[a]
+// (boundary faces: one side, from vbdry)
+template <int N, int G>
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_goback(const double* __restrict__ GBt, const int32_t* __restrict__ cls,
+                                                const int64_t* __restrict__ fl, const int32_t* __restrict__ flf,
+                                                const int64_t* __restrict__ fr, const int32_t* __restrict__ frf,
+                                                const double* __restrict__ vbar, const double* __restrict__ vbdry,
+                                                double* __restrict__ out, int64_t f1, int64_t F, int64_t E,
+                                                const i4* __restrict__ grp, uint32_t n_groups) {
+    constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
+    __shared__ double A[lds_size<N, G, 2>()];
+    const uint32_t gi = group_of();
+    if (gi >= n_groups) return;
+    const i4 g = grp[gi];
+    const int c0 = blockIdx.y * CP;
+    const int64_t j0 = (int64_t)g.x * 64, j1 = j0 + 63 < f1 ? j0 + 63 : f1 - 1;
+    if (j0 >= f1) return;
+    if (g.y < 0) {
+        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
+            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
+            const int64_t j = j0 + t / (N * G * CP);
+            if (j > j1) break;
+            const int64_t l = fl[j], rr = fr[j];
+            double s = row_dot<N>(GBt + ((int64_t)cls[l] * 4 + flf[j]) * N * N,
+                                  (rr >= 0 ? vbar : vbdry) + ((cc * E + l) * G + a) * N, r);
+            if (rr >= 0)
+                s += row_dot<N>(GBt + ((int64_t)cls[rr] * 4 + frf[j]) * N * N, vbar + ((cc * E + rr) * G + a) * N, r);
+            out[((cc * F + j) * G + a) * N + r] = s;
+        }
+        return;
+    }
+    const bool inner = g.z >= 0;
+    const Lane l;
+    const int64_t j = j0 + 16 * l.wave + (l.lane & 15);
+    const bool valid = j <= j1;
+    const double* src = inner ? vbar : vbdry;
+    double acc[NQ][CP * G];
+    zero(acc);
+    // the left rows are in flight while the blocks are staged
+    const int64_t side[2] = {valid ? fl[j] : -1, valid && inner ? fr[j] : -1};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (q == 1 && !inner) break;
+        double b[CP * G][NQ];
+#pragma unroll
+        for (int k = 0; k < CP; ++k) {
+            const __amdgpu_buffer_rsrc_t rv = m64_rsrc(src + (c0 + k) * E * G * N, (uint32_t)(8 * E * G * N));
+#pragma unroll
+            for (int a = 0; a < G; ++a)
+                m64_load<N>(rv, side[q] >= 0 ? (uint32_t)((side[q] * G + a) * N * 8) : M64_OOB, l.hi, b[k * G + a]);
+        }
+        if (q == 0) {
+            m64_stage<N, RT>(GBt + (int64_t)g.y * N * N, A, 1);
+            if (inner) m64_stage<N, RT>(GBt + (int64_t)g.z * N * N, A + N * NP, 1);
+            __syncthreads();
+        }
+        m64_block<N, CP * G>(A + q * N * NP, b, l.lo, l.hi, acc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CP; ++k)
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, out + (c0 + k) * F * G * N, j0 + 16 * l.wave, j1 + 1, acc, k * G,
+                       [](int) { return 1.0; });
+}
+
+// dual-grid pressure gradient: w[d][j][a] = dt sum_b TW[a][b] (US_{l,d} p_l[b] + UN_{l,d} p_r[b])
+template <int N, int G>
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_dualgrad(const double* __restrict__ USt, const double* __restrict__ UNt,
+                                                  const int32_t* __restrict__ cls, const int64_t* __restrict__ fl,
+                                                  const int32_t* __restrict__ flf, const int64_t* __restrict__ fr,
+                                                  const double* __restrict__ TW,
+                                                  const double* __restrict__ p, double dt, double* __restrict__ w,
+                                                  int64_t F, int64_t E, const i4* __restrict__ grp,
+                                                  uint32_t n_groups) {
+    constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
+    __shared__ double A[lds_size<N, G, 2 * CP>()];
+    const uint32_t gi = group_of();
+    if (gi >= n_groups) return;
+    const i4 g = grp[gi];
+    const int d0 = blockIdx.y * CP;
+    const int64_t j0 = (int64_t)g.x * 64, j1 = j0 + 63 < F ? j0 + 63 : F - 1;
+    if (g.y < 0) {
+        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
+            const int r = t % N, a = t / N % G, d = d0 + t / (N * G) % CP;
+            const int64_t j = j0 + t / (N * G * CP);
+            if (j > j1) break;
+            const int64_t l = fl[j], rr = fr[j], key = ((int64_t)cls[l] * 4 + flf[j]) * 3 + d;
+            double s = 0.0;
+            for (int b = 0; b < G; ++b) {
+                s += TW[a * G + b] * row_dot<N>(USt + key * N * N, p + (l * G + b) * N, r);
+                if (rr >= 0) s += TW[a * G + b] * row_dot<N>(UNt + key * N * N, p + (rr * G + b) * N, r);
+            }
+            w[((d * F + j) * G + a) * N + r] = dt * s;
+        }
+        return;
+    }
+    const bool inner = g.z >= 0;
+    const int64_t key = (int64_t)g.y * 3 + d0;
+    const Lane l;
+    const int64_t j = j0 + 16 * l.wave + (l.lane & 15);
+    const bool valid = j <= j1;
+    const __amdgpu_buffer_rsrc_t rp = m64_rsrc(p, (uint32_t)(8 * E * G * N));
+    // both sides' rows in flight while the blocks are staged
+    const int64_t side[2] = {valid ? fl[j] : -1, valid && inner ? fr[j] : -1};
+    double b[2][G][NQ];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int a = 0; a < G; ++a)
+            m64_load<N>(rp, side[q] >= 0 ? (uint32_t)((side[q] * G + a) * N * 8) : M64_OOB, l.hi, b[q][a]);
+    m64_stage<N, RT>(USt + key * N * N, A, CP);
+    if (inner) m64_stage<N, RT>(UNt + key * N * N, A + CP * N * NP, CP);
+    double acc[CP][NQ][G];
+#pragma unroll
+    for (int d = 0; d < CP; ++d) zero(acc[d]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (q == 1 && !inner) break;
+        double bt[G][NQ];
+#pragma unroll
+        for (int a = 0; a < G; ++a)
+#pragma unroll
+            for (int t = 0; t < NQ; ++t) {
+                double s = 0.0;
+#pragma unroll
+                for (int bb = 0; bb < G; ++bb) s += TW[a * G + bb] * b[q][bb][t];
+                bt[a][t] = s;
+            }
+#pragma unroll
+        for (int d = 0; d < CP; ++d) m64_block<N, G>(A + (q * CP + d) * N * NP, bt, l.lo, l.hi, acc[d]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < CP; ++d)
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, w + (d0 + d) * F * G * N, j0 + 16 * l.wave, j1 + 1, acc[d], 0,
+                       [dt](int) { return dt; });
+}
+
+// pressure right-hand side: b[i][a] = dt W_a sum_{f,d} Q^T_{i,f,d} Fv[d][face][a]
+template <int N, int G>
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __restrict__ QTt, const int32_t* __restrict__ cls,
+                                             const int32_t* __restrict__ run_cls, const int64_t* __restrict__ tet_face,
+                                             const double* __restrict__ W, const double* __restrict__ Fv, double dt,
+                                             double* __restrict__ out, int64_t E, int64_t F, uint32_t n_groups) {
+    constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP;
+    __shared__ double A[lds_size<N, G, 3>()];
+    const uint32_t g = group_of();
+    if (g >= n_groups) return;
+    const int c = run_cls[g];
+    const int64_t e0 = (int64_t)g * 64;
+    if (c < 0) {
+        for (int t = threadIdx.x; t < 64 * G * N; t += RT) {
+            const int r = t % N, a = t / N % G;
+            const int64_t i = e0 + t / (N * G);
+            if (i >= E) break;
+            double s = 0.0;
+            for (int f = 0; f < 4; ++f)
+                for (int d = 0; d < 3; ++d)
+                    s += row_dot<N>(QTt + (((int64_t)cls[i] * 4 + f) * 3 + d) * N * N,
+                                    Fv + ((d * F + tet_face[4 * i + f]) * G + a) * N, r);
+            out[(i * G + a) * N + r] = dt * W[a] * s;
+        }
+        return;
+    }
+    const Lane l;
+    const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
+    const bool valid = i < E;
+    __amdgpu_buffer_rsrc_t rv[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) rv[d] = m64_rsrc(Fv + d * F * G * N, (uint32_t)(8 * F * G * N));
+    double acc[NQ][G];
+    zero(acc);
+#pragma unroll 1
+    for (int f = 0; f < 4; ++f) {
+        double b[3][G][NQ];
+        const int64_t j = valid ? tet_face[4 * i + f] : -1;
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int a = 0; a < G; ++a)
+                m64_load<N>(rv[d], valid ? (uint32_t)((j * G + a) * N * 8) : M64_OOB, l.hi, b[d][a]);
+        __syncthreads();
+        m64_stage<N, RT>(QTt + ((int64_t)c * 4 + f) * 3 * N * N, A, 3);
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 3; ++d) m64_block<N, G>(A + d * N * NP, b[d], l.lo, l.hi, acc);
+    }
+    __syncthreads();
+    put_rows<N, G>(A, l.wave, l.lane, l.hi, out, e0 + 16 * l.wave, E, acc, 0, [&](int a) { return dt * W[a]; });
+}
+
+// viscous right-hand side: M (sum_b g0g1[a][b] vprev_b - T[a][b] lam_b) - ups_a - nu dt W_a sum_{bdry f} BB_f vbc
+template <int N, int G>
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double* __restrict__ MIt, const double* __restrict__ BBt,
+                                                  const int32_t* __restrict__ cls, const int32_t* __restrict__ run_cls,
+                                                  const int32_t* __restrict__ nbr, const int64_t* __restrict__ tet_face,
+                                                  const double* __restrict__ g0g1, const double* __restrict__ Tm,
+                                                  const double* __restrict__ W, const double* __restrict__ vprev,
+                                                  const double* __restrict__ ups, const double* __restrict__ lam,
+                                                  const double* __restrict__ vbc, double nu_dt,
+                                                  double* __restrict__ rhs, int64_t E, int64_t F, uint32_t n_groups) {
+    constexpr int NQ = M64<N>::NQ, CP = comps<N, G>();
+    __shared__ double A[lds_size<N, G, 1>()];
+    const uint32_t g = group_of();
+    if (g >= n_groups) return;
+    const int c0 = blockIdx.y * CP, c = run_cls[g];
+    const int64_t e0 = (int64_t)g * 64;
+    if (c < 0) {
+        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
+            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
+            const int64_t i = e0 + t / (N * G * CP);
+            if (i >= E) break;
+            const double* M = MIt + (int64_t)cls[i] * N * N;
+            double s = -ups[((cc * E + i) * G + a) * N + r];
+            for (int b = 0; b < G; ++b)
+                s += g0g1[a * G + b] * row_dot<N>(M, vprev + ((cc * E + i) * G + b) * N, r) -
+                     Tm[a * G + b] * row_dot<N>(M, lam + ((cc * E + i) * G + b) * N, r);
+            for (int f = 0; f < 4; ++f)
+                if (nbr[4 * i + f] < 0)
+                    s -= nu_dt * W[a] * row_dot<N>(BBt + ((int64_t)cls[i] * 4 + f) * N * N,
+                                                   vbc + ((cc * F + tet_face[4 * i + f]) * G + a) * N, r);
+            rhs[((cc * E + i) * G + a) * N + r] = s;
+        }
+        return;
+    }
+    m64_stage<N, RT>(MIt + (int64_t)c * N * N, A, 1);
+    const Lane l;
+    const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
+    const bool valid = i < E;
+    double acc[NQ][CP * G];
+    // start from -ups in the rows this lane will store
+#pragma unroll
+    for (int rg = 0; rg < NQ; ++rg)
+#pragma unroll
+        for (int k = 0; k < CP; ++k)
+#pragma unroll
+            for (int a = 0; a < G; ++a)
+                acc[rg][k * G + a] = valid && 4 * rg + l.hi < N
+                                         ? -ups[(((c0 + k) * E + i) * G + a) * N + 4 * rg + l.hi] : 0.0;
+    double bt[CP * G][NQ];
+#pragma unroll
+    for (int k = 0; k < CP; ++k) {
+        const __amdgpu_buffer_rsrc_t rp = m64_rsrc(vprev + (c0 + k) * E * G * N, (uint32_t)(8 * E * G * N));
+        const __amdgpu_buffer_rsrc_t rl = m64_rsrc(lam + (c0 + k) * E * G * N, (uint32_t)(8 * E * G * N));
+#pragma unroll
+        for (int a = 0; a < G; ++a)
+#pragma unroll
+            for (int t = 0; t < NQ; ++t) bt[k * G + a][t] = 0.0;
+#pragma unroll
+        for (int b = 0; b < G; ++b) {
+            double v[NQ], u[NQ];
+            const uint32_t off = valid ? (uint32_t)((i * G + b) * N * 8) : M64_OOB;
+            m64_load<N>(rp, off, l.hi, v);
+            m64_load<N>(rl, off, l.hi, u);
+#pragma unroll
+            for (int a = 0; a < G; ++a)
+#pragma unroll
+                for (int t = 0; t < NQ; ++t) bt[k * G + a][t] += g0g1[a * G + b] * v[t] - Tm[a * G + b] * u[t];
+        }
+    }
+    __syncthreads();
+    m64_block<N, CP * G>(A, bt, l.lo, l.hi, acc);
+    // boundary faces (the same ones on every element of a class)
+    for (int f = 0; f < 4; ++f) {
+        if (nbr[4 * e0 + f] >= 0) continue;
+        __syncthreads();
+        m64_stage<N, RT>(BBt + ((int64_t)c * 4 + f) * N * N, A, 1);
+        const int64_t j = valid ? tet_face[4 * i + f] : -1;
+        double b[CP * G][NQ];
+#pragma unroll
+        for (int k = 0; k < CP; ++k) {
+            const __amdgpu_buffer_rsrc_t rb = m64_rsrc(vbc + (c0 + k) * F * G * N, (uint32_t)(8 * F * G * N));
+#pragma unroll
+            for (int a = 0; a < G; ++a) {
+                m64_load<N>(rb, valid ? (uint32_t)((j * G + a) * N * 8) : M64_OOB, l.hi, b[k * G + a]);
+#pragma unroll
+                for (int t = 0; t < NQ; ++t) b[k * G + a][t] *= -nu_dt * W[a];
+            }
+        }
+        __syncthreads();
+        m64_block<N, CP * G>(A, b, l.lo, l.hi, acc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CP; ++k)
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, rhs + (c0 + k) * E * G * N, e0 + 16 * l.wave, E, acc, k * G,
+                       [](int) { return 1.0; });
+}
+
+inline uint32_t groups(int64_t n) { return (uint32_t)((n + 63) / 64); }
+inline unsigned blocks(int64_t n) { return (unsigned)((groups(n) + 7) / 8 * 8); }
+
+}  // namespace
+
+// Meshes whose classes hold a wavefront of elements on average, with the runs
+// of several classes (and with them the face groups) a quarter at most, and
+// every component within the 2 GiB of a buffer offset.
+bool rows_mfma_supported(const stdg_mesh* m) {
+    const int64_t runs = (m->E + 63) / 64, F = (int64_t)m->faces.size();
+    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && (int64_t)m->n_classes * 64 <= m->E &&
+           4 * m->d.n_mixed_runs <= runs && 8 * F * m->Nst < ((int64_t)1 << 31);
+}
+
+#define STDG_ROWS(CALL)                                                                     \
+    STDG_NG(CALL, 4, 1) STDG_NG(CALL, 4, 2) STDG_NG(CALL, 4, 3) STDG_NG(CALL, 4, 4)          \
+    STDG_NG(CALL, 4, 5) STDG_NG(CALL, 10, 1) STDG_NG(CALL, 10, 2) STDG_NG(CALL, 10, 3)       \
+    STDG_NG(CALL, 10, 4) STDG_NG(CALL, 10, 5) STDG_NG(CALL, 20, 1) STDG_NG(CALL, 20, 2)      \
+    STDG_NG(CALL, 20, 3) STDG_NG(CALL, 20, 4) STDG_NG(CALL, 20, 5) STDG_NG(CALL, 35, 1)      \
+    STDG_NG(CALL, 35, 2) STDG_NG(CALL, 35, 3) STDG_NG(CALL, 35, 4) STDG_NG(CALL, 35, 5)      \
+    return hipErrorInvalidValue;
+#define STDG_NG(CALL, n, g)           \
+    if (m->N == n && m->G == g) {     \
+        CALL(n, g);                   \
+        return hipGetLastError();     \
+    }
+
+hipError_t rows_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s) {
+    const int64_t E = m->E, F = (int64_t)m->faces.size();
+#define STDG_CALL(n, g)                                                                                           \
+    hipLaunchKernelGGL((kr_average<n, g>), dim3(blocks(E), 3 / comps<n, g>()), dim3(RT), 0, s, m->pd.At, m->d.cls, \
+                       m->d.run_cls, m->pd.tet_face, vhat, vbar, E, F, groups(E))
+    STDG_ROWS(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t rows_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0, int64_t f1,
+                       hipStream_t s) {
+    if (f1 <= f0) return hipSuccess;
+    const PicardDevice& d = m->pd;
+    const int64_t F = (int64_t)m->faces.size();
+    // (the records list all groups from face 0: those past f1 return; the
+    // boundary faces alone, f0 > 0, are the register kernel's)
+    if (f0 != 0) return hipErrorNotSupported;
+#define STDG_CALL(n, g)                                                                                               \
+    hipLaunchKernelGGL((kr_goback<n, g>), dim3(blocks(F), 3 / comps<n, g>()), dim3(RT), 0, s, d.GBt, m->d.cls,   \
+                       d.fl, d.flf, d.fr, d.frf, vbar, vbdry, out, f1, F, m->E, (const i4*)d.face_groups, groups(F))
+    STDG_ROWS(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t rows_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s) {
+    const PicardDevice& d = m->pd;
+    const int64_t F = (int64_t)m->faces.size();
+#define STDG_CALL(n, g)                                                                                             \
+    hipLaunchKernelGGL((kr_dualgrad<n, g>), dim3(blocks(F), 3 / comps<n, g>()), dim3(RT), 0, s, d.USt, d.UNt,        \
+                       m->d.cls, d.fl, d.flf, d.fr, d.TW, p, dt, w, F, m->E, (const i4*)d.face_groups, groups(F))
+    STDG_ROWS(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t rows_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, double* b, hipStream_t s) {
+    const int64_t E = m->E, F = (int64_t)m->faces.size();
+#define STDG_CALL(n, g)                                                                                          \
+    hipLaunchKernelGGL((kr_rhs<n, g>), dim3(blocks(E)), dim3(RT), 0, s, m->pd.QTt, m->d.cls, m->d.run_cls,        \
+                       m->pd.tet_face, m->pd.W, Fv, dt, b, E, F, groups(E))
+    STDG_ROWS(STDG_CALL)
+#undef STDG_CALL
+}
+
+hipError_t rows_visc_rhs(const stdg_mesh* m, const double* vprev, const double* ups, const double* lam,
+                         const double* vbc, double* rhs, hipStream_t s) {
+    const PicardDevice& d = m->pd;
+    const int64_t E = m->E, F = (int64_t)m->faces.size();
+#define STDG_CALL(n, g)                                                                                            \
+    hipLaunchKernelGGL((kr_visc_rhs<n, g>), dim3(blocks(E), 3 / comps<n, g>()), dim3(RT), 0, s, d.MIt, d.BBt,       \
+                       m->d.cls, m->d.run_cls, m->d.nbr, d.tet_face, d.g0g1, d.Tm, d.W, vprev, ups, lam, vbc,      \
+                       m->cfg.nu * m->cfg.dt, rhs, E, F, groups(E))
+    STDG_ROWS(STDG_CALL)
+#undef STDG_CALL
+}
+
+}  // namespace stdg

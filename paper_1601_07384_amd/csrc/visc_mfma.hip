@@ -13,8 +13,8 @@
 // the row traffic (x of five elements per element through the caches) beside
 // 14 N^2 flops a column.  663,552 elements, p = 3, p_gamma = 0: 1,005 us for
 // the operator, the block-Jacobi and the dot kernel with one thread per row,
-// 338 us here (373 with the dot against a third vector); 196,608, p = 2,
-// p_gamma = 1: 281 -> 101 (114) us.
+// 317 us here (385 with the dot against a third vector); 196,608, p = 2,
+// p_gamma = 1: 281 -> 97 (117) us.
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -36,7 +36,8 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
                                                   double* __restrict__ y, const double* w, double* __restrict__ part,
                                                   int64_t E, uint32_t n_runs, uint32_t xbytes) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, NC = 3 * G;
-    __shared__ double A[6 * N * NP];
+    static_assert((N * G) % 2 == 0, "rows leave two values at a time");
+    __shared__ double A[6 * N * NP > 64 * G * N ? 6 * N * NP : 64 * G * N];
     __shared__ double Dl[PRE ? G * NP * G * NP : 1];
     __shared__ double red[VT / 64];
     const uint32_t run = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
@@ -131,22 +132,26 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
                         }
                 }
         }
-        if (valid)
+        // out through the blocks' LDS, the dots beside the stores
+        __syncthreads();
+        const int64_t first = (int64_t)run * 64 + 16 * wave, left = E - first;
+        const int count = left <= 0 ? 0 : (int)(left < 16 ? left : 16) * G * N;
+        if (count > 0)
 #pragma unroll
-            for (int rg = 0; rg < NQ; ++rg) {
-                const int row = 4 * rg + hi;
-                if (row < N)
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) {
-                        const int64_t at = (q / G) * cs + (e * G + q % G) * N + row;
-                        const double v = PRE ? z[rg][q] : acc[rg][q];
-                        y[at] = v;
-                        if (DOTS == 1) d0 += w[at] * v;
-                        if (DOTS == 2) {
-                            d0 += x[at] * v;
-                            d1 += v * v;
+            for (int cc = 0; cc < 3; ++cc) {
+                const int64_t at = cc * cs + first * G * N;
+                m64_flush<N, G>(
+                    A + wave * 16 * G * N, lane, hi, count,
+                    [&](int rg, int a) { return PRE ? z[rg][cc * G + a] : acc[rg][cc * G + a]; },
+                    [&](int i, m64_d2u v) {
+                        m64_put(y + at, i, count, v);
+                        if (DOTS >= 1) {
+                            // (an even number of values: N G is even)
+                            const m64_d2u u = *reinterpret_cast<const m64_d2u*>((DOTS == 1 ? w : x) + at + i);
+                            d0 += u.x * v.x + u.y * v.y;
+                            if (DOTS == 2) d1 += v.x * v.x + v.y * v.y;
                         }
-                    }
+                    });
             }
     }
     if (DOTS >= 1) {
