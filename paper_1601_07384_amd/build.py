@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstdg.so")
 SOURCES = ["fem.cpp", "mesh.cpp", "picard_tables.cpp", "capi.cpp", "apply.hip", "krylov.hip",
            "picard.hip", "mlp.hip", "cg_fused.hip", "cg_lane.hip", "cg_elem.hip", "cg_coarse.hip",
-           "picard_fast.hip", "visc_mfma.hip", "rows_mfma.hip"]
+           "picard_fast.hip", "visc_mfma.hip", "rows_mfma.hip", "conv_mfma.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fopenmp",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

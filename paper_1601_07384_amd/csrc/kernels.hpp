@@ -100,6 +100,7 @@ hipError_t rows_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, do
 hipError_t rows_visc_rhs(const stdg_mesh* m, const double* vprev, const double* ups, const double* lam,
                          const double* vbc, double* rhs, hipStream_t s);
 bool fast_rows_supported(const stdg_mesh* m);
+hipError_t conv_mfma(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s);
 hipError_t fast_convection(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s);
 hipError_t fast_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s);
 hipError_t fast_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0,

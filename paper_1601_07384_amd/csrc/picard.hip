@@ -552,7 +552,8 @@ hipError_t launch_conv_ng(const stdg_mesh* m, const double* vbar, const double* 
 hipError_t launch_convection(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups,
                              hipStream_t s) {
     {
-        const hipError_t e = fast_convection(m, vbar, vbc, ups, s);
+        hipError_t e = conv_mfma(m, vbar, vbc, ups, s);
+        if (e == hipErrorNotSupported) e = fast_convection(m, vbar, vbc, ups, s);
         if (e != hipErrorNotSupported) return e;
     }
 #define STDG_CV(n, g) \
