@@ -38,7 +38,6 @@ struct stdg_model {
     void* grad = nullptr;
     void* mom1 = nullptr;
     void* mom2 = nullptr;
-    void* one = nullptr;        // a single 1 (ones row for bias gradients)
     void* F = nullptr;          // [batch][nin]
     void* Z1 = nullptr;         // [batch][hid]
     void* H1 = nullptr;
@@ -48,7 +47,7 @@ struct stdg_model {
     void* dY = nullptr;
     void* dZ2 = nullptr;        // [batch][hid]
     void* dZ1 = nullptr;
-    void* part = nullptr;       // split-K partials [KSPLIT][max block]
+    void* part = nullptr;       // split-K partials of the gradient [KSPLIT][np]
     double* lpart = nullptr;    // loss partials
     double* lbatch = nullptr;   // per-batch loss
     int64_t lbatch_n = 0;
@@ -92,48 +91,108 @@ __device__ inline float sig(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 enum { EPI_STORE = 0, EPI_BIAS_ACT = 1, EPI_BIAS = 2, EPI_DACT = 3 };
 
+// Four consecutive k (or m / n) values of an operand; the vector load where
+// `vec` (wavefront-uniform: unit stride, multiples of four, 16-byte aligned)
+// holds, else one at a time; zeros past the end.
+template <typename T> struct Quad { T v[4]; };
+template <typename T>
+__device__ inline Quad<T> load4(const T* __restrict__ p, int64_t step, int left, bool vec) {
+    typedef T V4 __attribute__((ext_vector_type(4)));
+    Quad<T> q;
+    if (vec && left >= 4) {
+        const V4 t = *reinterpret_cast<const V4*>(p);
+        q.v[0] = t.x; q.v[1] = t.y; q.v[2] = t.z; q.v[3] = t.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q.v[i] = i < left ? p[i * step] : T(0);
+    }
+    return q;
+}
+
 // C = op(A) op(B) over the k-slice blockIdx.z, A(m,k) = A[m*sam + k*sak],
 // B(k,n) = B[k*sbk + n*sbn].  64x64 tile per 256-thread block, each wave a
-// 32x32 quarter as 2x2 MFMA 16x16x4 tiles; k staged 16 at a time in LDS.
+// 32x32 quarter as 2x2 MFMA 16x16x4 tiles; KB contraction steps at a time in
+// LDS, the next ones already in flight to registers while the matrix cores
+// work, in loads of four along the operand's contiguous direction (`va`, `vb`:
+// see load4).  With `ones` the last row of A is not read but all ones: the
+// weight gradient's extra row is then the bias gradient.
 // MFMA 16x16x4 operand layout: lane l holds A[l%16][l/16] and B[l/16][l%16];
 // result register r of lane l is D[MF<T>::row(l, r)][l%16] (the FP64 and
 // FP32 instructions interleave the rows differently).
-// Epilogues: STORE (slice z written at C + z*M*ldc), BIAS_ACT (Zout = acc +
+// Epilogues: STORE (slice z written at C + z*cstride), BIAS_ACT (Zout = acc +
 // bias, C = silu), BIAS (C = acc + bias), DACT (C = acc * silu'(Zin)).
-template <typename T, int EPI>
+// 24,576 rows, 224 -> 128 -> 128 -> 20 units: first forward product 43 -> 23 us,
+// data gradients 24 -> 16, last forward product 25 -> 11, weight and bias
+// gradients (six products and their sums before, three and one now) 482 -> 87.
+// AK, BK: the operand is contiguous along k
+template <typename T, int EPI, bool AK, bool BK>
 __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int kchunk, const T* __restrict__ A, int64_t sam,
-                                              int64_t sak, const T* __restrict__ B, int64_t sbk, int64_t sbn,
-                                              T* __restrict__ C, int64_t ldc, const T* __restrict__ bias,
-                                              T* __restrict__ Zout, const T* __restrict__ Zin) {
-    __shared__ T As[16][65];
-    __shared__ T Bs[16][65];
+                                              int64_t sak, int va, int ones, const T* __restrict__ B, int64_t sbk,
+                                              int64_t sbn, int vb, T* __restrict__ C, int64_t ldc, int64_t cstride,
+                                              const T* __restrict__ bias, T* __restrict__ Zout,
+                                              const T* __restrict__ Zin) {
+    constexpr int KB = sizeof(T) == 4 ? 32 : 16;
+    constexpr int NQ = 64 * KB / 4 / 256;            // quads of an operand per thread
+    __shared__ T As[KB][65];
+    __shared__ T Bs[KB][65];
     using V = typename MF<T>::V;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
     const int kb = blockIdx.z * kchunk;
     const int ke = min(K, kb + kchunk);
     const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+    constexpr bool ak = AK, bk = BK;
     V acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = V{0, 0, 0, 0};
-    for (int k0 = kb; k0 < ke; k0 += 16) {
-        for (int e = tid; e < 1024; e += 256) {
-            int mm, kk;
-            if (sak == 1) { kk = e & 15; mm = e >> 4; } else { mm = e & 63; kk = e >> 6; }
-            const int gm = m0 + mm, gk = k0 + kk;
-            As[kk][mm] = (gm < M && gk < ke) ? A[(int64_t)gm * sam + (int64_t)gk * sak] : T(0);
+    Quad<T> qa[NQ], qb[NQ];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const int e = tid + 256 * j;
+            const int mm = ak ? e / (KB / 4) : e % 16 * 4, ka = ak ? e % (KB / 4) * 4 : e / 16;
+            const int gm = m0 + mm, gka = k0 + ka;
+            if (ak) {
+                qa[j] = gm < M - ones ? load4(A + (int64_t)gm * sam + gka, 1, ke - gka, va)
+                                      : load4<T>(nullptr, 0, 0, false);
+                if (ones && gm == M - 1)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) qa[j].v[i] = gka + i < ke ? T(1) : T(0);
+            } else {
+                qa[j] = gka < ke ? load4(A + (int64_t)gm * sam + (int64_t)gka * sak, sam, M - ones - gm, va)
+                                 : load4<T>(nullptr, 0, 0, false);
+                if (ones && gka < ke)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (gm + i == M - 1) qa[j].v[i] = T(1);
+            }
+            const int nn = bk ? e / (KB / 4) : e % 16 * 4, kk = bk ? e % (KB / 4) * 4 : e / 16;
+            const int gn = n0 + nn, gkb = k0 + kk;
+            if (bk) qb[j] = gn < N ? load4(B + gkb + (int64_t)gn * sbn, 1, ke - gkb, vb) : load4<T>(nullptr, 0, 0, false);
+            else qb[j] = gkb < ke ? load4(B + (int64_t)gkb * sbk + (int64_t)gn * sbn, sbn, N - gn, vb)
+                                  : load4<T>(nullptr, 0, 0, false);
         }
-        for (int e = tid; e < 1024; e += 256) {
-            int nn, kk;
-            if (sbn == 1) { nn = e & 63; kk = e >> 6; } else { kk = e & 15; nn = e >> 4; }
-            const int gn = n0 + nn, gk = k0 + kk;
-            Bs[kk][nn] = (gn < N && gk < ke) ? B[(int64_t)gk * sbk + (int64_t)gn * sbn] : T(0);
-        }
+    };
+    fetch(kb);
+    for (int k0 = kb; k0 < ke; k0 += KB) {
         __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < 16; kk += 4) {
+        for (int j = 0; j < NQ; ++j) {
+            const int e = tid + 256 * j;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (ak) As[e % (KB / 4) * 4 + i][e / (KB / 4)] = qa[j].v[i];
+                else As[e / 16][e % 16 * 4 + i] = qa[j].v[i];
+                if (bk) Bs[e % (KB / 4) * 4 + i][e / (KB / 4)] = qb[j].v[i];
+                else Bs[e / 16][e % 16 * 4 + i] = qb[j].v[i];
+            }
+        }
+        __syncthreads();
+        if (k0 + KB < ke) fetch(k0 + KB);
+#pragma unroll
+        for (int kk = 0; kk < KB; kk += 4) {
             T a[2], b[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) a[i] = As[kk + (lane >> 4)][wm + i * 16 + (lane & 15)];
@@ -144,9 +203,8 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int kchunk, c
 #pragma unroll
                 for (int j = 0; j < 2; ++j) acc[i][j] = MF<T>::op(a[i], b[j], acc[i][j]);
         }
-        __syncthreads();
     }
-    T* Cz = C + (int64_t)blockIdx.z * M * ldc;
+    T* Cz = C + (int64_t)blockIdx.z * cstride;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -174,48 +232,63 @@ __global__ void __launch_bounds__(256) k_gemm(int M, int N, int K, int kchunk, c
             }
 }
 
-// out[t] = sum_z part[z * count + t], z in order (deterministic).
+// out[t] = sum_z part[z * count + t] over the nz slices that hold t (nz1 up to
+// n1, nz2 up to n2, nz3 after), z in order (deterministic)
 template <typename T>
-__global__ void k_sum_slices(const T* __restrict__ part, int nz, int64_t count, T* __restrict__ out) {
+__global__ void k_sum_slices(const T* __restrict__ part, int nz1, int64_t n1, int nz2, int64_t n2, int nz3,
+                             int64_t count, T* __restrict__ out) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= count) return;
+    const int nz = t < n1 ? nz1 : (t < n2 ? nz2 : nz3);
     T s = 0;
+#pragma unroll 8
     for (int z = 0; z < nz; ++z) s += part[(int64_t)z * count + t];
     out[t] = s;
 }
 
 // Feature rows.  Row r is sample q = idx[r] (or r + row0 without idx): step
 // s = q / E, element i = q % E.  scales[3 s + {0,1,2}] = s_P, s_D, s_B.
+// FR rows per workgroup: the 64-bit divisions once per row, 32-bit ones within
+// them (24,576 rows of 224: 30.8 -> 27.9 us).
+constexpr int FR = 8;
 template <typename T>
-__global__ void k_features(const double* __restrict__ P, const double* __restrict__ Pm,
-                           const double* __restrict__ Bv, const int32_t* __restrict__ nbr,
-                           const int64_t* __restrict__ idx, int64_t row0, int64_t n, int64_t E, int nst,
-                           const double* __restrict__ scales, T* __restrict__ F) {
-    const int nin = 11 * nst + 4;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * nin) return;
-    const int64_t row = t / nin;
-    const int f = (int)(t % nin);
-    const int64_t q = idx ? idx[row] : row + row0;
-    const int64_t s = q / E, i = q % E;
-    const int64_t base = s * E * nst;
-    double v;
-    if (f < 10 * nst) {
-        const int slot = (f / nst) % 5, c = f % nst;
-        const int64_t k = slot == 0 ? i : (int64_t)nbr[4 * i + slot - 1];
-        if (k < 0) {
-            v = 0.0;
-        } else if (f < 5 * nst) {
-            v = P[base + k * nst + c] / scales[3 * s];
-        } else {
-            v = (P[base + k * nst + c] - Pm[base + k * nst + c]) / scales[3 * s + 1];
-        }
-    } else if (f < 11 * nst) {
-        v = Bv[base + i * nst + (f - 10 * nst)] / scales[3 * s + 2];
-    } else {
-        v = nbr[4 * i + (f - 11 * nst)] >= 0 ? 1.0 : 0.0;
+__global__ void __launch_bounds__(256) k_features(const double* __restrict__ P, const double* __restrict__ Pm,
+                                                  const double* __restrict__ Bv, const int32_t* __restrict__ nbr,
+                                                  const int64_t* __restrict__ idx, int64_t row0, int64_t n, int64_t E,
+                                                  int nst, const double* __restrict__ scales, T* __restrict__ F) {
+    const unsigned nin = 11 * nst + 4;
+    __shared__ int64_t step[FR], elem[FR];
+    if (threadIdx.x < FR) {
+        const int64_t row = (int64_t)blockIdx.x * FR + threadIdx.x;
+        const int64_t q = row >= n ? 0 : (idx ? idx[row] : row + row0);
+        step[threadIdx.x] = q / E;
+        elem[threadIdx.x] = q % E;
     }
-    F[t] = (T)v;
+    __syncthreads();
+    for (unsigned t = threadIdx.x; t < FR * nin; t += 256) {
+        const unsigned rr = t / nin, f = t - rr * nin;
+        const int64_t row = (int64_t)blockIdx.x * FR + rr;
+        if (row >= n) return;
+        const int64_t s = step[rr], i = elem[rr];
+        const int64_t base = s * E * nst;
+        double v;
+        if (f < 10u * nst) {
+            const unsigned g = f / (unsigned)nst, slot = g % 5, c = f - g * nst;
+            const int64_t k = slot == 0 ? i : (int64_t)nbr[4 * i + slot - 1];
+            if (k < 0) {
+                v = 0.0;
+            } else if (g < 5) {
+                v = P[base + k * nst + c] / scales[3 * s];
+            } else {
+                v = (P[base + k * nst + c] - Pm[base + k * nst + c]) / scales[3 * s + 1];
+            }
+        } else if (f < 11u * nst) {
+            v = Bv[base + i * nst + (f - 10 * nst)] / scales[3 * s + 2];
+        } else {
+            v = nbr[4 * i + (f - 11 * nst)] >= 0 ? 1.0 : 0.0;
+        }
+        F[row * nin + f] = (T)v;
+    }
 }
 
 // Block partial sums of squares of P, P - Pm and B over one step's vector.
@@ -367,33 +440,40 @@ inline unsigned nb256(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + 25
 
 #define MCK(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) { set_error(std::string(#x) + ": " + hipGetErrorString(e_)); return STDG_ERR_DEVICE; } } while (0)
 
+// whether loads of four along the operand's unit-stride direction are aligned
+template <typename T> int quads(const T* p, int64_t s0, int64_t s1) {
+    return (s0 == 1 || s1 == 1) && (s0 == 1 ? s1 : s0) % 4 == 0 && (uintptr_t)p % (4 * sizeof(T)) == 0;
+}
+
 template <typename T, int EPI>
-hipError_t gemm(hipStream_t s, int M, int N, int K, int nz, const T* A, int64_t sam, int64_t sak, const T* B,
-                int64_t sbk, int64_t sbn, T* C, int64_t ldc, const T* bias = nullptr, T* Zout = nullptr,
-                const T* Zin = nullptr) {
-    int kchunk = (K + nz - 1) / nz;
-    kchunk = (kchunk + 15) / 16 * 16;
-    nz = (K + kchunk - 1) / kchunk;
-    if (nz < 1) nz = 1;
-    dim3 grid((M + 63) / 64, (N + 63) / 64, nz);
-    hipLaunchKernelGGL((k_gemm<T, EPI>), grid, dim3(256), 0, s, M, N, K, kchunk, A, sam, sak, B, sbk, sbn, C, ldc,
-                       bias, Zout, Zin);
+hipError_t gemm(hipStream_t s, int M, int N, int K, const T* A, int64_t sam, int64_t sak, const T* B, int64_t sbk,
+                int64_t sbn, T* C, int64_t ldc, const T* bias = nullptr, T* Zout = nullptr, const T* Zin = nullptr) {
+    // (activations row by row; weights as stored, or transposed for the data gradient)
+    dim3 grid((M + 63) / 64, (N + 63) / 64, 1);
+    if (sbn == 1)
+        hipLaunchKernelGGL((k_gemm<T, EPI, true, false>), grid, dim3(256), 0, s, M, N, K, (K + 15) / 16 * 16, A, sam,
+                           sak, quads(A, sam, sak), 0, B, sbk, sbn, quads(B, sbk, sbn), C, ldc, (int64_t)0, bias, Zout,
+                           Zin);
+    else
+        hipLaunchKernelGGL((k_gemm<T, EPI, true, true>), grid, dim3(256), 0, s, M, N, K, (K + 15) / 16 * 16, A, sam,
+                           sak, quads(A, sam, sak), 0, B, sbk, sbn, quads(B, sbk, sbn), C, ldc, (int64_t)0, bias, Zout,
+                           Zin);
     return hipGetLastError();
 }
 
-// weight gradient G[M][N] = A^T B over the batch (K rows), split-K + ordered sum
+// slices of the weight gradient [A^T; 1] B over the batch (K rows) of a layer
+// with N units: M weight rows and the bias row, slice z at part + z np + off;
+// nz receives their number
 template <typename T>
 hipError_t grad_gemm(stdg_model* md, hipStream_t s, int M, int N, int K, const T* A, int64_t sam, int64_t sak,
-                     const T* B, int64_t sbk, int64_t sbn, T* G) {
-    int nz = std::max(1, std::min(KSPLIT, K / 256));
-    int kchunk = ((K + nz - 1) / nz + 15) / 16 * 16;
+                     const T* B, int64_t sbk, int64_t sbn, int64_t off, int& nz) {
+    nz = std::max(1, std::min(KSPLIT, K / 256));
+    const int kchunk = ((K + nz - 1) / nz + 15) / 16 * 16;
     nz = std::max(1, (K + kchunk - 1) / kchunk);
-    T* part = (T*)md->part;
-    dim3 grid((M + 63) / 64, (N + 63) / 64, nz);
-    hipLaunchKernelGGL((k_gemm<T, EPI_STORE>), grid, dim3(256), 0, s, M, N, K, kchunk, A, sam, sak, B, sbk, sbn,
-                       part, (int64_t)N, (const T*)nullptr, (T*)nullptr, (const T*)nullptr);
-    const int64_t count = (int64_t)M * N;
-    hipLaunchKernelGGL(k_sum_slices<T>, dim3(nb256(count)), dim3(256), 0, s, part, nz, count, G);
+    dim3 grid((M + 1 + 63) / 64, (N + 63) / 64, nz);
+    hipLaunchKernelGGL((k_gemm<T, EPI_STORE, false, false>), grid, dim3(256), 0, s, M + 1, N, K, kchunk, A, sam, sak,
+                       quads(A, sam, sak), 1, B, sbk, sbn, quads(B, sbk, sbn), (T*)md->part + off, (int64_t)N, md->np,
+                       (const T*)nullptr, (T*)nullptr, (const T*)nullptr);
     return hipGetLastError();
 }
 
@@ -401,36 +481,37 @@ template <typename T>
 int forward_t(stdg_model* md, int64_t n, hipStream_t s) {
     const T* th = (const T*)md->theta;
     const int nin = md->nin, H = md->hid, no = md->nout;
-    MCK((gemm<T, EPI_BIAS_ACT>(s, (int)n, H, nin, 1, (const T*)md->F, nin, 1, th + md->oW1, H, 1, (T*)md->H1, H,
+    MCK((gemm<T, EPI_BIAS_ACT>(s, (int)n, H, nin, (const T*)md->F, nin, 1, th + md->oW1, H, 1, (T*)md->H1, H,
                                th + md->ob1, (T*)md->Z1)));
-    MCK((gemm<T, EPI_BIAS_ACT>(s, (int)n, H, H, 1, (const T*)md->H1, H, 1, th + md->oW2, H, 1, (T*)md->H2, H,
+    MCK((gemm<T, EPI_BIAS_ACT>(s, (int)n, H, H, (const T*)md->H1, H, 1, th + md->oW2, H, 1, (T*)md->H2, H,
                                th + md->ob2, (T*)md->Z2)));
-    MCK((gemm<T, EPI_BIAS>(s, (int)n, no, H, 1, (const T*)md->H2, H, 1, th + md->oW3, no, 1, (T*)md->Y, no,
+    MCK((gemm<T, EPI_BIAS>(s, (int)n, no, H, (const T*)md->H2, H, 1, th + md->oW3, no, 1, (T*)md->Y, no,
                            th + md->ob3)));
     return STDG_OK;
 }
 
-// gradient of the loss of the rows in md->F (forward already run, dY set)
+// gradient of the loss of the rows in md->F (forward already run, dY set); the
+// parameters are stored weights then bias layer by layer, so a layer's
+// gradient is one matrix with the bias as its last row
 template <typename T>
 int backward_t(stdg_model* md, int64_t n, hipStream_t s) {
     const T* th = (const T*)md->theta;
-    T* g = (T*)md->grad;
     const int nin = md->nin, H = md->hid, no = md->nout;
     const int K = (int)n;
-    const T* one = (const T*)md->one;
+    int nz[3];
     // output layer
-    MCK(grad_gemm<T>(md, s, H, no, K, (const T*)md->H2, 1, H, (const T*)md->dY, no, 1, g + md->oW3));
-    MCK(grad_gemm<T>(md, s, 1, no, K, one, 0, 0, (const T*)md->dY, no, 1, g + md->ob3));
-    MCK((gemm<T, EPI_DACT>(s, K, H, no, 1, (const T*)md->dY, no, 1, th + md->oW3, 1, no, (T*)md->dZ2, H, nullptr,
+    MCK(grad_gemm<T>(md, s, H, no, K, (const T*)md->H2, 1, H, (const T*)md->dY, no, 1, md->oW3, nz[2]));
+    MCK((gemm<T, EPI_DACT>(s, K, H, no, (const T*)md->dY, no, 1, th + md->oW3, 1, no, (T*)md->dZ2, H, nullptr,
                            nullptr, (const T*)md->Z2)));
     // second layer
-    MCK(grad_gemm<T>(md, s, H, H, K, (const T*)md->H1, 1, H, (const T*)md->dZ2, H, 1, g + md->oW2));
-    MCK(grad_gemm<T>(md, s, 1, H, K, one, 0, 0, (const T*)md->dZ2, H, 1, g + md->ob2));
-    MCK((gemm<T, EPI_DACT>(s, K, H, H, 1, (const T*)md->dZ2, H, 1, th + md->oW2, 1, H, (T*)md->dZ1, H, nullptr,
+    MCK(grad_gemm<T>(md, s, H, H, K, (const T*)md->H1, 1, H, (const T*)md->dZ2, H, 1, md->oW2, nz[1]));
+    MCK((gemm<T, EPI_DACT>(s, K, H, H, (const T*)md->dZ2, H, 1, th + md->oW2, 1, H, (T*)md->dZ1, H, nullptr,
                            nullptr, (const T*)md->Z1)));
     // first layer
-    MCK(grad_gemm<T>(md, s, nin, H, K, (const T*)md->F, 1, nin, (const T*)md->dZ1, H, 1, g + md->oW1));
-    MCK(grad_gemm<T>(md, s, 1, H, K, one, 0, 0, (const T*)md->dZ1, H, 1, g + md->ob1));
+    MCK(grad_gemm<T>(md, s, nin, H, K, (const T*)md->F, 1, nin, (const T*)md->dZ1, H, 1, md->oW1, nz[0]));
+    hipLaunchKernelGGL(k_sum_slices<T>, dim3(nb256(md->np)), dim3(256), 0, s, (const T*)md->part, nz[0], md->oW2, nz[1],
+                       md->oW3, nz[2], md->np, (T*)md->grad);
+    MCK(hipGetLastError());
     return STDG_OK;
 }
 
@@ -461,7 +542,7 @@ int adam_t(stdg_model* md, hipStream_t s) {
 template <typename T>
 int features_t(stdg_model* md, const stdg_mesh* m, const double* P, const double* Pm, const double* B,
                const int64_t* idx, int64_t row0, int64_t n, T* F, hipStream_t s) {
-    hipLaunchKernelGGL(k_features<T>, dim3(nb256(n * md->nin)), dim3(256), 0, s, P, Pm, B, m->d.nbr, idx, row0, n,
+    hipLaunchKernelGGL(k_features<T>, dim3((unsigned)((n + FR - 1) / FR)), dim3(256), 0, s, P, Pm, B, m->d.nbr, idx, row0, n,
                        md->E, md->nst, md->scales, F);
     MCK(hipGetLastError());
     return STDG_OK;
@@ -645,10 +726,10 @@ extern "C" int stdg_model_create(const stdg_mesh* m, const stdg_model_config* cf
         return STDG_ERR_NOMEM;
     };
     hipError_t e;
-    const int64_t part_n = (int64_t)KSPLIT * std::max<int64_t>({nin * H, H * H, H * no});
+    const int64_t part_n = (int64_t)KSPLIT * md->np;
     struct { void** p; size_t bytes; } al[] = {
         {&md->theta, ts * md->np}, {&md->grad, ts * md->np}, {&md->mom1, ts * md->np}, {&md->mom2, ts * md->np},
-        {&md->one, ts}, {&md->F, ts * bs * nin}, {&md->Z1, ts * bs * H}, {&md->H1, ts * bs * H},
+        {&md->F, ts * bs * nin}, {&md->Z1, ts * bs * H}, {&md->H1, ts * bs * H},
         {&md->Z2, ts * bs * H}, {&md->H2, ts * bs * H}, {&md->Y, ts * bs * no}, {&md->dY, ts * bs * no},
         {&md->dZ2, ts * bs * H}, {&md->dZ1, ts * bs * H}, {&md->part, ts * part_n},
         {(void**)&md->lpart, sizeof(double) * NRB}, {(void**)&md->spart, sizeof(double) * 3 * NRB}};
@@ -671,7 +752,7 @@ extern "C" int stdg_model_create(const stdg_mesh* m, const stdg_model_config* cf
 
 extern "C" int stdg_model_free(stdg_model* md) {
     if (!md) return STDG_OK;
-    for (void* p : {md->theta, md->grad, md->mom1, md->mom2, md->one, md->F, md->Z1, md->H1, md->Z2, md->H2, md->Y,
+    for (void* p : {md->theta, md->grad, md->mom1, md->mom2, md->F, md->Z1, md->H1, md->Z2, md->H2, md->Y,
                     md->dY, md->dZ2, md->dZ1, md->part, (void*)md->lpart, (void*)md->lbatch, (void*)md->scales,
                     (void*)md->spart, (void*)md->idx, (void*)md->ve, (void*)md->vR, (void*)md->vG,
                     (void*)md->CT})
@@ -716,8 +797,6 @@ extern "C" int stdg_model_set_params(stdg_model* md, const double* host) {
     STDG_HIP(hipMemset(md->mom1, 0, ts * md->np));
     STDG_HIP(hipMemset(md->mom2, 0, ts * md->np));
     STDG_HIP(hipMemset(md->grad, 0, ts * md->np));
-    if (is64(md)) { const double one = 1.0; STDG_HIP(hipMemcpy(md->one, &one, 8, hipMemcpyHostToDevice)); }
-    else { const float one = 1.0f; STDG_HIP(hipMemcpy(md->one, &one, 4, hipMemcpyHostToDevice)); }
     md->t_adam = 0;
     return STDG_OK;
 }
