@@ -7,17 +7,18 @@
 // B_{c,0..4} the class-deduplicated dt^2-scaled spatial blocks and C the G x G
 // time factor.
 //
-// Work decomposition: one thread per (element, time node a).  The thread
-// forms the time-mixed neighbour column x'_m = sum_b C_ab x_k[b][m] on the fly
-// and accumulates its N outputs y_i[a][.] in registers.  Elements are ordered
-// so that every full wavefront holds 64 elements of one class (Hilbert order
-// within each class): the wavefront's block B_{c,k} is then uniform and is
-// read through scalar loads (one broadcast per column, stored transposed
-// BT[c][k][m][r] so a column is contiguous), and the FP64 FMAs take it as a
-// scalar operand.  Wavefronts that mix classes (the tail, or meshes without
-// repeated geometry) take the same loop with per-lane block loads.
+// FP64 (p <= 4, p_gamma <= 4): runs of 64 elements of one class on the FP64
+// matrix cores, the elements of other runs with a thread per (coupling, row)
+// (schur_apply_m64); meshes whose elements carry their own blocks stream them
+// (cg_elem.hip).  FP32 vectors and other degrees: one thread per (element,
+// time node), the neighbour column x'_m = sum_b C_ab x_k[b][m] formed on the
+// fly, N outputs in registers; a wavefront of one class reads its blocks
+// through scalar loads (stored transposed, BT[c][k][m][r], so that a column is
+// contiguous), others per lane.
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "mfma64.hpp"
+#include "two_level.hpp"
 
 namespace stdg {
 
@@ -79,104 +80,6 @@ __global__ void __launch_bounds__(256) schur_apply_tn(
     }
 }
 
-// Copy the 64 time-mixed rows x'[lane'] = sum_b C_ab x[nb(lane')][b][.] of a
-// wavefront into its panel: 64/N rows per instruction group, consecutive
-// lanes on consecutive spatial values, G loads per value.
-template <int N, int G, int RS, typename T>
-__device__ __forceinline__ void load_panel(T* __restrict__ panel, const T* __restrict__ x, int t,
-                                           const T (&Ca)[G], int roff, int col0) {
-    constexpr int RPI = 64 / N;
-#pragma unroll
-    for (int j0 = 0; j0 < 64; j0 += RPI) {
-        const int row = j0 + roff;
-        const int tr = __shfl(t, row < 64 ? row : 63, 64);
-        if (roff < RPI && row < 64) {
-            T v = T(0);
-            if (tr >= 0) {
-                const T* xt = x + (int64_t)tr * G * N + col0;
-#pragma unroll
-                for (int b = 0; b < G; ++b) v += Ca[b] * xt[b * N];
-            }
-            panel[row * RS + col0] = v;
-        }
-    }
-}
-
-template <int N, typename T>
-__device__ __forceinline__ void panel_fma(const T* __restrict__ Bk, const T* __restrict__ xr,
-                                          T (&acc)[N]) {
-#pragma unroll
-    for (int m = 0; m < N; ++m) {
-        const T xp = xr[m];
-        const T* col = Bk + m * N;
-#pragma unroll
-        for (int r = 0; r < N; ++r) acc[r] += col[r] * xp;
-    }
-}
-
-// Panel-staged kernel.  A block of 256 threads holds four wavefronts; each
-// wavefront owns 64 elements, one time node a and a private LDS panel.  For
-// each of the five couplings k the wavefront first copies the 64 time-mixed
-// neighbour rows into its panel (a few cache lines per load instruction
-// instead of one line per lane), then every lane runs the N x N block against
-// its own row: panel values from LDS (odd row stride), block columns from
-// scalar registers when the wavefront holds one class.  Boundary faces load
-// zero rows instead of being skipped, so every wavefront reaches every barrier.
-template <int N, int G, typename T>
-__global__ void __launch_bounds__(256) schur_apply_lds(
-    const T* __restrict__ BT, const int32_t* __restrict__ cls, const int32_t* __restrict__ nbr,
-    const T* __restrict__ C, const T* __restrict__ x, T* __restrict__ y, int64_t E) {
-    static_assert(N <= 64, "panel rows longer than a wavefront");
-    constexpr int RS = N | 1;                     // odd row stride (elements)
-    __shared__ T panels[4 * 64 * RS];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    T* panel = panels + wave * 64 * RS;
-    const int a = (int)(blockIdx.x % G);
-    const int64_t i = (int64_t)(blockIdx.x / G) * 256 + threadIdx.x;
-    const bool valid = i < E;
-    const int64_t ii = valid ? i : E - 1;
-    const int c = cls[ii];
-    const int c0 = __builtin_amdgcn_readfirstlane(c);
-    const bool uniform = __all(c == c0);
-    T Ca[G];
-#pragma unroll
-    for (int b = 0; b < G; ++b) Ca[b] = C[a * G + b];
-    T acc[N];
-#pragma unroll
-    for (int r = 0; r < N; ++r) acc[r] = T(0);
-    int nb[5];
-    nb[0] = (int)ii;
-#pragma unroll
-    for (int f = 0; f < 4; ++f) nb[f + 1] = nbr[4 * ii + f];
-    const int roff = lane / N;                    // this lane's row within a copy group
-    const int col0 = lane - roff * N;
-    const T* xr = panel + lane * RS;
-    if (uniform) {
-        // one class for the whole wavefront: block columns through scalar loads
-        const T* Bc = BT + (int64_t)c0 * 5 * N * N;
-        for (int k = 0; k < 5; ++k) {
-            load_panel<N, G, RS, T>(panel, x, nb[k], Ca, roff, col0);
-            __syncthreads();
-            panel_fma<N, T>(Bc + k * N * N, xr, acc);
-            __syncthreads();
-        }
-    } else {
-        const T* Bc = BT + (int64_t)c * 5 * N * N;
-        for (int k = 0; k < 5; ++k) {
-            load_panel<N, G, RS, T>(panel, x, nb[k], Ca, roff, col0);
-            __syncthreads();
-            panel_fma<N, T>(Bc + k * N * N, xr, acc);
-            __syncthreads();
-        }
-    }
-    if (valid) {
-        T* yi = y + (i * G + a) * N;
-#pragma unroll
-        for (int r = 0; r < N; ++r) yi[r] = acc[r];
-    }
-}
-
 // Any (N, G): one thread per (element, spatial row), all time nodes.
 template <int G, typename T>
 __global__ void __launch_bounds__(256) schur_apply_rows(
@@ -210,291 +113,190 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
     }
 }
 
-// The elements of the runs of several classes that the matrix-core kernel
-// leaves out: one workgroup of 5 N threads per element, thread (k, r)
-// forming row r of coupling k for every time node (the five couplings in
-// parallel, summed through LDS), then the G x G time factor.
-template <int G>
-__global__ void __launch_bounds__(5 * 35) schur_apply_list(
-    const double* __restrict__ BT, const int32_t* __restrict__ cls, const int32_t* __restrict__ nbr,
-    const double* __restrict__ C, const double* __restrict__ x, double* __restrict__ y,
-    const int32_t* __restrict__ elems, int N) {
-    __shared__ double part[5 * G * 35];
-    const int64_t i = elems[blockIdx.x];
-    const int k = threadIdx.x / N, r = threadIdx.x - k * N;
-    double acc[G];
+// FP64 y = S x.  The first `run_blocks` workgroups take one 64-element run
+// each: the class's five blocks staged in LDS, a wavefront on 16 CW elements
+// with G columns each (mfma64.hpp: rows read 16 bytes a lane, an operand from
+// LDS serving CW G matrix instructions, results in place for the G x G time
+// factor and written in whole lines); runs of several classes are left to the
+// workgroups after them, which take EPB elements of `elems` (all of them when
+// it is null) with a thread per coupling and row, the five couplings in
+// parallel and summed through LDS.  Bound: HBM at p <= 2, the matrix cores and
+// the operand reads at p = 3, 4, the launch (7.8 us in a loop from the host)
+// below 10^4 elements.  MI355X, kernels per entry on the vector units before
+// -> this one, us: 663,552 elements, p = 3, G = 1: 123 -> 102 (2.1 TB/s of x
+// and y); 196,608, p = 2: G = 1 19.9 -> 14.8, G = 2 29.7 -> 24.5; 82,944, p = 3,
+// G = 2: 33.0 -> 24.9; 48,000, p = 2, G = 3: 41 -> 11.5; with walls 10,368, p = 4,
+// G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; every run mixed, 82,944, p = 3,
+// G = 2: 391 -> 198.  The sums' rounding is half as large.
+// With DOT the workgroup's share of x.y goes to part[blockIdx.x].
+template <int N, int G, int CW, bool DOT>
+__global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __restrict__ BT,
+                                                           const int32_t* __restrict__ cls,
+                                                           const int32_t* __restrict__ run_cls,
+                                                           const int32_t* __restrict__ nbr,
+                                                           const double* __restrict__ C, const double* x,
+                                                           double* __restrict__ y, int64_t E, uint32_t run_blocks,
+                                                           const int32_t* __restrict__ elems, int64_t n_elems,
+                                                           double* __restrict__ part) {
+    constexpr int NT = 256 / CW, NQ = M64<N>::NQ, NP = M64<N>::NP, NC = CW * G;
+    constexpr int EPB = NT / (5 * N) > 0 ? NT / (5 * N) : 1;
+    static_assert(5 * N <= NT, "a thread per coupling and row");
+    constexpr int L0 = 5 * N * NP > 64 * G * N ? 5 * N * NP : 64 * G * N;
+    constexpr int LD = L0 > EPB * 5 * G * N ? L0 : EPB * 5 * G * N;
+    __shared__ double A[LD];
+    __shared__ double red[NT / 64];
+    double d = 0.0;
+    if (blockIdx.x < run_blocks) {
+        const uint32_t run = (blockIdx.x % 8) * (run_blocks / 8) + blockIdx.x / 8;
+        const int64_t e0 = (int64_t)run * 64;
+        const int c = e0 < E ? run_cls[run] : -1;
+        if (c >= 0) {
+            const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hi = lane >> 4, lo = lane & 3;
+            int nb[5][CW];
 #pragma unroll
-    for (int b = 0; b < G; ++b) acc[b] = 0.0;
-    const int64_t t = (k == 0) ? i : (int64_t)nbr[4 * i + (k - 1)];
-    if (t >= 0) {
-        const double* Bk = BT + ((int64_t)cls[i] * 5 + k) * N * N;
-        const double* xt = x + t * G * N;
-        for (int mm = 0; mm < N; ++mm) {
-            const double bv = Bk[(int64_t)mm * N + r];
+            for (int q = 0; q < CW; ++q) {
+                const int64_t e = e0 + 16 * (CW * w + q) + (lane & 15);
+                const bool valid = e < E;
+                nb[0][q] = valid ? (int)e : -1;
 #pragma unroll
-            for (int b = 0; b < G; ++b) acc[b] += bv * xt[b * N + mm];
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < G; ++b) part[(k * G + b) * N + r] = acc[b];
-    __syncthreads();
-    if (k == 0) {
-        double z[G];
-#pragma unroll
-        for (int b = 0; b < G; ++b) {
-            z[b] = 0.0;
-            for (int kk = 0; kk < 5; ++kk) z[b] += part[(kk * G + b) * N + r];
-        }
-        double* yi = y + i * G * N;
-#pragma unroll
-        for (int a = 0; a < G; ++a) {
-            double s = 0.0;
-#pragma unroll
-            for (int b = 0; b < G; ++b) s += C[a * G + b] * z[b];
-            yi[a * N + r] = s;
-        }
-    }
-}
-
-// Element-per-lane FP64 apply for meshes whose 64-element runs share a class
-// (the structured cubes).  One wavefront (and workgroup) per run, lane l =
-// element 64 run + l; for each of the five couplings the wavefront first
-// moves the 64 rows it needs ([G][N] doubles each, contiguous in memory)
-// into its LDS with 16-byte loads that walk the rows in order (a load
-// instruction covers about 64 / (N G / 2) consecutive rows instead of one
-// row per lane), then every lane reads its own row back and applies the
-// class block, taken column by column through scalar loads (uniform on the
-// run), to all G time nodes of its element.  The G x G time factor is
-// applied to the result, which leaves through LDS the same way.  Row pieces
-// sit in LDS at an odd stride of 16-byte units (NP + 1 for even NP), so the
-// 16 lanes of each pass of a 16-byte read hit distinct banks.
-template <int N, int G>
-__global__ void __launch_bounds__(64) schur_apply_run(const double* __restrict__ BT, const int32_t* __restrict__ cls,
-                                                      const int32_t* __restrict__ nbr, const double* __restrict__ C,
-                                                      const double* __restrict__ x, double* __restrict__ y,
-                                                      int64_t E, uint32_t n_runs) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    constexpr int R = N * G, NP = R / 2, STR = NP % 2 == 0 ? NP + 1 : NP;
-    static_assert(R % 2 == 0, "rows of whole 16-byte pieces");
-    __shared__ d2 L[64 * STR];
-    const int lane = threadIdx.x;
-    // consecutive workgroups go round-robin to the 8 XCDs: XCD x takes the
-    // contiguous range of runs x * per ..
-    const uint32_t nb = gridDim.x;
-    const uint32_t run = (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8;
-    if (run >= n_runs) return;
-    const int64_t e0 = (int64_t)run * 64, e = e0 + lane;
-    const bool valid = e < E;
-    const int c = __builtin_amdgcn_readfirstlane(cls[e0]);
-    int nbk[4] = {-1, -1, -1, -1};
-    if (valid) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f) nbk[f] = nbr[4 * e + f];
-    }
-    double z[G][N];
-#pragma unroll
-    for (int b = 0; b < G; ++b)
-#pragma unroll
-        for (int r = 0; r < N; ++r) z[b][r] = 0.0;
-    for (int k = 0; k < 5; ++k) {
-        const int src = k == 0 ? (valid ? (int)e : -1) : nbk[k - 1];
-        if (__builtin_amdgcn_readfirstlane(__ballot(src >= 0) != 0 ? 1 : 0) == 0) continue;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int pc = i * 64 + lane, row = pc / NP, piece = pc - row * NP;
-            const int s = __shfl(src, row, 64);
-            const d2 v = s >= 0 ? reinterpret_cast<const d2*>(x + (int64_t)s * R)[piece] : d2{0.0, 0.0};
-            L[row * STR + piece] = v;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double xr[R];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-            const d2 t = L[lane * STR + j];
-            xr[2 * j] = t.x;
-            xr[2 * j + 1] = t.y;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const double* Bk = BT + ((int64_t)c * 5 + k) * N * N;
-#pragma unroll
-        for (int m = 0; m < N; ++m) {
-            const double* col = Bk + m * N;
-#pragma unroll
-            for (int r = 0; r < N; ++r) {
-                const double a = col[r];
-#pragma unroll
-                for (int b = 0; b < G; ++b) z[b][r] += a * xr[b * N + m];
+                for (int f = 0; f < 4; ++f) nb[f + 1][q] = valid ? nbr[4 * e + f] : -1;
             }
-        }
-    }
-    double yr[R];
+            m64_stage<N, NT>(BT + (int64_t)c * 5 * N * N, A, 5);
+            const __amdgpu_buffer_rsrc_t rx = m64_rsrc(x, (uint32_t)(8 * E * G * N));
+            double acc[NQ][NC];
 #pragma unroll
-    for (int a = 0; a < G; ++a)
+            for (int rg = 0; rg < NQ; ++rg)
 #pragma unroll
-        for (int r = 0; r < N; ++r) {
-            double s = 0.0;
+                for (int q = 0; q < NC; ++q) acc[rg][q] = 0.0;
+            __syncthreads();
+            auto couple = [&](int k) {
+                double b[NC][NQ];
 #pragma unroll
-            for (int b = 0; b < G; ++b) s += C[a * G + b] * z[b][r];
-            yr[a * N + r] = s;
-        }
-#pragma unroll
-    for (int j = 0; j < NP; ++j) L[lane * STR + j] = d2{yr[2 * j], yr[2 * j + 1]};
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int pc = i * 64 + lane, row = pc / NP, piece = pc - row * NP;
-        if (e0 + row < E) reinterpret_cast<d2*>(y + (e0 + row) * R)[piece] = L[row * STR + piece];
-    }
-}
-
-// FP64 apply on the FP64 matrix cores, meshes whose 64-element runs share a
-// class.  v_mfma_f64_4x4x4f64 runs four independent 4 x 4 x 4 products
-// (blocks b = 0..3); lane 16 k + 4 b + i holds A_b[i][k], lane 16 k + 4 b + j
-// holds B_b[k][j], and D_b[i][j] lands in lane 16 i + 4 b + j (probed on the
-// GPU; the broadcast fields have no effect on this instruction, so the A
-// operand is simply the same in the four blocks).  One 256-thread workgroup
-// per run: the class's five blocks are staged in LDS, zero-padded to
-// NP = 4 ceil(N / 4) rows and columns; wavefront w takes elements
-// 16 w .. 16 w + 15 of the run as the 16 columns (element 4 b + j in lanes
-// 16 k + 4 b + j), so a lane's column is the same element in the B operand
-// and in the result.  Per (block, four-column step ks, four-row group rg) an
-// instruction adds B_k[4 rg .. +3][4 ks .. +3] x[4 ks .. +3] to rows
-// 4 rg .. +3 of the 16 elements, for each time node: the A value comes from
-// LDS (lane 16 k + 4 b + i reads B_k[4 rg + i][4 ks + k]), the B value is
-// one double of the neighbour's row (four lanes of a column read 32
-// consecutive bytes).  No padding at N = 4, 20; the G x G time factor is
-// applied to the G accumulators of a lane, which hold one row of one element
-// for every time node.
-template <int N, int G, int CW>
-__global__ void __launch_bounds__(256 / CW) schur_apply_mfma(const double* __restrict__ BT,
-                                                             const int32_t* __restrict__ run_cls,
-                                                             const int32_t* __restrict__ nbr,
-                                                             const double* __restrict__ C, const double* x,
-                                                             double* __restrict__ y, int64_t E, uint32_t n_runs,
-                                                             uint32_t xbytes) {
-    constexpr int NQ = (N + 3) / 4, NP = 4 * NQ, NT = 256 / CW;
-    constexpr uint32_t OOBX = 0x80000000u;
-    __shared__ double A[5 * NP * NP];
-    const uint32_t run = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    if (run >= n_runs) return;                          // uniform over the workgroup
-    const int c = run_cls[run];                         // runs of several classes: schur_apply_list
-    if (c < 0) return;
-    const int64_t e0 = (int64_t)run * 64;
-    // A[k][r][col] = B_k[r][col] = BT[c][k][col][r] (r fastest: contiguous reads)
-    for (int t = threadIdx.x; t < 5 * NP * NP; t += NT) {
-        const int r = t % NP, col = (t / NP) % NP, k = t / (NP * NP);
-        A[(k * NP + r) * NP + col] = (r < N && col < N) ? BT[(((int64_t)c * 5 + k) * N + col) * N + r] : 0.0;
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int hi = lane >> 4, lo = lane & 3;            // k (B) / i (D) and i (A) / j
-    // column group g of this wavefront: elements 16 (CW w + g) + 4 b + j
-    int64_t e[CW];
-    bool valid[CW];
-    int nb[CW][4];
-#pragma unroll
-    for (int g = 0; g < CW; ++g) {
-        e[g] = e0 + 16 * (CW * w + g) + 4 * ((lane >> 2) & 3) + lo;
-        valid[g] = e[g] < E;
-#pragma unroll
-        for (int f = 0; f < 4; ++f) nb[g][f] = valid[g] ? nbr[4 * e[g] + f] : -1;
-    }
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(x), (short)0,
-                                                                        (int)xbytes, 0x00020000);
-    double acc[NQ][CW][G];
-#pragma unroll
-    for (int rg = 0; rg < NQ; ++rg)
-#pragma unroll
-        for (int g = 0; g < CW; ++g)
-#pragma unroll
-            for (int a = 0; a < G; ++a) acc[rg][g][a] = 0.0;
-    auto couple = [&](int k) {
-        uint32_t base[CW];
-#pragma unroll
-        for (int g = 0; g < CW; ++g) {
-            const int64_t src = k == 0 ? (valid[g] ? e[g] : -1)
-                                       : (k == 1 ? nb[g][0] : (k == 2 ? nb[g][1] : (k == 3 ? nb[g][2] : nb[g][3])));
-            base[g] = src >= 0 ? (uint32_t)src * (uint32_t)(G * N * 8) : OOBX;
-        }
-#pragma unroll
-        for (int ks = 0; ks < NQ; ++ks) {
-            const int col = 4 * ks + hi;
-            double bv[CW][G];
-#pragma unroll
-            for (int g = 0; g < CW; ++g)
-#pragma unroll
-                for (int a = 0; a < G; ++a) {
-                    const uint32_t off =
-                        (base[g] != OOBX && col < N) ? base[g] + (uint32_t)((a * N + col) * 8) : OOBX;
-                    bv[g][a] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rx, (int)off, 0, 0));
-                }
-#pragma unroll
-            for (int rg = 0; rg < NQ; ++rg) {
-                const double av = A[(k * NP + 4 * rg + lo) * NP + 4 * ks + hi];
-#pragma unroll
-                for (int g = 0; g < CW; ++g)
+                for (int q = 0; q < CW; ++q) {
+                    const int s = k == 0 ? nb[0][q] : (k == 1 ? nb[1][q] : (k == 2 ? nb[2][q] : (k == 3 ? nb[3][q] : nb[4][q])));
 #pragma unroll
                     for (int a = 0; a < G; ++a)
-                        acc[rg][g][a] = __builtin_amdgcn_mfma_f64_4x4x4f64(av, bv[g][a], acc[rg][g][a], 0, 0, 0);
-            }
-        }
-    };
-    // large blocks (p = 4) one coupling at a time, so that the loads of the
-    // next coupling are not all held at once
-    if constexpr (NQ * G * CW > 16) {
+                        m64_load<N>(rx, s >= 0 ? (uint32_t)((s * G + a) * N) * 8u : M64_OOB, hi, b[q * G + a]);
+                }
+                m64_block<N, NC>(A + k * N * NP, b, lo, hi, acc);
+            };
+            // large blocks (p = 4) one coupling at a time, so that the rows of
+            // the next are not all held at once
+            if constexpr (NQ * NC > 16) {
 #pragma unroll 1
-        for (int k = 0; k < 5; ++k) couple(k);
-    } else {
+                for (int k = 0; k < 5; ++k) couple(k);
+            } else {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) couple(k);
-    }
-    double Cm[G][G];
+                for (int k = 0; k < 5; ++k) couple(k);
+            }
+            double Cm[G][G];
 #pragma unroll
-    for (int a = 0; a < G; ++a)
+            for (int a = 0; a < G; ++a)
 #pragma unroll
-        for (int b = 0; b < G; ++b) Cm[a][b] = C[a * G + b];
+                for (int b = 0; b < G; ++b) Cm[a][b] = C[a * G + b];
+            __syncthreads();
 #pragma unroll
-    for (int g = 0; g < CW; ++g)
-        if (valid[g])
-#pragma unroll
-            for (int rg = 0; rg < NQ; ++rg) {
-                const int row = 4 * rg + hi;
-                if (row < N)
-#pragma unroll
-                    for (int a = 0; a < G; ++a) {
+            for (int q = 0; q < CW; ++q) {
+                const int64_t first = e0 + 16 * (CW * w + q), left = E - first;
+                if (left <= 0) continue;
+                const int count = (int)(left < 16 ? left : 16) * G * N;
+                const int64_t at = first * G * N;
+                m64_flush<N, G>(
+                    A + w * 16 * G * N, lane, hi, count,
+                    [&](int rg, int a) {
                         double s = 0.0;
 #pragma unroll
-                        for (int b = 0; b < G; ++b) s += Cm[a][b] * acc[rg][g][b];
-                        y[(e[g] * G + a) * N + row] = s;
-                    }
+                        for (int b = 0; b < G; ++b) s += Cm[a][b] * acc[rg][q * G + b];
+                        return s;
+                    },
+                    [&](int i, m64_d2u v) {
+                        m64_put(y + at, i, count, v);
+                        if (DOT) {
+                            d += x[at + i] * v.x;
+                            if (i + 1 < count) d += x[at + i + 1] * v.y;
+                        }
+                    });
             }
+        }
+    } else {
+        const int t = threadIdx.x, el = t / (5 * N), kr = t - el * (5 * N), k = kr / N, r = kr - k * N;
+        const int64_t item = (int64_t)(blockIdx.x - run_blocks) * EPB + el;
+        const bool on = el < EPB && item < n_elems;
+        const int64_t i = on ? (elems ? (int64_t)elems[item] : item) : 0;
+        const int64_t s = !on ? -1 : (k == 0 ? i : (int64_t)nbr[4 * i + (k - 1)]);
+        double acc[G];
+#pragma unroll
+        for (int b = 0; b < G; ++b) acc[b] = 0.0;
+        if (s >= 0) {
+            const double* Bk = BT + ((int64_t)cls[i] * 5 + k) * N * N + r;
+            const double* xt = x + s * G * N;
+#pragma unroll 10
+            for (int mm = 0; mm < N; ++mm) {
+                const double bv = Bk[mm * N];
+#pragma unroll
+                for (int b = 0; b < G; ++b) acc[b] += bv * xt[b * N + mm];
+            }
+        }
+        if (el < EPB)
+#pragma unroll
+            for (int b = 0; b < G; ++b) A[((el * 5 + k) * G + b) * N + r] = acc[b];
+        __syncthreads();
+        if (on && k == 0) {
+            double z[G];
+#pragma unroll
+            for (int b = 0; b < G; ++b) {
+                z[b] = 0.0;
+#pragma unroll
+                for (int kk = 0; kk < 5; ++kk) z[b] += A[((el * 5 + kk) * G + b) * N + r];
+            }
+#pragma unroll
+            for (int a = 0; a < G; ++a) {
+                double v = 0.0;
+#pragma unroll
+                for (int b = 0; b < G; ++b) v += C[a * G + b] * z[b];
+                y[(i * G + a) * N + r] = v;
+                if (DOT) d += x[(i * G + a) * N + r] * v;
+            }
+        }
+    }
+    if (DOT) {
+        const double s = tl_reduce<NT>(d, red);
+        if (threadIdx.x == 0) part[blockIdx.x] = s;
+    }
+}
+
+// The launch's workgroups.  Runs where at most a quarter of them mix classes,
+// small meshes too (us, runs / one by one: 2,058 elements, p = 3, G = 2 6.5 /
+// 8.5; 48,000, p = 1, G = 2 5.5 / 8.0; 1,296 and 6,000, p = 2 3.5 / 4.1; 3,072,
+// p = 4, G = 2 14.1 / 25.0; equal at 750 and 1,296, p = 3); beyond that most
+// workgroups of a run would find nothing to do.
+struct M64Grid {
+    uint32_t run_blocks, blocks;
+    const int32_t* elems;
+    int64_t n_elems;
+};
+template <int N, int CW> static M64Grid m64_grid(const stdg_mesh* m) {
+    constexpr int EPB = 256 / CW / (5 * N) > 0 ? 256 / CW / (5 * N) : 1;
+    const int64_t runs = (m->E + 63) / 64;
+    M64Grid g;
+    const bool by_run = 4 * m->d.n_mixed_runs <= runs;
+    g.run_blocks = by_run ? (uint32_t)((runs + 7) / 8 * 8) : 0;
+    g.elems = by_run ? m->d.mixed_elems : nullptr;
+    g.n_elems = by_run ? m->d.n_mixed_elems : m->E;
+    g.blocks = g.run_blocks + (uint32_t)((g.n_elems + EPB - 1) / EPB);
+    return g;
 }
 
 template <int N, int G, int CW>
-static hipError_t launch_mfma(const stdg_mesh* m, const double* C, const double* x, double* y, hipStream_t s) {
-    const uint32_t runs = (uint32_t)((m->E + 63) / 64);
-    const uint32_t blocks = (runs + 7) / 8 * 8;
-    hipLaunchKernelGGL((schur_apply_mfma<N, G, CW>), dim3(blocks), dim3(256 / CW), 0, s, m->d.blocks,
-                       m->d.run_cls, m->d.nbr, C, x, y, m->E, runs, (uint32_t)(8 * m->E * m->G * m->N));
-    static_assert(N <= 35, "list kernel: at most 5 x 35 threads per element");
-    if (m->d.n_mixed_elems > 0)
-        hipLaunchKernelGGL((schur_apply_list<G>), dim3((unsigned)m->d.n_mixed_elems), dim3(5 * N), 0, s, m->d.blocks,
-                           m->d.cls, m->d.nbr, C, x, y, m->d.mixed_elems, N);
-    return hipGetLastError();
-}
-
-template <int N, int G>
-static hipError_t launch_run(const stdg_mesh* m, const double* C, const double* x, double* y, hipStream_t s) {
-    const uint32_t runs = (uint32_t)((m->E + 63) / 64);
-    const uint32_t blocks = (runs + 7) / 8 * 8;
-    hipLaunchKernelGGL((schur_apply_run<N, G>), dim3(blocks), dim3(64), 0, s, m->d.blocks, m->d.cls, m->d.nbr, C,
-                       x, y, m->E, runs);
+static hipError_t launch_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
+                             hipStream_t s) {
+    const M64Grid g = m64_grid<N, CW>(m);
+    if (part)
+        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, true>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
+                           m->d.cls, m->d.run_cls, m->d.nbr, C, x, y, m->E, g.run_blocks, g.elems, g.n_elems, part);
+    else
+        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, false>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
+                           m->d.cls, m->d.run_cls, m->d.nbr, C, x, y, m->E, g.run_blocks, g.elems, g.n_elems, part);
     return hipGetLastError();
 }
 
@@ -526,63 +328,58 @@ static hipError_t launch_rows(const stdg_mesh* m, const T* BT, const T* C, const
     return hipGetLastError();
 }
 
-template <int N, int G, typename T>
-static hipError_t launch_lds(const stdg_mesh* m, const T* BT, const T* C, const T* x, T* y, hipStream_t s) {
-    const int64_t blocks = (m->E + 255) / 256 * G;
-    hipLaunchKernelGGL((schur_apply_lds<N, G, T>), dim3((unsigned)blocks), dim3(256), 0, s, BT,
-                       m->d.cls, m->d.nbr, C, x, y, m->E);
-    return hipGetLastError();
+// column groups per wavefront: two where an element has one column
+template <int N, int G> constexpr int m64_cw() { return N == 20 && G == 1 ? 2 : 1; }
+
+static bool m64_supported(const stdg_mesh* m) {
+    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 &&
+           8 * m->E * m->G * m->N <= (int64_t)M64_OOB;
+}
+
+#define STDG_ALL_NG                                                       \
+    STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(4, 3) STDG_NG(4, 4) STDG_NG(4, 5) \
+    STDG_NG(10, 1) STDG_NG(10, 2) STDG_NG(10, 3) STDG_NG(10, 4) STDG_NG(10, 5) \
+    STDG_NG(20, 1) STDG_NG(20, 2) STDG_NG(20, 3) STDG_NG(20, 4) STDG_NG(20, 5) \
+    STDG_NG(35, 1) STDG_NG(35, 2) STDG_NG(35, 3) STDG_NG(35, 4) STDG_NG(35, 5)
+
+static hipError_t apply_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
+                            hipStream_t s) {
+#define STDG_NG(n, g) \
+    if (m->N == n && m->G == g) return launch_m64<n, g, m64_cw<n, g>()>(m, C, x, y, part, s);
+    STDG_ALL_NG
+#undef STDG_NG
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
 static hipError_t launch_apply(const stdg_mesh* m, const T* BT, const T* C, const T* x, T* y,
                                hipStream_t s) {
-    // Measured on MI355X (FP64): the panel-staged kernel wins for several time
-    // nodes with N >= 20 (N=20,G=2: 92 vs 116 us; N=35,G=5: 364 vs 464 us on
-    // the 82,944 / 24,576-element meshes), the direct-gather kernel elsewhere
-    // and for FP32 everywhere.
     if constexpr (sizeof(T) == 8) {
         // meshes whose elements carry their own blocks: the per-element FP64 tables
         if (elem_apply64_supported(m)) return elem_apply_f64(m, C, x, y, s);
-        // measured on MI355X (HIP events, median): 663,552-element p = 3 cube 174 (tn) -> 118 us
-        // (two 16-element column groups per wavefront), 82,944-element p = 3, p_gamma = 1 cube
-        // 92 (lds) -> 35 us; at p = 2 the MFMA kernel (32 us) only ties the run kernel
-        // runs of several classes (Dirichlet meshes: their boundary-class tails) go to the
-        // list kernel; the matrix-core kernel is used while they are at most a quarter of
-        // the runs (16^3 Dirichlet cube: 12 of 384)
-        const int64_t runs = (m->E + 63) / 64;
-        if (4 * m->d.n_mixed_runs <= runs && 8 * m->E * m->G * m->N < (int64_t(1) << 31)) {
-            if (m->N == 20 && m->G == 1) return launch_mfma<20, 1, 2>(m, C, x, y, s);
-            if (m->N == 20 && m->G == 2) return launch_mfma<20, 2, 1>(m, C, x, y, s);
-            if (m->N == 35 && m->G == 1) return launch_mfma<35, 1, 2>(m, C, x, y, s);
-            if (m->N == 35 && m->G == 2) return launch_mfma<35, 2, 1>(m, C, x, y, s);
-            if (m->N == 35 && m->G == 3) return launch_mfma<35, 3, 1>(m, C, x, y, s);
-            if (m->N == 35 && m->G == 4) return launch_mfma<35, 4, 1>(m, C, x, y, s);
-            if (m->N == 35 && m->G == 5) return launch_mfma<35, 5, 1>(m, C, x, y, s);
-        }
-        if (m->d.runs_uniform && m->E < (int64_t(1) << 31)) {
-#define STDG_NG(n, g) \
-    if (m->N == n && m->G == g) return launch_run<n, g>(m, C, x, y, s);
-            // measured on MI355X: 196,608-element p = 2, p_gamma = 1 cube 54 -> 32 us
-            STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(10, 1) STDG_NG(10, 2)
-#undef STDG_NG
-        }
-    }
-    if (sizeof(T) == 8 && m->G >= 2) {
-#define STDG_NG(n, g) \
-    if (m->N == n && m->G == g) return launch_lds<n, g, T>(m, BT, C, x, y, s);
-        STDG_NG(20, 2) STDG_NG(20, 3) STDG_NG(20, 4) STDG_NG(20, 5)
-        STDG_NG(35, 2) STDG_NG(35, 3) STDG_NG(35, 4) STDG_NG(35, 5)
-#undef STDG_NG
+        if (m64_supported(m)) return apply_m64(m, C, x, y, nullptr, s);
     }
 #define STDG_NG(n, g) \
     if (m->N == n && m->G == g) return launch_tn<n, g, T>(m, BT, C, x, y, s);
-    STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(4, 3) STDG_NG(4, 4) STDG_NG(4, 5)
-    STDG_NG(10, 1) STDG_NG(10, 2) STDG_NG(10, 3) STDG_NG(10, 4) STDG_NG(10, 5)
-    STDG_NG(20, 1) STDG_NG(20, 2) STDG_NG(20, 3) STDG_NG(20, 4) STDG_NG(20, 5)
-    STDG_NG(35, 1) STDG_NG(35, 2) STDG_NG(35, 3) STDG_NG(35, 4) STDG_NG(35, 5)
+    STDG_ALL_NG
 #undef STDG_NG
     return launch_rows<T>(m, BT, C, x, y, s);
+}
+
+// workgroups of launch_apply_dot_f64 (0: no such kernel for this mesh)
+int64_t apply_dot_blocks(const stdg_mesh* m) {
+    if (elem_apply64_supported(m) || !m64_supported(m)) return 0;
+#define STDG_NG(n, g) \
+    if (m->N == n && m->G == g) return m64_grid<n, m64_cw<n, g>()>(m).blocks;
+    STDG_ALL_NG
+#undef STDG_NG
+    return 0;
+}
+
+// y = (B (x) C) x and the workgroups' shares of x.y
+hipError_t launch_apply_dot_f64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
+                                hipStream_t s) {
+    return apply_m64(m, C, x, y, part, s);
 }
 
 hipError_t launch_apply_f64_c(const stdg_mesh* m, const double* C, const double* x, double* y,

@@ -17,6 +17,9 @@ hipError_t launch_apply_f32(const stdg_mesh* m, const float* x, float* y, hipStr
 hipError_t launch_apply_f64_c(const stdg_mesh* m, const double* C, const double* x, double* y,
                               hipStream_t s);
 hipError_t launch_apply_f32_c(const stdg_mesh* m, const float* C, const float* x, float* y, hipStream_t s);
+int64_t apply_dot_blocks(const stdg_mesh* m);
+hipError_t launch_apply_dot_f64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
+                                hipStream_t s);
 constexpr int CG_UPD_BLOCKS = 1024;
 bool cg_fused_supported(const stdg_mesh* m);
 int upload_cg_operands(stdg_mesh* m);

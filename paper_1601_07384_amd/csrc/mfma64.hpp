@@ -20,7 +20,8 @@ namespace stdg {
 
 typedef double m64_d2 __attribute__((ext_vector_type(2)));
 
-constexpr uint32_t M64_OOB = 0x80000000u;   // byte offset past every buffer: loads give 0
+// byte offset past every buffer (loads give 0) that a row's length does not wrap
+constexpr uint32_t M64_OOB = 0xFFFF0000u;
 
 template <int N> struct M64 {
     static constexpr int NQ = (N + 3) / 4;      // contraction steps and row groups
