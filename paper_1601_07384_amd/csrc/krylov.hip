@@ -39,7 +39,7 @@ constexpr int RT = 256;     // threads per reduction block
 constexpr int NBLK = 1024;  // reduction blocks (fixed: determinism)
 
 enum Slot {
-    S_RR = 0, S_PQ, S_ALPHA, S_BETA, S_RES, S_BN2, S_RN2, S_NORM, S_INV, S_TMP,
+    S_RR = 0, S_PQ, S_ALPHA, S_CGDONE, S_RES, S_BN2, S_RN2, S_NORM, S_INV, S_TMP,
     S_FRR = 10,         // fused CG: rr of even / odd iterations (two slots)
     S_CHK = 12,         // fused CG: lagged residual checks (two slots)
     S_TIME = 16,        // G per-time-node sums
@@ -86,8 +86,8 @@ __global__ void __launch_bounds__(RT) k_dot(const A* __restrict__ a, const B* __
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// out = sum(partial[0..np)); mode selects a scalar update done by thread 0.
-enum FinMode { FIN_STORE = 0, FIN_CG_ALPHA = 1, FIN_CG_BETA = 2, FIN_SQRT = 3 };
+// out = sum(partial[0..np)), or its root
+enum FinMode { FIN_STORE = 0, FIN_SQRT = 1 };
 __global__ void __launch_bounds__(RT) k_finalize(const double* __restrict__ partial, int np,
                                                  double* __restrict__ scal, int slot, int mode) {
     __shared__ double sm[RT / 64];
@@ -95,29 +95,32 @@ __global__ void __launch_bounds__(RT) k_finalize(const double* __restrict__ part
     for (int i = threadIdx.x; i < np; i += RT) acc += partial[i];
     double s = block_sum(acc, sm);
     if (threadIdx.x != 0) return;
-    if (mode == FIN_STORE) {
-        scal[slot] = s;
-    } else if (mode == FIN_CG_ALPHA) {            // s = p.q
-        const double rr = scal[S_RR];
-        scal[S_PQ] = s;
-        scal[S_ALPHA] = (s > 0.0 && rr > 0.0) ? rr / s : 0.0;
-    } else if (mode == FIN_CG_BETA) {             // s = r.r (new)
-        const double rr = scal[S_RR];
-        scal[S_BETA] = (rr > 0.0 && scal[S_ALPHA] != 0.0) ? s / rr : 0.0;
-        scal[S_RR] = s;
-    } else if (mode == FIN_SQRT) {
-        scal[slot] = sqrt(s);
-    }
+    scal[slot] = mode == FIN_SQRT ? sqrt(s) : s;
 }
 
-// CG: x += alpha p; r -= alpha q; partial sums of r.r
+// Plain CG, three kernels per iteration: the operator with the shares of p.q
+// (or the operator and k_dot), then k_cg_xr and k_cg_p, whose workgroups sum
+// the previous kernel's partials themselves (at most 2,048 values, in a fixed
+// order) instead of waiting for a kernel of one workgroup between them.
+// Bound: the latency of three dependent kernels (131,820 unknowns are 4 MB of
+// vectors).  r.r of iteration i lives in slot S_FRR + (i & 1).  A converged
+// solve leaves the iteration's number in S_CGDONE and what is still queued
+// changes nothing, so the host reads it one interval behind the queue.
+// MI355X, 13,182 elements, p = 2: FIXME us per iteration.
+constexpr int CG_PARTS = 2048;
+
+// x += alpha p; r -= alpha q; partial sums of r.r
 template <typename T>
 __global__ void __launch_bounds__(RT) k_cg_xr(T* __restrict__ x, T* __restrict__ r,
                                               const T* __restrict__ p, const T* __restrict__ q,
-                                              const double* __restrict__ scal, int64_t n,
+                                              const double* __restrict__ pq, int n_pq, int it,
+                                              double* __restrict__ scal, int64_t n,
                                               double* __restrict__ partial) {
     __shared__ double sm[RT / 64];
-    const T alpha = (T)scal[S_ALPHA];
+    if (scal[S_CGDONE] != 0.0) return;
+    const double s = tl_sum<RT>(pq, n_pq, 1, sm), rr = scal[S_FRR + (it & 1)];
+    const double al = (s > 0.0 && rr > 0.0) ? rr / s : 0.0;
+    const T alpha = (T)al;
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x; i < n; i += (int64_t)gridDim.x * RT) {
         x[i] += alpha * p[i];
@@ -125,15 +128,31 @@ __global__ void __launch_bounds__(RT) k_cg_xr(T* __restrict__ x, T* __restrict__
         r[i] = ri;
         acc += (double)ri * (double)ri;
     }
-    double s = block_sum(acc, sm);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    const double t = tl_reduce<RT>(acc, sm);
+    if (threadIdx.x == 0) {
+        partial[blockIdx.x] = t;
+        if (blockIdx.x == 0) scal[S_ALPHA] = al;
+    }
 }
 
+// p = r + beta p; with `check` the convergence test of iteration it + 1
 template <typename T>
-__global__ void k_cg_p(T* __restrict__ p, const T* __restrict__ r, const double* __restrict__ scal,
-                       int64_t n) {
-    const T beta = (T)scal[S_BETA];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+__global__ void __launch_bounds__(RT) k_cg_p(T* __restrict__ p, const T* __restrict__ r, double* __restrict__ scal,
+                                             int it, int64_t n, const double* __restrict__ partial, int np, int check,
+                                             double tol) {
+    __shared__ double sm[RT / 64];
+    const double done = scal[S_CGDONE];
+    if (done != 0.0 && done <= (double)it) return;
+    const double s = tl_sum<RT>(partial, np, 1, sm), rr = scal[S_FRR + (it & 1)];
+    const T beta = (T)((rr > 0.0 && scal[S_ALPHA] != 0.0) ? s / rr : 0.0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        scal[S_FRR + ((it + 1) & 1)] = s;
+        if (check) {
+            scal[S_RR] = s;
+            if (sqrt(s) <= tol) scal[S_CGDONE] = (double)(it + 1);
+        }
+    }
+    for (int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x; i < n; i += (int64_t)gridDim.x * RT)
         p[i] = r[i] + beta * p[i];
 }
 
@@ -359,6 +378,7 @@ struct Ctx {
     int applies = 0;
     double loop_ms = 0.0;    // device time of the one-kernel CG iterations (HIP events)
     int loop_iters = 0;
+    hipEvent_t const* ev = nullptr;   // two events of the solver's polls (null: it waits)
     bool run_layout = false; // FP32 vectors in the run layout of the element-per-lane kernels (n padded)
 };
 
@@ -606,31 +626,77 @@ int cg(Ctx& c, const T* b, T* x, T* r, T* p, T* q, double tol_abs, int max_it, i
             hipLaunchKernelGGL((k_dot<double, double>), dim3(NBLK), dim3(RT), 0, c.s, r, r, n, c.partial);
         }
     }
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, (int)S_RR, (int)FIN_STORE);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, (int)S_FRR, (int)FIN_STORE);
     hipLaunchKernelGGL(k_copy<T>, dim3(gb), dim3(256), 0, c.s, r, p, n);
+    hipLaunchKernelGGL(k_fill<double>, dim3(1), dim3(64), 0, c.s, c.scal + S_CGDONE, 0.0, (int64_t)1);
     CK(hipGetLastError());
     double rr;
-    if (int e = read_scal(c, S_RR, rr)) return e;
+    if (int e = read_scal(c, S_FRR, rr)) return e;
     iters = 0;
     res_out = std::sqrt(rr);
     if (res_out <= tol_abs) return STDG_OK;
-    while (iters < max_it) {
-        CK(Apply<T>::run(c, p, q)); c.applies++;
-        hipLaunchKernelGGL((k_dot<T, T>), dim3(NBLK), dim3(RT), 0, c.s, p, q, n, c.partial);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, 0, (int)FIN_CG_ALPHA);
-        hipLaunchKernelGGL(k_cg_xr<T>, dim3(NBLK), dim3(RT), 0, c.s, x, r, p, q, c.scal, n, c.partial);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, 0, (int)FIN_CG_BETA);
-        hipLaunchKernelGGL(k_cg_p<T>, dim3(gb), dim3(256), 0, c.s, p, r, c.scal, n);
+    // two elements per thread while that fills the card
+    const int rb = (int)std::min<int64_t>(NBLK, (n + 2 * RT - 1) / (2 * RT));
+    int64_t fused = 0;
+    if constexpr (std::is_same<T, double>::value)
+        if (c.op == 0 || c.op == 2) fused = apply_dot_blocks(c.m);
+    if (fused > (int64_t)NBLK * 207) fused = 0;
+    double* const part_rr = c.partial + (fused > 0 ? fused : NBLK);
+    int it = 0, slot = 0, pending = -1, found = 0;
+    auto look = [&](int sl) -> int {
+        if (c.ev) {
+            CK(hipEventSynchronize(c.ev[sl]));
+        } else {
+            CK(hipStreamSynchronize(c.s));
+        }
+        const double* h = c.hscal + 4 * sl;
+        if (!std::isfinite(h[S_RR])) { set_error("non-finite residual in CG"); return STDG_ERR_NUMERIC; }
+        res_out = std::sqrt(h[S_RR]);
+        if (h[S_CGDONE] == 0.0) return 0;
+        iters = (int)h[S_CGDONE];
+        return 1;
+    };
+    while (it < max_it && !found) {
+        const double* pq = c.partial;
+        int n_pq = rb;
+        if (fused > 0) {
+            if constexpr (std::is_same<T, double>::value)
+                CK(launch_apply_dot_f64(c.m, c.op == 2 ? c.m->d.Cid : c.m->d.C, p, q, c.partial, c.s));
+            n_pq = (int)fused;
+            if (fused > CG_PARTS) {
+                hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, n_pq, c.scal, (int)S_PQ,
+                                   (int)FIN_STORE);
+                pq = c.scal + S_PQ;
+                n_pq = 1;
+            }
+        } else {
+            CK(Apply<T>::run(c, p, q));
+            hipLaunchKernelGGL((k_dot<T, T>), dim3(rb), dim3(RT), 0, c.s, p, q, n, c.partial);
+        }
+        const bool check = (it + 1) % check_every == 0 || it + 1 == max_it;
+        hipLaunchKernelGGL(k_cg_xr<T>, dim3(rb), dim3(RT), 0, c.s, x, r, p, q, pq, n_pq, it, c.scal, n, part_rr);
+        hipLaunchKernelGGL(k_cg_p<T>, dim3(rb), dim3(RT), 0, c.s, p, r, c.scal, it, n, part_rr, rb, check ? 1 : 0,
+                           tol_abs);
         CK(hipGetLastError());
-        ++iters;
-        if (iters % check_every == 0 || iters == max_it) {
-            if (int e = read_scal(c, S_RR, rr)) return e;
-            if (!std::isfinite(rr)) { set_error("non-finite residual in CG"); return STDG_ERR_NUMERIC; }
-            res_out = std::sqrt(rr);
-            if (res_out <= tol_abs) return STDG_OK;
+        ++it;
+        if (!check) continue;
+        // with events the host reads one interval behind the queue, without
+        // them (the no-allocation solve) it waits for this one
+        CK(hipMemcpyAsync(c.hscal + 4 * slot, c.scal, 4 * sizeof(double), hipMemcpyDeviceToHost, c.s));
+        if (c.ev) {
+            CK(hipEventRecord(c.ev[slot], c.s));
+            if (pending >= 0) found = look(pending);
+            pending = slot;
+            slot ^= 1;
+        } else {
+            found = look(slot);
         }
     }
-    return STDG_NOT_CONVERGED;
+    if (!found && pending >= 0) found = look(pending);
+    if (found < 0) return found;
+    if (!found) iters = it;
+    c.applies += iters;
+    return found ? STDG_OK : STDG_NOT_CONVERGED;
 }
 
 // ---------------------------------------------------------------- BiCGStab
@@ -890,14 +956,13 @@ int ensure_workspace(stdg_mesh* m, int mres, bool need32) {
         STDG_HIP(hipMalloc(&w.partial, sizeof(double) * NBLK * 208));
         STDG_HIP(hipMalloc(&w.scal, sizeof(double) * (S_COUNT + 4 * 256 + 208 * 208)));
         STDG_HIP(hipHostMalloc(&w.hscal, sizeof(double) * (8 + 2 * TL_COUNT)));
+        for (hipEvent_t& e : w.ev) STDG_HIP(hipEventCreate(&e));
     }
     if (need32) {
         // long enough for the run layout as well (padded to whole 64-element runs)
         const size_t n32 = std::max<size_t>(n, (size_t)lane_len(m));
         for (float** f : {&w.r32, &w.p32, &w.q32, &w.x32, &w.b32, &w.p32b, &w.r32b, &w.q32b})
             if (!*f) STDG_HIP(hipMalloc(f, n32 * sizeof(float)));
-        if (!w.ev[0])
-            for (hipEvent_t& e : w.ev) STDG_HIP(hipEventCreate(&e));
     }
     if (mres > w.restart) {
         if (w.V) STDG_HIP(hipFree(w.V));
@@ -1085,6 +1150,7 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
     c.scal = w.scal;
     c.hscal = w.hscal;
     c.gm = w.scal + S_COUNT;
+    c.ev = w.ev[0] ? w.ev : nullptr;
     c.precond = o.precond == STDG_PRECOND_BLOCK_JACOBI;
     const int64_t n = c.n;
     const int gb = grid_for(n);
