@@ -7,9 +7,9 @@
 // B_{c,0..4} the class-deduplicated dt^2-scaled spatial blocks and C the G x G
 // time factor.
 //
-// FP64 (p <= 4, p_gamma <= 4): runs of 64 elements of one class on the FP64
-// matrix cores, the elements of other runs with a thread per (coupling, row)
-// (schur_apply_m64); meshes whose elements carry their own blocks stream them
+// FP64 (p <= 4, p_gamma <= 4): groups of up to 64 elements of one class on the
+// FP64 matrix cores, meshes without such groups with a thread per (coupling,
+// row) (schur_apply_m64); meshes whose elements carry their own blocks stream them
 // (cg_elem.hip).  FP32 vectors and other degrees: one thread per (element,
 // time node), the neighbour column x'_m = sum_b C_ab x_k[b][m] formed on the
 // fly, N outputs in registers; a wavefront of one class reads its blocks
@@ -113,14 +113,13 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
     }
 }
 
-// FP64 y = S x.  The first `run_blocks` workgroups take one 64-element run
-// each: the class's five blocks staged in LDS, a wavefront on 16 CW elements
-// with G columns each (mfma64.hpp: rows read 16 bytes a lane, an operand from
-// LDS serving CW G matrix instructions, results in place for the G x G time
-// factor and written in whole lines); runs of several classes are left to the
-// workgroups after them, which take EPB elements of `elems` (all of them when
-// it is null) with a thread per coupling and row, the five couplings in
-// parallel and summed through LDS.  Bound: HBM at p <= 2, the matrix cores and
+// FP64 y = S x.  With `seg_blocks` a workgroup takes a group of up to 64
+// elements of one class: the class's five blocks staged in LDS, a wavefront on
+// 16 CW elements with G columns each (mfma64.hpp: rows read 16 bytes a lane, an
+// operand from LDS serving CW G matrix instructions, results in place for the
+// G x G time factor and written in whole lines).  Otherwise it takes EPB
+// elements with a thread per coupling and row, the five couplings in parallel
+// and summed through LDS.  Bound: HBM at p <= 2, the matrix cores and
 // the operand reads at p = 3, 4, the launch (7.8 us in a loop from the host)
 // below 10^4 elements.  MI355X, kernels per entry on the vector units before
 // -> this one, us: 663,552 elements, p = 3, G = 1: 123 -> 102 (2.1 TB/s of x
@@ -132,11 +131,11 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
 template <int N, int G, int CW, bool DOT>
 __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __restrict__ BT,
                                                            const int32_t* __restrict__ cls,
-                                                           const int32_t* __restrict__ run_cls,
+                                                           const m64_i4* __restrict__ segs,
                                                            const int32_t* __restrict__ nbr,
                                                            const double* __restrict__ C, const double* x,
-                                                           double* __restrict__ y, int64_t E, uint32_t run_blocks,
-                                                           const int32_t* __restrict__ elems, int64_t n_elems,
+                                                           double* __restrict__ y, int64_t E, uint32_t seg_blocks,
+                                                           uint32_t n_segs,
                                                            double* __restrict__ part) {
     constexpr int NT = 256 / CW, NQ = M64<N>::NQ, NP = M64<N>::NP, NC = CW * G;
     constexpr int EPB = NT / (5 * N) > 0 ? NT / (5 * N) : 1;
@@ -146,17 +145,18 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
     __shared__ double A[LD];
     __shared__ double red[NT / 64];
     double d = 0.0;
-    if (blockIdx.x < run_blocks) {
-        const uint32_t run = (blockIdx.x % 8) * (run_blocks / 8) + blockIdx.x / 8;
-        const int64_t e0 = (int64_t)run * 64;
-        const int c = e0 < E ? run_cls[run] : -1;
-        if (c >= 0) {
+    if (seg_blocks > 0) {
+        const uint32_t group = m64_group(seg_blocks);
+        if (group < n_segs) {
+            const m64_i4 sg = segs[group];
+            const int c = sg.z;
+            const int64_t e0 = sg.x, e1 = e0 + sg.y;
             const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hi = lane >> 4, lo = lane & 3;
             int nb[5][CW];
 #pragma unroll
             for (int q = 0; q < CW; ++q) {
                 const int64_t e = e0 + 16 * (CW * w + q) + (lane & 15);
-                const bool valid = e < E;
+                const bool valid = e < e1;
                 nb[0][q] = valid ? (int)e : -1;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) nb[f + 1][q] = valid ? nbr[4 * e + f] : -1;
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
             __syncthreads();
 #pragma unroll
             for (int q = 0; q < CW; ++q) {
-                const int64_t first = e0 + 16 * (CW * w + q), left = E - first;
+                const int64_t first = e0 + 16 * (CW * w + q), left = e1 - first;
                 if (left <= 0) continue;
                 const int count = (int)(left < 16 ? left : 16) * G * N;
                 const int64_t at = first * G * N;
@@ -220,9 +220,9 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
         }
     } else {
         const int t = threadIdx.x, el = t / (5 * N), kr = t - el * (5 * N), k = kr / N, r = kr - k * N;
-        const int64_t item = (int64_t)(blockIdx.x - run_blocks) * EPB + el;
-        const bool on = el < EPB && item < n_elems;
-        const int64_t i = on ? (elems ? (int64_t)elems[item] : item) : 0;
+        const int64_t item = (int64_t)blockIdx.x * EPB + el;
+        const bool on = el < EPB && item < E;
+        const int64_t i = on ? item : 0;
         const int64_t s = !on ? -1 : (k == 0 ? i : (int64_t)nbr[4 * i + (k - 1)]);
         double acc[G];
 #pragma unroll
@@ -265,38 +265,31 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
     }
 }
 
-// The launch's workgroups.  Runs where at most a quarter of them mix classes,
-// small meshes too (us, runs / one by one: 2,058 elements, p = 3, G = 2 6.5 /
-// 8.5; 48,000, p = 1, G = 2 5.5 / 8.0; 1,296 and 6,000, p = 2 3.5 / 4.1; 3,072,
-// p = 4, G = 2 14.1 / 25.0; equal at 750 and 1,296, p = 3); beyond that most
-// workgroups of a run would find nothing to do.
+// The launch's workgroups: groups where they fill (segs_fill), small meshes too
+// (us, groups / one by one: 2,058 elements, p = 3, G = 2 6.5 / 8.5; 48,000,
+// p = 1, G = 2 5.5 / 8.0; 3,072, p = 4, G = 2 14.1 / 25.0; equal at 750 and 1,296,
+// p = 3).
 struct M64Grid {
-    uint32_t run_blocks, blocks;
-    const int32_t* elems;
-    int64_t n_elems;
+    uint32_t seg_blocks, blocks;
 };
 template <int N, int CW> static M64Grid m64_grid(const stdg_mesh* m) {
     constexpr int EPB = 256 / CW / (5 * N) > 0 ? 256 / CW / (5 * N) : 1;
-    const int64_t runs = (m->E + 63) / 64;
-    M64Grid g;
-    const bool by_run = 4 * m->d.n_mixed_runs <= runs;
-    g.run_blocks = by_run ? (uint32_t)((runs + 7) / 8 * 8) : 0;
-    g.elems = by_run ? m->d.mixed_elems : nullptr;
-    g.n_elems = by_run ? m->d.n_mixed_elems : m->E;
-    g.blocks = g.run_blocks + (uint32_t)((g.n_elems + EPB - 1) / EPB);
-    return g;
+    const bool fill = segs_fill(m);
+    return {fill ? m64_blocks(m->d.n_segs) : 0, fill ? m64_blocks(m->d.n_segs) : (uint32_t)((m->E + EPB - 1) / EPB)};
 }
 
 template <int N, int G, int CW>
 static hipError_t launch_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
                              hipStream_t s) {
     const M64Grid g = m64_grid<N, CW>(m);
+    const m64_i4* segs = (const m64_i4*)m->d.segs;
+    const uint32_t ns = (uint32_t)m->d.n_segs;
     if (part)
         hipLaunchKernelGGL((schur_apply_m64<N, G, CW, true>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
-                           m->d.cls, m->d.run_cls, m->d.nbr, C, x, y, m->E, g.run_blocks, g.elems, g.n_elems, part);
+                           m->d.cls, segs, m->d.nbr, C, x, y, m->E, g.seg_blocks, ns, part);
     else
         hipLaunchKernelGGL((schur_apply_m64<N, G, CW, false>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
-                           m->d.cls, m->d.run_cls, m->d.nbr, C, x, y, m->E, g.run_blocks, g.elems, g.n_elems, part);
+                           m->d.cls, segs, m->d.nbr, C, x, y, m->E, g.seg_blocks, ns, part);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Space-time DG convection with the Rusanov flux (eq. convdg) on the FP64
-// matrix cores, for meshes whose 64-element runs share a geometry class.
+// matrix cores, for meshes whose groups of one geometry class fill.
 //
 // Evaluating the velocity at the quadrature points and testing the fluxes
 // against the basis are contractions with tables that a class (the volume
@@ -9,7 +9,7 @@
 // from its three components, and the fluxes are the contraction operand
 // (over the points) of the second product as they stand.
 //
-// One workgroup per run and component-wise 16 elements per wavefront; the
+// One workgroup per group and component-wise 16 elements per wavefront; the
 // time points run inside, their sums weighted into the G output rows in
 // registers.  The tables pass through LDS in chunks of QC points: one copy
 // [point][N padded] serves both products.  663,552 elements, p = 3: 60 matrix
@@ -68,24 +68,26 @@ __device__ __forceinline__ void test_points(const double* L, int g, int lo, int 
 
 template <int N, int G>
 __global__ void __launch_bounds__(CT) kc_convection(
-    const double* __restrict__ vbar, const double* __restrict__ vbc, const int32_t* __restrict__ run_cls,
+    const double* __restrict__ vbar, const double* __restrict__ vbc, const m64_i4* __restrict__ segs,
     const int32_t* __restrict__ nbr, const int64_t* __restrict__ tet_face, const double* __restrict__ cJinv,
     const double* __restrict__ cdet, const double* __restrict__ cnrm, const double* __restrict__ PHf,
     const double* __restrict__ PHn, const double* __restrict__ FW, const double* __restrict__ PHv,
     const double* __restrict__ dPHv, const double* __restrict__ wv, const double* __restrict__ tw,
     const double* __restrict__ gq, int nqv, int nqf, int qt, double dt, double* __restrict__ ups, int64_t E, int64_t F,
-    uint32_t n_runs) {
+    uint32_t n_segs) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP;
     // volume: values and the three gradient components; faces: own and neighbour's values
     constexpr int LD = 4 * QC * NP > 64 * G * N ? 4 * QC * NP : 64 * G * N;
     __shared__ double L[LD];
     __shared__ double Wq[QC];
-    const uint32_t run = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    if (run >= n_runs) return;
-    const int cl = run_cls[run];
+    const uint32_t group = m64_group(gridDim.x);
+    if (group >= n_segs) return;
+    const m64_i4 sg = segs[group];
+    const int cl = sg.z;
+    const int64_t e0 = sg.x, e1 = e0 + sg.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hi = lane >> 4, lo = lane & 3;
-    const int64_t e = (int64_t)run * 64 + 16 * wave + (lane & 15);
-    const bool valid = e < E;
+    const int64_t e = e0 + 16 * wave + (lane & 15);
+    const bool valid = e < e1;
     const int64_t cs = E * G * N;
     // coefficients at a time point of the element row at `base` of a vector
     // with component stride `str`
@@ -160,7 +162,7 @@ __global__ void __launch_bounds__(CT) kc_convection(
             const int64_t k = valid ? nbr[4 * e + f] : -1;
             double xn[3][NQ];
             // (the elements of a class have the same boundary faces)
-            if (nbr[4 * (int64_t)run * 64 + f] >= 0) coeffs(vbar, E, k, valid, gt, xn);
+            if (nbr[4 * e0 + f] >= 0) coeffs(vbar, E, k, valid, gt, xn);
             else coeffs(vbc, F, valid ? tet_face[4 * e + f] : -1, valid, gt, xn);
             const double* nr = cnrm + (int64_t)cl * 12 + f * 3;
             const double n0 = nr[0], n1 = nr[1], n2 = nr[2];
@@ -200,7 +202,7 @@ __global__ void __launch_bounds__(CT) kc_convection(
                 for (int c = 0; c < 3; ++c) acc[a][rg][c] += gt[a] * o[rg][c];
     }
     __syncthreads();
-    const int64_t first = (int64_t)run * 64 + 16 * wave, left = E - first;
+    const int64_t first = e0 + 16 * wave, left = e1 - first;
     if (left <= 0) return;
     const int count = (int)(left < 16 ? left : 16) * G * N;
 #pragma unroll
@@ -215,19 +217,18 @@ template <int N, int G>
 hipError_t launch_conv(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s) {
     const PicardTables& t = m->pt;
     const PicardDevice& d = m->pd;
-    const uint32_t runs = (uint32_t)((m->E + 63) / 64);
-    hipLaunchKernelGGL((kc_convection<N, G>), dim3((runs + 7) / 8 * 8), dim3(CT), 0, s, vbar, vbc, m->d.run_cls,
+    hipLaunchKernelGGL((kc_convection<N, G>), dim3(m64_blocks(m->d.n_segs)), dim3(CT), 0, s, vbar, vbc, (const m64_i4*)m->d.segs,
                        m->d.nbr, d.tet_face, d.cJinv, d.cdet, d.cnrm, d.PHf, d.PHn, d.FW, d.PHv, d.dPHv, d.wv, d.tw,
-                       d.gq, t.nqv, t.nqf, t.qt, m->cfg.dt, ups, m->E, (int64_t)m->faces.size(), runs);
+                       d.gq, t.nqv, t.nqf, t.qt, m->cfg.dt, ups, m->E, (int64_t)m->faces.size(), (uint32_t)m->d.n_segs);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// one class per run, the sums of all time nodes in registers (N G up to 40),
+// groups that fill, the sums of all time nodes in registers (N G up to 40),
 // and buffer offsets below 2 GiB
 hipError_t conv_mfma(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s) {
-    if (!m->d.runs_uniform || 8 * (int64_t)m->faces.size() * m->Nst >= ((int64_t)1 << 31)) return hipErrorNotSupported;
+    if (!segs_fill(m) || 8 * (int64_t)m->faces.size() * m->Nst >= ((int64_t)1 << 31)) return hipErrorNotSupported;
 #define STDG_CV(n, g) \
     if (m->N == n && m->G == g) return launch_conv<n, g>(m, vbar, vbc, ups, s);
     STDG_CV(4, 1) STDG_CV(4, 2) STDG_CV(4, 3) STDG_CV(4, 4) STDG_CV(4, 5)

@@ -72,11 +72,10 @@ struct DeviceTables {
     double* elem_ops64 = nullptr; // per-element FP64 operator blocks of the FP64 apply on such meshes
     float* own_inv = nullptr;     // inverse own blocks per class for the element-major two-level kernels
     float* lane_ops = nullptr;    // class operands of the element-per-lane kernels (null: a run mixes classes)
-    int runs_uniform = 0;         // every 64-element run of the element order holds one class
-    int32_t* run_cls = nullptr;   // [runs] class of a one-class 64-element run, -1 for a run of several
-    int32_t* mixed_elems = nullptr;   // elements of the runs of several classes
-    int64_t n_mixed_elems = 0;
-    int64_t n_mixed_runs = 0;
+    // consecutive elements of one class, up to 64 of them (a "group"): first
+    // element, count, class, 0
+    int32_t* segs = nullptr;
+    int64_t n_segs = 0;
     int32_t* cls = nullptr;       // [E]
     int32_t* nbr = nullptr;       // [E][4]  -1 on a boundary face
     double* C = nullptr;          // [G][G]  time factor W T^-1 W
@@ -134,7 +133,8 @@ struct PicardDevice {
     int64_t* fr = nullptr;           // [F] right element (-1 boundary)
     int32_t* flf = nullptr;          // [F] left local face
     int32_t* frf = nullptr;          // [F] right local face
-    int32_t* face_groups = nullptr;  // [ceil(F / 64)][4] groups of 64 faces (rows_mfma.hip)
+    int32_t* face_groups = nullptr;  // [n_face_groups][4] consecutive faces of one left and one right block (rows_mfma.hip)
+    int64_t n_face_groups = 0;
     double* work = nullptr;          // step workspace
     size_t work_len = 0;
     double* conv_tmp = nullptr;      // convection sums per time point [qt][3][E][N]

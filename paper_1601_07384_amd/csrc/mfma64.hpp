@@ -23,6 +23,14 @@ typedef double m64_d2 __attribute__((ext_vector_type(2)));
 // byte offset past every buffer (loads give 0) that a row's length does not wrap
 constexpr uint32_t M64_OOB = 0xFFFF0000u;
 
+// A group of entities that share their blocks (Mesh tables `segs`,
+// `face_groups`): x the first, y their number (up to 64), z (and w) the blocks.
+typedef int m64_i4 __attribute__((ext_vector_type(4)));
+
+// workgroup -> group, consecutive ones on one XCD (grids are multiples of 8)
+__device__ inline uint32_t m64_group(uint32_t blocks) { return (blockIdx.x % 8) * (blocks / 8) + blockIdx.x / 8; }
+inline unsigned m64_blocks(int64_t groups) { return (unsigned)((groups + 7) / 8 * 8); }
+
 template <int N> struct M64 {
     static constexpr int NQ = (N + 3) / 4;      // contraction steps and row groups
     static constexpr int NP = 4 * NQ;           // padded rows

@@ -7,6 +7,7 @@
 // Every spatial block is N x N row-major; a kernel thread computes one output
 // row r of one (component, element or face, time node).
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <numeric>
@@ -578,12 +579,12 @@ int upload(T*& dst, const std::vector<T>& src) {
 
 }  // namespace
 
-// Block-row steps: the matrix-core kernels of rows_mfma.hip where classes fill
-// wavefronts, the register kernels of picard_fast.hip for other meshes at
+// Block-row steps: the matrix-core kernels of rows_mfma.hip where the groups of
+// one class fill, the register kernels of picard_fast.hip for other meshes at
 // p <= 4, the thread-per-coefficient kernels above otherwise.
 hipError_t run_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0,
                       int64_t f1, hipStream_t s) {
-    if (f0 == 0 && rows_mfma_supported(m)) return rows_goback(m, vbar, vbdry, out, f0, f1, s);
+    if (rows_mfma_supported(m, true)) return rows_goback(m, vbar, vbdry, out, f0, f1, s);
     if (fast_rows_supported(m)) return fast_goback(m, vbar, vbdry, out, f0, f1, s);
     const PicardDevice& d = m->pd;
     const int64_t n = 3 * (f1 - f0) * m->G * m->N;
@@ -594,7 +595,7 @@ hipError_t run_goback(const stdg_mesh* m, const double* vbar, const double* vbdr
 }
 
 hipError_t run_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s) {
-    if (rows_mfma_supported(m)) return rows_average(m, vhat, vbar, s);
+    if (rows_mfma_supported(m, false)) return rows_average(m, vhat, vbar, s);
     if (fast_rows_supported(m)) return fast_average(m, vhat, vbar, s);
     const int64_t n = 3 * m->E * m->Nst;
     hipLaunchKernelGGL(k_average, dim3(nblk(n)), dim3(256), 0, s, m->pd.A, m->d.cls, m->pd.tet_face, vhat, vbar, m->E,
@@ -603,7 +604,7 @@ hipError_t run_average(const stdg_mesh* m, const double* vhat, double* vbar, hip
 }
 
 hipError_t run_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s) {
-    if (rows_mfma_supported(m)) return rows_dualgrad(m, p, dt, w, s);
+    if (rows_mfma_supported(m, true)) return rows_dualgrad(m, p, dt, w, s);
     if (fast_rows_supported(m)) return fast_dualgrad(m, p, dt, w, s);
     const PicardDevice& d = m->pd;
     const int64_t F = (int64_t)m->faces.size();
@@ -613,7 +614,7 @@ hipError_t run_dualgrad(const stdg_mesh* m, const double* p, double dt, double* 
 }
 
 hipError_t run_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, double* b, hipStream_t s) {
-    if (rows_mfma_supported(m)) return rows_rhs_pressure(m, Fv, dt, b, s);
+    if (rows_mfma_supported(m, false)) return rows_rhs_pressure(m, Fv, dt, b, s);
     if (fast_rows_supported(m)) return fast_rhs_pressure(m, Fv, dt, b, s);
     hipLaunchKernelGGL(k_rhs_pressure, dim3(nblk(m->E * m->Nst)), dim3(256), 0, s, m->pd.QT, m->d.cls, m->pd.tet_face,
                        m->pd.W, Fv, dt, b, m->E, (int64_t)m->faces.size(), m->G, m->N);
@@ -622,7 +623,7 @@ hipError_t run_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, dou
 
 hipError_t run_visc_rhs(const stdg_mesh* m, const double* vprev, const double* ups, const double* lam,
                         const double* vbc, double* rhs, hipStream_t s) {
-    if (rows_mfma_supported(m)) return rows_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
+    if (rows_mfma_supported(m, false)) return rows_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
     if (fast_rows_supported(m)) return fast_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
     const PicardDevice& d = m->pd;
     hipLaunchKernelGGL(k_visc_rhs, dim3(nblk(3 * m->E * m->Nst)), dim3(256), 0, s, d.MIT, d.BB, m->d.cls, m->d.nbr,
@@ -714,22 +715,21 @@ int upload_picard_tables(stdg_mesh* m) {
     if ((e = upload(d.fl, fl)) || (e = upload(d.fr, fr)) || (e = upload(d.flf, flf)) || (e = upload(d.frf, frf)) ||
         (e = upload(d.tet_face, m->tet_face)))
         return e;
-    // groups of 64 faces: index, block of the left side, of the right side (-1:
-    // boundary), the left one -1 when the group holds several
-    std::vector<int32_t> order((F + 63) / 64), grp(4 * order.size());
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return fl[64 * (int64_t)a] < fl[64 * (int64_t)b]; });
+    // groups of up to 64 consecutive faces: first, count, block of the left
+    // side, of the right side (-1: boundary); in the order of their first left
+    // element, so that neighbouring groups of different sides share their
+    // elements' rows while they are cached
     auto left = [&](int64_t j) { return m->cls[fl[j]] * 4 + flf[j]; };
     auto right = [&](int64_t j) { return fr[j] >= 0 ? m->cls[fr[j]] * 4 + frf[j] : -1; };
-    for (size_t i = 0; i < order.size(); ++i) {
-        const int64_t j0 = 64 * (int64_t)order[i], j1 = std::min<int64_t>(j0 + 64, F) - 1;
-        bool one = true;
-        for (int64_t j = j0 + 1; j <= j1; ++j) one = one && left(j) == left(j0) && right(j) == right(j0);
-        grp[4 * i] = order[i];
-        grp[4 * i + 1] = one ? left(j0) : -1;
-        grp[4 * i + 2] = right(j0);
+    std::vector<std::array<int32_t, 4>> list;
+    for (int64_t j = 0, n = 1; j < F; j += n, n = 1) {
+        while (n < 64 && j + n < F && left(j + n) == left(j) && right(j + n) == right(j)) ++n;
+        list.push_back({(int32_t)j, (int32_t)n, (int32_t)left(j), (int32_t)right(j)});
     }
+    std::stable_sort(list.begin(), list.end(), [&](const auto& a, const auto& b) { return fl[a[0]] < fl[b[0]]; });
+    std::vector<int32_t> grp;
+    for (const auto& g : list) grp.insert(grp.end(), g.begin(), g.end());
+    d.n_face_groups = (int64_t)list.size();
     if ((e = upload(d.face_groups, grp))) return e;
     return STDG_OK;
 }

@@ -3,19 +3,20 @@
 // A2_mod): every output row of N coefficients is a sum of small N x N blocks
 // times gathered rows, the blocks shared by a geometry class (and local face).
 //
-// One workgroup takes 64 consecutive entities (elements, or faces, which are
-// sorted by the classes and local faces of their two sides).  When all 64
-// share their blocks, these are staged in LDS and four wavefronts take 16
-// entities each, their components and time nodes as further columns, so an
-// operand read from LDS feeds several matrix instructions and a row is read
-// with 16-byte loads (mfma64.hpp); otherwise (the groups where the class
-// changes, a few per class) the threads take one output value each.  They
-// replace, on meshes of mostly uniform groups, kernels with one output row
-// per thread, which read every row with a stride of N doubles between lanes.
-// What bounds them is the row traffic.  82,944 elements, p = 3, p_gamma = 1:
-// average 275 -> 76 us, goback 383 -> 170, right-hand side 266 -> 67;
-// 663,552 elements, p_gamma = 0: average 976 -> 291 us (0.96 GB), goback
-// 1,437 -> 357, gradient 912 -> 299, right-hand side 1,068 -> 273.
+// One workgroup takes a group of up to 64 consecutive entities that share
+// their blocks (elements of one class, or faces, which are sorted by the
+// classes and local faces of their two sides).  The blocks are staged in LDS
+// and four wavefronts take 16 entities each, their components and time nodes
+// as further columns, so an operand read from LDS feeds several matrix
+// instructions and a row is read with 16-byte loads (mfma64.hpp).  They
+// replace, where the groups fill, kernels with one output row per thread,
+// which read every row with a stride of N doubles between lanes.
+// What bounds them is the row traffic, on small meshes the latency of one
+// group.  82,944 elements, p = 3, p_gamma = 1: average 275 -> 76 us, goback 383
+// -> 170, right-hand side 266 -> 67; 663,552 elements, p_gamma = 0: average 976
+// -> 291 us (0.96 GB), goback 1,437 -> 357, gradient 912 -> 299, right-hand side
+// 1,068 -> 273; the three transfers of 1,296 elements with walls, p = 3,
+// p_gamma = 1: 162 -> 37.
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -66,23 +67,6 @@ __device__ __forceinline__ void put_rows(double* lds, int wave, int lane, int hi
                     [&](int i, m64_d2u v) { m64_put(dst, i, count, v); });
 }
 
-template <int N> __device__ inline double row_dot(const double* __restrict__ Bt, const double* __restrict__ x, int r) {
-    double s = 0.0;
-    for (int m = 0; m < N; ++m) s += Bt[m * N + r] * x[m];
-    return s;
-}
-
-// workgroup -> group, consecutive ones on one XCD
-__device__ inline uint32_t group_of() { return (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8; }
-
-// Group of 64 faces (sorted by their sides): the block of the left and of the
-// right side (class 4 + local face; right -1 on the boundary), left -1 when
-// the group holds several.  One record instead of the chain face -> element ->
-// class at the head of every workgroup; the records are in the order of
-// their first left element, so that neighbouring groups of different sides
-// share their elements' rows while they are cached.
-typedef int i4 __attribute__((ext_vector_type(4)));
-
 struct Lane {
     int lane, wave, hi, lo;
     __device__ Lane() {
@@ -95,33 +79,21 @@ struct Lane {
 
 // eq. average: vbar[c][i][a] = sum_f A_{i,f} vhat[c][face(i,f)][a]
 template <int N, int G>
-__global__ void __launch_bounds__(RT) kr_average(const double* __restrict__ At, const int32_t* __restrict__ cls,
-                                                 const int32_t* __restrict__ run_cls,
+__global__ void __launch_bounds__(RT) kr_average(const double* __restrict__ At, const m64_i4* __restrict__ segs,
                                                  const int64_t* __restrict__ tet_face, const double* __restrict__ vhat,
                                                  double* __restrict__ vbar, int64_t E, int64_t F, uint32_t n_groups) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
     __shared__ double A[lds_size<N, G, 4>()];
-    const uint32_t g = group_of();
-    if (g >= n_groups) return;
-    const int c0 = blockIdx.y * CP, c = run_cls[g];
-    const int64_t e0 = (int64_t)g * 64;
-    if (c < 0) {
-        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
-            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
-            const int64_t i = e0 + t / (N * G * CP);
-            if (i >= E) break;
-            double s = 0.0;
-            for (int f = 0; f < 4; ++f)
-                s += row_dot<N>(At + ((int64_t)cls[i] * 4 + f) * N * N, vhat + ((cc * F + tet_face[4 * i + f]) * G + a) * N, r);
-            vbar[((cc * E + i) * G + a) * N + r] = s;
-        }
-        return;
-    }
+    const uint32_t gi = m64_group(gridDim.x);
+    if (gi >= n_groups) return;
+    const m64_i4 g = segs[gi];
+    const int c0 = blockIdx.y * CP, c = g.z;
+    const int64_t e0 = g.x, e1 = e0 + g.y;
     m64_stage<N, RT>(At + (int64_t)c * 4 * N * N, A, 4);
     __syncthreads();
     const Lane l;
     const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
-    const bool valid = i < E;
+    const bool valid = i < e1;
     __amdgpu_buffer_rsrc_t rv[CP];
 #pragma unroll
     for (int k = 0; k < CP; ++k) rv[k] = m64_rsrc(vhat + (c0 + k) * F * G * N, (uint32_t)(8 * F * G * N));
@@ -143,45 +115,30 @@ __global__ void __launch_bounds__(RT) kr_average(const double* __restrict__ At, 
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < CP; ++k)
-        put_rows<N, G>(A, l.wave, l.lane, l.hi, vbar + (c0 + k) * E * G * N, e0 + 16 * l.wave, E, acc, k * G,
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, vbar + (c0 + k) * E * G * N, e0 + 16 * l.wave, e1, acc, k * G,
                        [](int) { return 1.0; });
 }
 
-// eq. goback on faces 0 .. f1: out[c][j][a] = GB_l vbar_l[a] + GB_r vbar_r[a]
+// eq. goback on faces f0 .. f1: out[c][j][a] = GB_l vbar_l[a] + GB_r vbar_r[a]
 // (boundary faces: one side, from vbdry)
 template <int N, int G>
-__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_goback(const double* __restrict__ GBt, const int32_t* __restrict__ cls,
-                                                const int64_t* __restrict__ fl, const int32_t* __restrict__ flf,
-                                                const int64_t* __restrict__ fr, const int32_t* __restrict__ frf,
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_goback(const double* __restrict__ GBt, const int64_t* __restrict__ fl,
+                                                const int64_t* __restrict__ fr,
                                                 const double* __restrict__ vbar, const double* __restrict__ vbdry,
-                                                double* __restrict__ out, int64_t f1, int64_t F, int64_t E,
-                                                const i4* __restrict__ grp, uint32_t n_groups) {
+                                                double* __restrict__ out, int64_t f0, int64_t f1, int64_t F, int64_t E,
+                                                const m64_i4* __restrict__ grp, uint32_t n_groups) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
     __shared__ double A[lds_size<N, G, 2>()];
-    const uint32_t gi = group_of();
+    const uint32_t gi = m64_group(gridDim.x);
     if (gi >= n_groups) return;
-    const i4 g = grp[gi];
+    const m64_i4 g = grp[gi];
     const int c0 = blockIdx.y * CP;
-    const int64_t j0 = (int64_t)g.x * 64, j1 = j0 + 63 < f1 ? j0 + 63 : f1 - 1;
-    if (j0 >= f1) return;
-    if (g.y < 0) {
-        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
-            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
-            const int64_t j = j0 + t / (N * G * CP);
-            if (j > j1) break;
-            const int64_t l = fl[j], rr = fr[j];
-            double s = row_dot<N>(GBt + ((int64_t)cls[l] * 4 + flf[j]) * N * N,
-                                  (rr >= 0 ? vbar : vbdry) + ((cc * E + l) * G + a) * N, r);
-            if (rr >= 0)
-                s += row_dot<N>(GBt + ((int64_t)cls[rr] * 4 + frf[j]) * N * N, vbar + ((cc * E + rr) * G + a) * N, r);
-            out[((cc * F + j) * G + a) * N + r] = s;
-        }
-        return;
-    }
-    const bool inner = g.z >= 0;
+    const int64_t j0 = g.x, j1 = j0 + g.y;
+    if (j0 < f0 || j0 >= f1) return;      // (f0 and f1 lie between groups)
+    const bool inner = g.w >= 0;
     const Lane l;
     const int64_t j = j0 + 16 * l.wave + (l.lane & 15);
-    const bool valid = j <= j1;
+    const bool valid = j < j1;
     const double* src = inner ? vbar : vbdry;
     double acc[NQ][CP * G];
     zero(acc);
@@ -199,8 +156,8 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_goback(const double* _
                 m64_load<N>(rv, side[q] >= 0 ? (uint32_t)((side[q] * G + a) * N * 8) : M64_OOB, l.hi, b[k * G + a]);
         }
         if (q == 0) {
-            m64_stage<N, RT>(GBt + (int64_t)g.y * N * N, A, 1);
-            if (inner) m64_stage<N, RT>(GBt + (int64_t)g.z * N * N, A + N * NP, 1);
+            m64_stage<N, RT>(GBt + (int64_t)g.z * N * N, A, 1);
+            if (inner) m64_stage<N, RT>(GBt + (int64_t)g.w * N * N, A + N * NP, 1);
             __syncthreads();
         }
         m64_block<N, CP * G>(A + q * N * NP, b, l.lo, l.hi, acc);
@@ -208,46 +165,30 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_goback(const double* _
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < CP; ++k)
-        put_rows<N, G>(A, l.wave, l.lane, l.hi, out + (c0 + k) * F * G * N, j0 + 16 * l.wave, j1 + 1, acc, k * G,
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, out + (c0 + k) * F * G * N, j0 + 16 * l.wave, j1, acc, k * G,
                        [](int) { return 1.0; });
 }
 
 // dual-grid pressure gradient: w[d][j][a] = dt sum_b TW[a][b] (US_{l,d} p_l[b] + UN_{l,d} p_r[b])
 template <int N, int G>
 __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_dualgrad(const double* __restrict__ USt, const double* __restrict__ UNt,
-                                                  const int32_t* __restrict__ cls, const int64_t* __restrict__ fl,
-                                                  const int32_t* __restrict__ flf, const int64_t* __restrict__ fr,
+                                                  const int64_t* __restrict__ fl, const int64_t* __restrict__ fr,
                                                   const double* __restrict__ TW,
                                                   const double* __restrict__ p, double dt, double* __restrict__ w,
-                                                  int64_t F, int64_t E, const i4* __restrict__ grp,
+                                                  int64_t F, int64_t E, const m64_i4* __restrict__ grp,
                                                   uint32_t n_groups) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, CP = comps<N, G>();
     __shared__ double A[lds_size<N, G, 2 * CP>()];
-    const uint32_t gi = group_of();
+    const uint32_t gi = m64_group(gridDim.x);
     if (gi >= n_groups) return;
-    const i4 g = grp[gi];
+    const m64_i4 g = grp[gi];
     const int d0 = blockIdx.y * CP;
-    const int64_t j0 = (int64_t)g.x * 64, j1 = j0 + 63 < F ? j0 + 63 : F - 1;
-    if (g.y < 0) {
-        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
-            const int r = t % N, a = t / N % G, d = d0 + t / (N * G) % CP;
-            const int64_t j = j0 + t / (N * G * CP);
-            if (j > j1) break;
-            const int64_t l = fl[j], rr = fr[j], key = ((int64_t)cls[l] * 4 + flf[j]) * 3 + d;
-            double s = 0.0;
-            for (int b = 0; b < G; ++b) {
-                s += TW[a * G + b] * row_dot<N>(USt + key * N * N, p + (l * G + b) * N, r);
-                if (rr >= 0) s += TW[a * G + b] * row_dot<N>(UNt + key * N * N, p + (rr * G + b) * N, r);
-            }
-            w[((d * F + j) * G + a) * N + r] = dt * s;
-        }
-        return;
-    }
-    const bool inner = g.z >= 0;
-    const int64_t key = (int64_t)g.y * 3 + d0;
+    const int64_t j0 = g.x, j1 = j0 + g.y;
+    const bool inner = g.w >= 0;
+    const int64_t key = (int64_t)g.z * 3 + d0;
     const Lane l;
     const int64_t j = j0 + 16 * l.wave + (l.lane & 15);
-    const bool valid = j <= j1;
+    const bool valid = j < j1;
     const __amdgpu_buffer_rsrc_t rp = m64_rsrc(p, (uint32_t)(8 * E * G * N));
     // both sides' rows in flight while the blocks are staged
     const int64_t side[2] = {valid ? fl[j] : -1, valid && inner ? fr[j] : -1};
@@ -282,39 +223,26 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_dualgrad(const double*
     __syncthreads();
 #pragma unroll
     for (int d = 0; d < CP; ++d)
-        put_rows<N, G>(A, l.wave, l.lane, l.hi, w + (d0 + d) * F * G * N, j0 + 16 * l.wave, j1 + 1, acc[d], 0,
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, w + (d0 + d) * F * G * N, j0 + 16 * l.wave, j1, acc[d], 0,
                        [dt](int) { return dt; });
 }
 
 // pressure right-hand side: b[i][a] = dt W_a sum_{f,d} Q^T_{i,f,d} Fv[d][face][a]
 template <int N, int G>
-__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __restrict__ QTt, const int32_t* __restrict__ cls,
-                                             const int32_t* __restrict__ run_cls, const int64_t* __restrict__ tet_face,
+__global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __restrict__ QTt, const m64_i4* __restrict__ segs,
+                                             const int64_t* __restrict__ tet_face,
                                              const double* __restrict__ W, const double* __restrict__ Fv, double dt,
                                              double* __restrict__ out, int64_t E, int64_t F, uint32_t n_groups) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP;
     __shared__ double A[lds_size<N, G, 3>()];
-    const uint32_t g = group_of();
-    if (g >= n_groups) return;
-    const int c = run_cls[g];
-    const int64_t e0 = (int64_t)g * 64;
-    if (c < 0) {
-        for (int t = threadIdx.x; t < 64 * G * N; t += RT) {
-            const int r = t % N, a = t / N % G;
-            const int64_t i = e0 + t / (N * G);
-            if (i >= E) break;
-            double s = 0.0;
-            for (int f = 0; f < 4; ++f)
-                for (int d = 0; d < 3; ++d)
-                    s += row_dot<N>(QTt + (((int64_t)cls[i] * 4 + f) * 3 + d) * N * N,
-                                    Fv + ((d * F + tet_face[4 * i + f]) * G + a) * N, r);
-            out[(i * G + a) * N + r] = dt * W[a] * s;
-        }
-        return;
-    }
+    const uint32_t gi = m64_group(gridDim.x);
+    if (gi >= n_groups) return;
+    const m64_i4 g = segs[gi];
+    const int c = g.z;
+    const int64_t e0 = g.x, e1 = e0 + g.y;
     const Lane l;
     const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
-    const bool valid = i < E;
+    const bool valid = i < e1;
     __amdgpu_buffer_rsrc_t rv[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) rv[d] = m64_rsrc(Fv + d * F * G * N, (uint32_t)(8 * F * G * N));
@@ -336,13 +264,13 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __re
         for (int d = 0; d < 3; ++d) m64_block<N, G>(A + d * N * NP, b[d], l.lo, l.hi, acc);
     }
     __syncthreads();
-    put_rows<N, G>(A, l.wave, l.lane, l.hi, out, e0 + 16 * l.wave, E, acc, 0, [&](int a) { return dt * W[a]; });
+    put_rows<N, G>(A, l.wave, l.lane, l.hi, out, e0 + 16 * l.wave, e1, acc, 0, [&](int a) { return dt * W[a]; });
 }
 
 // viscous right-hand side: M (sum_b g0g1[a][b] vprev_b - T[a][b] lam_b) - ups_a - nu dt W_a sum_{bdry f} BB_f vbc
 template <int N, int G>
 __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double* __restrict__ MIt, const double* __restrict__ BBt,
-                                                  const int32_t* __restrict__ cls, const int32_t* __restrict__ run_cls,
+                                                  const m64_i4* __restrict__ segs,
                                                   const int32_t* __restrict__ nbr, const int64_t* __restrict__ tet_face,
                                                   const double* __restrict__ g0g1, const double* __restrict__ Tm,
                                                   const double* __restrict__ W, const double* __restrict__ vprev,
@@ -351,32 +279,15 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double*
                                                   double* __restrict__ rhs, int64_t E, int64_t F, uint32_t n_groups) {
     constexpr int NQ = M64<N>::NQ, CP = comps<N, G>();
     __shared__ double A[lds_size<N, G, 1>()];
-    const uint32_t g = group_of();
-    if (g >= n_groups) return;
-    const int c0 = blockIdx.y * CP, c = run_cls[g];
-    const int64_t e0 = (int64_t)g * 64;
-    if (c < 0) {
-        for (int t = threadIdx.x; t < 64 * CP * G * N; t += RT) {
-            const int r = t % N, a = t / N % G, cc = c0 + t / (N * G) % CP;
-            const int64_t i = e0 + t / (N * G * CP);
-            if (i >= E) break;
-            const double* M = MIt + (int64_t)cls[i] * N * N;
-            double s = -ups[((cc * E + i) * G + a) * N + r];
-            for (int b = 0; b < G; ++b)
-                s += g0g1[a * G + b] * row_dot<N>(M, vprev + ((cc * E + i) * G + b) * N, r) -
-                     Tm[a * G + b] * row_dot<N>(M, lam + ((cc * E + i) * G + b) * N, r);
-            for (int f = 0; f < 4; ++f)
-                if (nbr[4 * i + f] < 0)
-                    s -= nu_dt * W[a] * row_dot<N>(BBt + ((int64_t)cls[i] * 4 + f) * N * N,
-                                                   vbc + ((cc * F + tet_face[4 * i + f]) * G + a) * N, r);
-            rhs[((cc * E + i) * G + a) * N + r] = s;
-        }
-        return;
-    }
+    const uint32_t gi = m64_group(gridDim.x);
+    if (gi >= n_groups) return;
+    const m64_i4 g = segs[gi];
+    const int c0 = blockIdx.y * CP, c = g.z;
+    const int64_t e0 = g.x, e1 = e0 + g.y;
     m64_stage<N, RT>(MIt + (int64_t)c * N * N, A, 1);
     const Lane l;
     const int64_t i = e0 + 16 * l.wave + (l.lane & 15);
-    const bool valid = i < E;
+    const bool valid = i < e1;
     double acc[NQ][CP * G];
     // start from -ups in the rows this lane will store
 #pragma unroll
@@ -433,22 +344,18 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double*
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < CP; ++k)
-        put_rows<N, G>(A, l.wave, l.lane, l.hi, rhs + (c0 + k) * E * G * N, e0 + 16 * l.wave, E, acc, k * G,
+        put_rows<N, G>(A, l.wave, l.lane, l.hi, rhs + (c0 + k) * E * G * N, e0 + 16 * l.wave, e1, acc, k * G,
                        [](int) { return 1.0; });
 }
 
-inline uint32_t groups(int64_t n) { return (uint32_t)((n + 63) / 64); }
-inline unsigned blocks(int64_t n) { return (unsigned)((groups(n) + 7) / 8 * 8); }
-
 }  // namespace
 
-// Meshes whose classes hold a wavefront of elements on average, with the runs
-// of several classes (and with them the face groups) a quarter at most, and
-// every component within the 2 GiB of a buffer offset.
-bool rows_mfma_supported(const stdg_mesh* m) {
-    const int64_t runs = (m->E + 63) / 64, F = (int64_t)m->faces.size();
-    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && (int64_t)m->n_classes * 64 <= m->E &&
-           4 * m->d.n_mixed_runs <= runs && 8 * F * m->Nst < ((int64_t)1 << 31);
+// groups of elements or of faces that fill, every component within the 2 GiB
+// of a buffer offset
+bool rows_mfma_supported(const stdg_mesh* m, bool faces) {
+    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 &&
+           (faces ? face_groups_fill(m) : segs_fill(m)) &&
+           8 * (int64_t)m->faces.size() * m->Nst < ((int64_t)1 << 31);
 }
 
 #define STDG_ROWS(CALL)                                                                     \
@@ -467,8 +374,8 @@ bool rows_mfma_supported(const stdg_mesh* m) {
 hipError_t rows_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s) {
     const int64_t E = m->E, F = (int64_t)m->faces.size();
 #define STDG_CALL(n, g)                                                                                           \
-    hipLaunchKernelGGL((kr_average<n, g>), dim3(blocks(E), 3 / comps<n, g>()), dim3(RT), 0, s, m->pd.At, m->d.cls, \
-                       m->d.run_cls, m->pd.tet_face, vhat, vbar, E, F, groups(E))
+    hipLaunchKernelGGL((kr_average<n, g>), dim3(m64_blocks(m->d.n_segs), 3 / comps<n, g>()), dim3(RT), 0, s, m->pd.At, \
+                       (const m64_i4*)m->d.segs, m->pd.tet_face, vhat, vbar, E, F, (uint32_t)m->d.n_segs)
     STDG_ROWS(STDG_CALL)
 #undef STDG_CALL
 }
@@ -478,12 +385,9 @@ hipError_t rows_goback(const stdg_mesh* m, const double* vbar, const double* vbd
     if (f1 <= f0) return hipSuccess;
     const PicardDevice& d = m->pd;
     const int64_t F = (int64_t)m->faces.size();
-    // (the records list all groups from face 0: those past f1 return; the
-    // boundary faces alone, f0 > 0, are the register kernel's)
-    if (f0 != 0) return hipErrorNotSupported;
 #define STDG_CALL(n, g)                                                                                               \
-    hipLaunchKernelGGL((kr_goback<n, g>), dim3(blocks(F), 3 / comps<n, g>()), dim3(RT), 0, s, d.GBt, m->d.cls,   \
-                       d.fl, d.flf, d.fr, d.frf, vbar, vbdry, out, f1, F, m->E, (const i4*)d.face_groups, groups(F))
+    hipLaunchKernelGGL((kr_goback<n, g>), dim3(m64_blocks(d.n_face_groups), 3 / comps<n, g>()), dim3(RT), 0, s, d.GBt, d.fl,       \
+                       d.fr, vbar, vbdry, out, f0, f1, F, m->E, (const m64_i4*)d.face_groups, (uint32_t)d.n_face_groups)
     STDG_ROWS(STDG_CALL)
 #undef STDG_CALL
 }
@@ -492,8 +396,8 @@ hipError_t rows_dualgrad(const stdg_mesh* m, const double* p, double dt, double*
     const PicardDevice& d = m->pd;
     const int64_t F = (int64_t)m->faces.size();
 #define STDG_CALL(n, g)                                                                                             \
-    hipLaunchKernelGGL((kr_dualgrad<n, g>), dim3(blocks(F), 3 / comps<n, g>()), dim3(RT), 0, s, d.USt, d.UNt,        \
-                       m->d.cls, d.fl, d.flf, d.fr, d.TW, p, dt, w, F, m->E, (const i4*)d.face_groups, groups(F))
+    hipLaunchKernelGGL((kr_dualgrad<n, g>), dim3(m64_blocks(d.n_face_groups), 3 / comps<n, g>()), dim3(RT), 0, s, d.USt, d.UNt,        \
+                       d.fl, d.fr, d.TW, p, dt, w, F, m->E, (const m64_i4*)d.face_groups, (uint32_t)d.n_face_groups)
     STDG_ROWS(STDG_CALL)
 #undef STDG_CALL
 }
@@ -501,8 +405,8 @@ hipError_t rows_dualgrad(const stdg_mesh* m, const double* p, double dt, double*
 hipError_t rows_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, double* b, hipStream_t s) {
     const int64_t E = m->E, F = (int64_t)m->faces.size();
 #define STDG_CALL(n, g)                                                                                          \
-    hipLaunchKernelGGL((kr_rhs<n, g>), dim3(blocks(E)), dim3(RT), 0, s, m->pd.QTt, m->d.cls, m->d.run_cls,        \
-                       m->pd.tet_face, m->pd.W, Fv, dt, b, E, F, groups(E))
+    hipLaunchKernelGGL((kr_rhs<n, g>), dim3(m64_blocks(m->d.n_segs)), dim3(RT), 0, s, m->pd.QTt, (const m64_i4*)m->d.segs,     \
+                       m->pd.tet_face, m->pd.W, Fv, dt, b, E, F, (uint32_t)m->d.n_segs)
     STDG_ROWS(STDG_CALL)
 #undef STDG_CALL
 }
@@ -512,9 +416,9 @@ hipError_t rows_visc_rhs(const stdg_mesh* m, const double* vprev, const double* 
     const PicardDevice& d = m->pd;
     const int64_t E = m->E, F = (int64_t)m->faces.size();
 #define STDG_CALL(n, g)                                                                                            \
-    hipLaunchKernelGGL((kr_visc_rhs<n, g>), dim3(blocks(E), 3 / comps<n, g>()), dim3(RT), 0, s, d.MIt, d.BBt,       \
-                       m->d.cls, m->d.run_cls, m->d.nbr, d.tet_face, d.g0g1, d.Tm, d.W, vprev, ups, lam, vbc,      \
-                       m->cfg.nu * m->cfg.dt, rhs, E, F, groups(E))
+    hipLaunchKernelGGL((kr_visc_rhs<n, g>), dim3(m64_blocks(m->d.n_segs), 3 / comps<n, g>()), dim3(RT), 0, s, d.MIt, d.BBt,       \
+                       (const m64_i4*)m->d.segs, m->d.nbr, d.tet_face, d.g0g1, d.Tm, d.W, vprev, ups, lam, vbc,      \
+                       m->cfg.nu * m->cfg.dt, rhs, E, F, (uint32_t)m->d.n_segs)
     STDG_ROWS(STDG_CALL)
 #undef STDG_CALL
 }

@@ -1,10 +1,10 @@
 // Viscous operator (eq. A1_mod) and its block-Jacobi step on the FP64 matrix
-// cores, for meshes whose 64-element runs share a geometry class:
+// cores, for meshes whose groups of one geometry class fill:
 //   y_i = D^-1 [ (MI (x) T) x_i + nu dt sum_k (SV_k (x) W) x_nb(k) ]   (PRE)
 // or the bracket alone, all three velocity components at once, with the dot
 // products BiCGStab needs of the result.
 //
-// One workgroup per run: the class's six N x N blocks (five couplings, mass)
+// One workgroup per group: the class's six N x N blocks (five couplings, mass)
 // and, with PRE, its NG x NG inverse diagonal block are staged in LDS; a
 // wavefront takes 16 elements with 3 G columns each (component, time node),
 // so an operand read from LDS feeds 3 G matrix instructions.  The bracket's
@@ -30,20 +30,22 @@ constexpr int VT = 256;     // threads: four wavefronts of 16 elements
 // (part[blk] and part[gridDim.x + blk])
 template <int N, int G, bool PRE, int DOTS>
 __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt, const double* __restrict__ MIt,
-                                                  const double* __restrict__ DV, const int32_t* __restrict__ run_cls,
+                                                  const double* __restrict__ DV, const m64_i4* __restrict__ segs,
                                                   const int32_t* __restrict__ nbr, const double* __restrict__ Tm,
                                                   const double* __restrict__ W, double nu_dt, const double* x,
                                                   double* __restrict__ y, const double* w, double* __restrict__ part,
-                                                  int64_t E, uint32_t n_runs, uint32_t xbytes) {
+                                                  int64_t E, uint32_t n_segs, uint32_t xbytes) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, NC = 3 * G;
     static_assert((N * G) % 2 == 0, "rows leave two values at a time");
     __shared__ double A[6 * N * NP > 64 * G * N ? 6 * N * NP : 64 * G * N];
     __shared__ double Dl[PRE ? G * NP * G * NP : 1];
     __shared__ double red[VT / 64];
-    const uint32_t run = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const uint32_t group = m64_group(gridDim.x);
     double d0 = 0.0, d1 = 0.0;
-    if (run < n_runs) {                                 // uniform over the workgroup
-        const int c = run_cls[run];
+    if (group < n_segs) {                               // uniform over the workgroup
+        const m64_i4 sg = segs[group];
+        const int c = sg.z;
+        const int64_t e1 = (int64_t)sg.x + sg.y;
         m64_stage<N, VT>(SVt + (int64_t)c * 5 * N * N, A, 5);
         m64_stage<N, VT>(MIt + (int64_t)c * N * N, A + 5 * N * NP, 1);
         if (PRE) {
@@ -56,8 +58,8 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
         }
         __syncthreads();
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hi = lane >> 4, lo = lane & 3;
-        const int64_t e = (int64_t)run * 64 + 16 * wave + (lane & 15);
-        const bool valid = e < E;
+        const int64_t e = (int64_t)sg.x + 16 * wave + (lane & 15);
+        const bool valid = e < e1;
         int nb[5];
         nb[0] = valid ? (int)e : -1;
 #pragma unroll
@@ -134,7 +136,7 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
         }
         // out through the blocks' LDS, the dots beside the stores
         __syncthreads();
-        const int64_t first = (int64_t)run * 64 + 16 * wave, left = E - first;
+        const int64_t first = (int64_t)sg.x + 16 * wave, left = e1 - first;
         const int count = left <= 0 ? 0 : (int)(left < 16 ? left : 16) * G * N;
         if (count > 0)
 #pragma unroll
@@ -168,19 +170,19 @@ template <int N, int G, bool PRE, int DOTS>
 hipError_t launch_visc(const stdg_mesh* m, const double* x, double* y, const double* w, double* part, hipStream_t s) {
     const PicardDevice& d = m->pd;
     hipLaunchKernelGGL((k_visc_mfma<N, G, PRE, DOTS>), dim3((unsigned)visc_mfma_blocks(m)), dim3(VT), 0, s, d.SVt, d.MIt,
-                       d.DV, m->d.run_cls, m->d.nbr, d.Tm, d.W, m->cfg.nu * m->cfg.dt, x, y, w, part, m->E,
-                       (uint32_t)((m->E + 63) / 64), (uint32_t)(8 * m->E * m->Nst));
+                       d.DV, (const m64_i4*)m->d.segs, m->d.nbr, d.Tm, d.W, m->cfg.nu * m->cfg.dt, x, y, w, part, m->E,
+                       (uint32_t)m->d.n_segs, (uint32_t)(8 * m->E * m->Nst));
     return hipGetLastError();
 }
 
 }  // namespace
 
-int64_t visc_mfma_blocks(const stdg_mesh* m) { return ((m->E + 63) / 64 + 7) / 8 * 8; }
+int64_t visc_mfma_blocks(const stdg_mesh* m) { return m64_blocks(m->d.n_segs); }
 
-// N G up to 40 (the inverse diagonal block in LDS), one class per run, and
+// N G up to 40 (the inverse diagonal block in LDS), groups that fill, and
 // offsets within a component below 2 GiB
 bool visc_mfma_supported(const stdg_mesh* m) {
-    return m->d.runs_uniform && (m->N == 4 || m->N == 10 || m->N == 20) && m->G <= 5 && m->Nst <= 40 &&
+    return segs_fill(m) && (m->N == 4 || m->N == 10 || m->N == 20) && m->G <= 5 && m->Nst <= 40 &&
            8 * m->E * m->Nst < ((int64_t)1 << 31);
 }
 
