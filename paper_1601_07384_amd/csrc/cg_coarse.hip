@@ -44,8 +44,6 @@ namespace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int MAXN = 80;        // grid lines per direction (two padded planes in 64 KB of LDS)
-constexpr int PT = 512;         // threads of the plane kernel
-constexpr int CT = 256;         // threads of the column kernel
 constexpr int CC = 32;          // columns per workgroup of the column kernel
 // lanes per grid node of the restriction: a node of a tensor grid is reached
 // by about 24 corners, one of a grid between scattered vertices by about 190
@@ -60,7 +58,6 @@ template <bool HASW>
 __global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ slot, const float* __restrict__ w, int K,
                                                   const float* __restrict__ e4, int64_t estr, float* __restrict__ g,
                                                   int nodes, const double* __restrict__ scal, int it) {
-    if (tl_done(scal, it)) return;
     constexpr int RL = HASW ? RLW : RL1;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t j = t / RL;
@@ -76,48 +73,68 @@ __global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ sl
     }
 #pragma unroll
     for (int o = RL / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, RL);
-    if (l == 0 && j < nodes) g[(int64_t)a * nodes + j] = s;
+    if (l == 0 && j < nodes && !tl_done(scal, it)) g[(int64_t)a * nodes + j] = s;
 }
 
-// one plane z = const: out = My^T in Mx, in and out [ny][nx] (Mx, My padded
-// to multiples of 16 with zeros; V forward, V^T backward)
-__global__ void __launch_bounds__(PT) k_plane(const float* __restrict__ in, float* __restrict__ out,
-                                              const float* __restrict__ Mx, const float* __restrict__ My, int nx,
-                                              int ny, const double* __restrict__ scal, int it) {
-    extern __shared__ float sh[];
-    if (tl_done(scal, it)) return;
-    const int px = (nx + 15) / 16 * 16, py = (ny + 15) / 16 * 16, sx = px + 1;
-    float* X = sh;                   // [py][sx]
-    float* U = sh + py * sx;
+// threads of the plane and column kernels on grids padded to 16 T lines: a
+// wavefront per 16 x 16 tile of a result while a workgroup holds as many
+template <int T> constexpr int plane_threads() { return T * T < 4 ? 256 : (T * T > 16 ? 1024 : 64 * T * T); }
+template <int T> constexpr int column_threads() { return T < 2 ? 256 : 128 * T; }
+
+// One plane z = const: out = My^T in Mx, in and out [ny][nx] (Mx, My padded
+// to multiples of 16 with zeros; V forward, V^T backward; the larger pad is
+// 16 T).  The wavefront's operands of both products are under way before the
+// plane is staged: loaded inside the products they cost a cache latency per
+// 16 lines (24^3, two time nodes: 4.4 -> 3.7 us; the column kernel 5.6 -> 4.4).
+template <int T>
+__global__ void __launch_bounds__(plane_threads<T>()) k_plane(const float* __restrict__ in, float* __restrict__ out,
+                                                              const float* __restrict__ Mx,
+                                                              const float* __restrict__ My, int nx, int ny,
+                                                              const double* __restrict__ scal, int it) {
+    constexpr int P = 16 * T, S = P + 1, NT = plane_threads<T>(), NW = NT / 64;
+    __shared__ float X[P * S], U[P * S];
+    const int px = (nx + 15) / 16 * 16, py = (ny + 15) / 16 * 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
-    const float* src = in + (int64_t)blockIdx.x * nx * ny;
-    for (int t = tid; t < py * px; t += PT) {
-        const int i = t / px, j = t - i * px;
-        X[i * sx + j] = (i < ny && j < nx) ? src[i * nx + j] : 0.0f;
+    float bx[4 * T], ay[4 * T];
+    auto column = [&](const float* __restrict__ M, int pad, int c, float (&v)[4 * T]) {
+#pragma unroll
+        for (int k = 0; k < 4 * T; ++k) v[k] = 4 * k < pad && c < pad ? M[(4 * k + hi) * pad + c] : 0.0f;
+    };
+    if (wave < T * T) {
+        column(Mx, px, wave % T * 16 + lo, bx);
+        column(My, py, wave / T * 16 + lo, ay);
     }
+    const float* src = in + (int64_t)blockIdx.x * nx * ny;
+#pragma unroll
+    for (int t = tid; t < P * P; t += NT) {
+        const int i = t / P, j = t % P;
+        X[i * S + j] = (i < ny && j < nx) ? src[i * nx + j] : 0.0f;
+    }
+    if (tl_done(scal, it)) return;
     __syncthreads();
-    const int tx = px / 16, tiles = (py / 16) * tx;
-    for (int t = wave; t < tiles; t += PT / 64) {
-        const int r0 = t / tx * 16, c0 = t % tx * 16;
+#pragma unroll
+    for (int t0 = 0; t0 < T * T; t0 += NW) {
+        const int t = t0 + wave, r0 = t / T * 16, c0 = t % T * 16;
+        if (t >= T * T) break;
+        if (t0 > 0) column(Mx, px, c0 + lo, bx);
         f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int k1 = 0; k1 < px; k1 += 16)
 #pragma unroll
-            for (int k = k1; k < k1 + 16; k += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[(r0 + lo) * sx + k + hi], Mx[(k + hi) * px + c0 + lo], acc, 0,
-                                                       0, 0);
+        for (int k = 0; k < 4 * T; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[(r0 + lo) * S + 4 * k + hi], bx[k], acc, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) U[(r0 + 4 * hi + r) * sx + c0 + lo] = acc[r];
+        for (int r = 0; r < 4; ++r) U[(r0 + 4 * hi + r) * S + c0 + lo] = acc[r];
     }
     __syncthreads();
     float* dst = out + (int64_t)blockIdx.x * nx * ny;
-    for (int t = wave; t < tiles; t += PT / 64) {
-        const int r0 = t / tx * 16, c0 = t % tx * 16;
-        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int k1 = 0; k1 < py; k1 += 16)
 #pragma unroll
-            for (int k = k1; k < k1 + 16; k += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(My[(k + hi) * py + r0 + lo], U[(k + hi) * sx + c0 + lo], acc, 0,
-                                                       0, 0);
+    for (int t0 = 0; t0 < T * T; t0 += NW) {
+        const int t = t0 + wave, r0 = t / T * 16, c0 = t % T * 16;
+        if (t >= T * T) break;
+        if (t0 > 0) column(My, py, r0 + lo, ay);
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < 4 * T; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ay[k], U[(4 * k + hi) * S + c0 + lo], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (r0 + 4 * hi + r < ny && c0 + lo < nx) dst[(r0 + 4 * hi + r) * nx + c0 + lo] = acc[r];
@@ -126,67 +143,152 @@ __global__ void __launch_bounds__(PT) k_plane(const float* __restrict__ in, floa
 
 // CC columns of one time node: forward in z, times scale / (l_x + l_y + l_z)
 // (0 for the constant mode), backward in z, in place; the workgroup's share
-// of the sum of (transformed value)^2 times that factor, i.e. of (P^T r) . K (P^T r)
-__global__ void __launch_bounds__(CT) k_columns(float* __restrict__ t, const float* __restrict__ Vz,
-                                                const float* __restrict__ VzT, const float* __restrict__ lam, int nx,
-                                                int ny, int nz, float scale, float cut, double* __restrict__ part,
-                                                const double* __restrict__ scal, int it) {
-    extern __shared__ float sh[];
-    __shared__ double red[CT / 64];
-    if (tl_done(scal, it)) return;
-    constexpr int S = CC + 1;
-    const int pz = (nz + 15) / 16 * 16, cols = nx * ny;
-    float* X = sh;                   // [pz][S]
-    float* U = sh + pz * S;
+// of the sum of (transformed value)^2 times that factor, i.e. of (P^T r) . K (P^T r).
+// pz = 16 T; operands under way first, as in k_plane.
+template <int T>
+__global__ void __launch_bounds__(column_threads<T>()) k_columns(float* __restrict__ t, const float* __restrict__ Vz,
+                                                                 const float* __restrict__ VzT,
+                                                                 const float* __restrict__ lam, int nx, int ny, int nz,
+                                                                 float scale, float cut, double* __restrict__ part,
+                                                                 const double* __restrict__ scal, int it) {
+    constexpr int P = 16 * T, S = CC + 1, NT = column_threads<T>(), CT = CC / 16;
+    __shared__ float X[P * S], U[P * S];
+    __shared__ double red[NT / 64];
+    const int cols = nx * ny;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
-    const int c0 = blockIdx.x * CC;
+    const int c0 = blockIdx.x * CC, r0 = wave / CT * 16, b0 = wave % CT * 16;
+    const bool tile = wave < T * CT;
     float* ta = t + (int64_t)blockIdx.y * nz * cols;
-    for (int q = tid; q < pz * CC; q += CT) {
-        const int i = q / CC, j = q - i * CC;
+    const int col = c0 + b0 + lo;
+    float af[4 * T], ab[4 * T], lxy = 0.0f, lz[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (tile) {
+#pragma unroll
+        for (int k = 0; k < 4 * T; ++k) {
+            af[k] = Vz[(4 * k + hi) * P + r0 + lo];
+            ab[k] = VzT[(4 * k + hi) * P + r0 + lo];
+        }
+        if (col < cols) lxy = lam[col % nx] + lam[nx + col / nx];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (r0 + 4 * hi + r < nz) lz[r] = lam[nx + ny + r0 + 4 * hi + r];
+    }
+#pragma unroll
+    for (int q = tid; q < P * CC; q += NT) {
+        const int i = q / CC, j = q % CC;
         X[i * S + j] = (i < nz && c0 + j < cols) ? ta[(int64_t)i * cols + c0 + j] : 0.0f;
     }
+    if (tl_done(scal, it)) return;
     __syncthreads();
-    const float* lx = lam;
-    const float* ly = lam + nx;
-    const float* lz = lam + nx + ny;
-    const int tiles = pz / 16 * (CC / 16);
     double d = 0.0;
-    for (int q = wave; q < tiles; q += CT / 64) {
-        const int r0 = q / (CC / 16) * 16, b0 = q % (CC / 16) * 16;
+    if (tile) {
         f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int k1 = 0; k1 < pz; k1 += 16)
 #pragma unroll
-            for (int k = k1; k < k1 + 16; k += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Vz[(k + hi) * pz + r0 + lo], X[(k + hi) * S + b0 + lo], acc, 0,
-                                                       0, 0);
-        const int col = c0 + b0 + lo;
-        const float lxy = col < cols ? lx[col % nx] + ly[col / nx] : 0.0f;
+        for (int k = 0; k < 4 * T; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(af[k], X[(4 * k + hi) * S + b0 + lo], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int kz = r0 + 4 * hi + r;
-            const float l = kz < nz ? lxy + lz[kz] : 0.0f;
+            const float l = kz < nz && col < cols ? lxy + lz[r] : 0.0f;
             const float f = l > cut ? scale / l : 0.0f;
             d += (double)acc[r] * (double)acc[r] * (double)f;
             U[kz * S + b0 + lo] = f * acc[r];
         }
     }
     __syncthreads();
-    for (int q = wave; q < tiles; q += CT / 64) {
-        const int r0 = q / (CC / 16) * 16, b0 = q % (CC / 16) * 16;
+    if (tile) {
         f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int k1 = 0; k1 < pz; k1 += 16)
 #pragma unroll
-            for (int k = k1; k < k1 + 16; k += 4)
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(VzT[(k + hi) * pz + r0 + lo], U[(k + hi) * S + b0 + lo], acc, 0,
-                                                       0, 0);
+        for (int k = 0; k < 4 * T; ++k)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ab[k], U[(4 * k + hi) * S + b0 + lo], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int iz = r0 + 4 * hi + r;
-            if (iz < nz && c0 + b0 + lo < cols) ta[(int64_t)iz * cols + c0 + b0 + lo] = acc[r];
+            if (iz < nz && col < cols) ta[(int64_t)iz * cols + col] = acc[r];
         }
     }
-    const double s = tl_reduce<CT>(d, red);
+    const double s = tl_reduce<NT>(d, red);
     if (tid == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+
+// A whole grid of at most SMALL_NODES nodes and SMALL_LINES lines in each
+// direction in one workgroup per time node, in place of the restriction (with
+// GATHER), the two plane kernels and the column kernel:
+// bound by its eight barriers and the gather (a lane's 24 scattered corners
+// take one CU's address unit 10 us at 1,000 nodes, hence SMALL_GATHER; the
+// restriction on its own 3.2 us).  7^3 nodes: four kernels 13.2 us -> 6.5; 9^3,
+// two time nodes: three kernels 10.7 -> 5.3.
+constexpr int SMALL_NODES = 1024, SMALL_LINES = 16, SMALL_GATHER = 384;
+template <bool GATHER, int NT>
+__global__ void __launch_bounds__(NT) k_small(const int32_t* __restrict__ slot, int K,
+                                                       const float* __restrict__ e4, int64_t estr,
+                                                       float* __restrict__ g, const float* __restrict__ V0,
+                                                       const float* __restrict__ V1, const float* __restrict__ V2,
+                                                       const float* __restrict__ lam, int nx, int ny, int nz,
+                                                       float scale, float cut, double* __restrict__ part,
+                                                       const double* __restrict__ scal, int it) {
+    constexpr int L = SMALL_LINES, S = L + 1;
+    __shared__ float a[NT], b[NT], V[3][L * S];
+    __shared__ double red[NT / 64];
+    const int t = threadIdx.x, nodes = nx * ny * nz;
+    for (int k = t; k < 3 * L * L; k += NT) {
+        const int d = k / (L * L), q = k % (L * L);
+        V[d][q / L * S + q % L] = (d == 0 ? V0 : (d == 1 ? V1 : V2))[q];
+    }
+    const bool on = t < nodes;
+    float v = 0.0f;
+    if (on) {
+        if (GATHER) {
+            typedef int i4 __attribute__((ext_vector_type(4)));
+            const float* ea = e4 + blockIdx.x * estr;
+            const i4* row = reinterpret_cast<const i4*>(slot + (int64_t)t * K);
+#pragma unroll 6
+            for (int k = 0; k < K / 4; ++k) {
+                const i4 c = row[k];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v += c[u] >= 0 ? ea[c[u]] : 0.0f;
+            }
+        } else {
+            v = g[(int64_t)blockIdx.x * nodes + t];
+        }
+        a[t] = v;
+    }
+    const int x = t % nx, y = t / nx % ny, z = t / (nx * ny);
+    const float l = on ? lam[x] + lam[nx + y] + lam[nx + ny + z] : 0.0f;
+    if (tl_done(scal, it)) return;
+    // sum over a line of `src` through this node (first entry at, step, n
+    // entries) times column c of V (forward) or its row (backward)
+    auto line = [&](const float* src, int at, int step, int n, const float* Vd, int c, bool fwd) {
+        // two sums, so that an LDS latency covers several terms
+        float s[2] = {0.0f, 0.0f};
+        int i = 0;
+        for (; i + 4 <= n; i += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s[u & 1] += src[at + (i + u) * step] * Vd[fwd ? (i + u) * S + c : c * S + i + u];
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (i + u < n) s[u & 1] += src[at + (i + u) * step] * Vd[fwd ? (i + u) * S + c : c * S + i + u];
+        return s[0] + s[1];
+    };
+    __syncthreads();
+    if (on) b[t] = line(a, t - x, 1, nx, V[0], x, true);
+    __syncthreads();
+    if (on) a[t] = line(b, t - y * nx, nx, ny, V[1], y, true);
+    __syncthreads();
+    double d = 0.0;
+    if (on) {
+        v = line(a, t - z * nx * ny, nx * ny, nz, V[2], z, true);
+        const float f = l > cut ? scale / l : 0.0f;
+        d = (double)v * (double)v * (double)f;
+        b[t] = f * v;
+    }
+    __syncthreads();
+    if (on) a[t] = line(b, t - z * nx * ny, nx * ny, nz, V[2], z, false);
+    __syncthreads();
+    if (on) b[t] = line(a, t - y * nx, nx, ny, V[1], y, false);
+    __syncthreads();
+    if (on) g[(int64_t)blockIdx.x * nodes + t] = line(b, t - x, 1, nx, V[0], x, false);
+    const double s = tl_reduce<NT>(d, red);
+    if (t == 0) part[blockIdx.x] = s;
 }
 
 // corner values of every element by trilinear interpolation (grids that do
@@ -511,9 +613,34 @@ void free_coarse(stdg_mesh* m) {
     c = CoarseTables();
 }
 
+namespace {
+bool small_grid(const CoarseTables& c) {
+    return c.nodes <= SMALL_NODES && std::max({c.n[0], c.n[1], c.n[2]}) <= SMALL_LINES;
+}
+
+template <int T> void plane(const CoarseTables& c, int G, bool fwd, const double* scal, int it, hipStream_t s) {
+    float* const* V = fwd ? c.V : c.VT;
+    hipLaunchKernelGGL(k_plane<T>, dim3(c.n[2] * G), dim3(plane_threads<T>()), 0, s, fwd ? c.g : c.t, fwd ? c.t : c.g,
+                       V[0], V[1], c.n[0], c.n[1], scal, it);
+}
+template <int T> void columns(const CoarseTables& c, int G, const double* scal, int it, hipStream_t s) {
+    hipLaunchKernelGGL(k_columns<T>, dim3((c.n[0] * c.n[1] + CC - 1) / CC, G), dim3(column_threads<T>()), 0, s, c.t,
+                       c.V[2], c.VT[2], c.lam, c.n[0], c.n[1], c.n[2], c.scale, c.cut, c.part, scal, it);
+}
+// f of the number of 16-line pads of n lines (up to MAXN)
+#define STDG_PADS(n, f, ...)                   \
+    switch (((n) + 15) / 16) {                 \
+        case 1: f<1>(__VA_ARGS__); break;      \
+        case 2: f<2>(__VA_ARGS__); break;      \
+        case 3: f<3>(__VA_ARGS__); break;      \
+        case 4: f<4>(__VA_ARGS__); break;      \
+        default: f<5>(__VA_ARGS__); break;     \
+    }
+}  // namespace
+
 int coarse_partials(const stdg_mesh* m) {
     const CoarseTables& c = m->d.coarse;
-    return (c.n[0] * c.n[1] + CC - 1) / CC * m->G;
+    return small_grid(c) ? m->G : (c.n[0] * c.n[1] + CC - 1) / CC * m->G;
 }
 
 // corner sums c.e4 -> K P^T r on the grid (c.g) and, off the grid, at the
@@ -522,19 +649,26 @@ hipError_t coarse_solve(const stdg_mesh* m, const double* scal, int it, hipStrea
     const CoarseTables& c = m->d.coarse;
     const int G = m->G, nx = c.n[0], ny = c.n[1], nz = c.n[2];
     const int64_t estr = 4 * c.epad;
+    const bool small = small_grid(c), gather = small && !c.wgt && c.nodes <= SMALL_GATHER;
     const dim3 rgrid((unsigned)(((int64_t)c.nodes * (c.wgt ? RLW : RL1) + 255) / 256), G);
     if (c.wgt)
         hipLaunchKernelGGL(k_restrict<true>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
                            scal, it);
-    else
+    else if (!gather)
         hipLaunchKernelGGL(k_restrict<false>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
                            scal, it);
-    const size_t plds = (size_t)2 * pad16(ny) * (pad16(nx) + 1) * sizeof(float);
-    hipLaunchKernelGGL(k_plane, dim3(nz * G), dim3(PT), plds, s, c.g, c.t, c.V[0], c.V[1], nx, ny, scal, it);
-    const size_t clds = (size_t)2 * pad16(nz) * (CC + 1) * sizeof(float);
-    hipLaunchKernelGGL(k_columns, dim3((nx * ny + CC - 1) / CC, G), dim3(CT), clds, s, c.t, c.V[2], c.VT[2], c.lam, nx,
-                       ny, nz, c.scale, c.cut, c.part, scal, it);
-    hipLaunchKernelGGL(k_plane, dim3(nz * G), dim3(PT), plds, s, c.t, c.g, c.VT[0], c.VT[1], nx, ny, scal, it);
+    if (small) {
+        // (a thread per node)
+        const bool few = c.nodes <= SMALL_GATHER;
+        hipLaunchKernelGGL((gather ? k_small<true, SMALL_GATHER>
+                                   : (few ? k_small<false, SMALL_GATHER> : k_small<false, SMALL_NODES>)),
+                           dim3(G), dim3(few ? SMALL_GATHER : SMALL_NODES), 0, s, c.slot, c.K, c.e4, estr, c.g,
+                           c.V[0], c.V[1], c.V[2], c.lam, nx, ny, nz, c.scale, c.cut, c.part, scal, it);
+    } else {
+        STDG_PADS(std::max(nx, ny), plane, c, G, true, scal, it, s)
+        STDG_PADS(nz, columns, c, G, scal, it, s)
+        STDG_PADS(std::max(nx, ny), plane, c, G, false, scal, it, s)
+    }
     if (c.tri)
         hipLaunchKernelGGL(k_corners, dim3((unsigned)((4 * m->E + 255) / 256), G), dim3(256), 0, s,
                            (const TriCorner*)c.tri, c.g, c.yc, 4 * m->E, estr, nx, ny, nz, c.per, scal, it);

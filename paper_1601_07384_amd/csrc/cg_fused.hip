@@ -89,16 +89,19 @@ constexpr int RED_T = 1024;             // threads of the one-block reductions
 constexpr int WPB = 4;                  // wavefronts per workgroup of the operator kernel (8 measured slower)
 constexpr int NPART = 5;                // partial dot products per block ...
 constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
-// elements from which the two-level CG is used.  An iteration costs seven to
-// eight launches instead of two, about 33 us instead of 10..14 where latency
-// is all, and saves as many as the mesh is wide.  Solve to 1e-10, ms, block
-// Jacobi against two-level: run layout (periodic cubes), p = 2: 1,296 elements
-// 2.17 / 2.41, 2,058 2.38 / 2.51, 3,072 2.90 / 2.56, p = 3: 2,058 3.15 / 3.14,
-// 3,072 3.85 / 3.02, 82,944 (p_gamma = 1) 22.7 / 6.3, 663,552 212 / 15.5; the
-// line leaves the even range to the older path.  Walls (tile kernel) 384
-// elements 3.31 / 2.47, 1,296 4.32 / 2.58, 3,072 4.98 / 2.85; scattered
-// vertices 384 4.06 / 3.58, 1,296 5.72 / 4.24.
-constexpr int64_t TL_MIN_E_RUN = 4096, TL_MIN_E = 384;
+// Elements from which the two-level CG is used.  An iteration costs four to
+// eight launches instead of two, 25..33 us instead of 10..17 where latency is
+// all, and saves as many as the mesh is wide; walls double those of block
+// Jacobi.  Solve to 1e-10, ms, block Jacobi against two-level: periodic, 750
+// elements, p = 2 1.80 / 1.90, 1,296 2.14 / 1.96, p = 3 2.86 / 2.44, 1,536 (8 x 8 x
+// 4), p = 1 2.02 / 1.34, p = 3 3.77 / 2.24, 3,072 (8^3), p = 2 2.84 / 2.15, p = 3
+// 3.84 / 2.61, 82,944, p = 3, p_gamma = 1 22.5 / 5.8, 663,552 212 / 15.5; walls 384
+// 3.31 / 2.47, 1,296 4.33 / 2.43; scattered vertices (elements with their own
+// operands) 384 4.06 / 3.58, 750 4.83 / 2.90.
+constexpr int64_t TL_MIN_E_PERIODIC = 1000, TL_MIN_E = 384;
+int64_t tl_min_elements(const stdg_mesh* m) {
+    return m->cfg.periodic && !elem_supported(m) ? TL_MIN_E_PERIODIC : TL_MIN_E;
+}
 
 __device__ inline Rsrc make_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
@@ -641,7 +644,7 @@ int upload_cg_operands(stdg_mesh* m) {
     int e = upload_lane_operands(m, invs);
     if (e == STDG_OK && !lane_supported(m)) e = upload_elem_operands(m, invs);
     // the second level, where the one-kernel iteration (and its workspaces) would serve
-    if (e != STDG_OK || !spd || m->E < (lane_supported(m) ? TL_MIN_E_RUN : TL_MIN_E) || !cg_fused_supported(m)) return e;
+    if (e != STDG_OK || !spd || m->E < tl_min_elements(m) || !cg_fused_supported(m)) return e;
     if ((e = upload_coarse(m))) return e;
     if (coarse_supported(m) && !lane_supported(m) && !elem_supported(m)) e = upload_own_inverse(m, invs);
     return e;
