@@ -9,7 +9,7 @@
 //
 // FP64 (p <= 4, p_gamma <= 4): groups of up to 64 elements of one class on the
 // FP64 matrix cores, meshes without such groups with a thread per (coupling,
-// row) (schur_apply_m64); meshes whose elements carry their own blocks stream them
+// row) (schur_apply_list); meshes whose elements carry their own blocks stream them
 // (cg_elem.hip).  FP32 vectors and other degrees: one thread per (element,
 // time node), the neighbour column x'_m = sum_b C_ab x_k[b][m] formed on the
 // fly, N outputs in registers; a wavefront of one class reads its blocks
@@ -113,150 +113,101 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
     }
 }
 
-// FP64 y = S x.  With `seg_blocks` a workgroup takes a group of up to 64
-// elements of one class: the class's five blocks staged in LDS, a wavefront on
-// 16 CW elements with G columns each (mfma64.hpp: rows read 16 bytes a lane, an
-// operand from LDS serving CW G matrix instructions, results in place for the
-// G x G time factor and written in whole lines).  Otherwise it takes EPB
-// elements with a thread per coupling and row, the five couplings in parallel
-// and summed through LDS.  Bound: HBM at p <= 2, the matrix cores and
-// the operand reads at p = 3, 4, the launch (7.8 us in a loop from the host)
+// FP64 y = S x.  A workgroup takes a group of up to 64 elements of one class:
+// the class's five blocks staged in LDS, a wavefront on 16 CW elements with G
+// columns each (mfma64.hpp: rows read 16 bytes a lane, an operand from LDS
+// serving CW G matrix instructions, results in place for the G x G time factor
+// and written in whole lines).  Bound: HBM at p <= 2, the matrix cores and the
+// operand reads at p = 3, 4, the launch (7.8 us in a loop from the host)
 // below 10^4 elements.  MI355X, kernels per entry on the vector units before
 // -> this one, us: 663,552 elements, p = 3, G = 1: 123 -> 102 (2.1 TB/s of x
 // and y); 196,608, p = 2: G = 1 19.9 -> 14.8, G = 2 29.7 -> 24.5; 82,944, p = 3,
 // G = 2: 33.0 -> 24.9; 48,000, p = 2, G = 3: 41 -> 11.5; with walls 10,368, p = 4,
-// G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; every run mixed, 82,944, p = 3,
-// G = 2: 391 -> 198.  The sums' rounding is half as large.
+// G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; no two
+// neighbours of one class (schur_apply_list), 82,944, p = 3, G = 2: 391 -> 198.  The sums' rounding is half as large.
 // With DOT the workgroup's share of x.y goes to part[blockIdx.x].
 template <int N, int G, int CW, bool DOT>
 __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __restrict__ BT,
-                                                           const int32_t* __restrict__ cls,
                                                            const m64_i4* __restrict__ segs,
                                                            const int32_t* __restrict__ nbr,
                                                            const double* __restrict__ C, const double* x,
-                                                           double* __restrict__ y, int64_t E, uint32_t seg_blocks,
-                                                           uint32_t n_segs,
+                                                           double* __restrict__ y, int64_t E, uint32_t n_segs,
                                                            double* __restrict__ part) {
     constexpr int NT = 256 / CW, NQ = M64<N>::NQ, NP = M64<N>::NP, NC = CW * G;
-    constexpr int EPB = NT / (5 * N) > 0 ? NT / (5 * N) : 1;
-    static_assert(5 * N <= NT, "a thread per coupling and row");
-    constexpr int L0 = 5 * N * NP > 64 * G * N ? 5 * N * NP : 64 * G * N;
-    constexpr int LD = L0 > EPB * 5 * G * N ? L0 : EPB * 5 * G * N;
+    constexpr int LD = 5 * N * NP > 64 * G * N ? 5 * N * NP : 64 * G * N;
     __shared__ double A[LD];
     __shared__ double red[NT / 64];
     double d = 0.0;
-    if (seg_blocks > 0) {
-        const uint32_t group = m64_group(seg_blocks);
-        if (group < n_segs) {
-            const m64_i4 sg = segs[group];
-            const int c = sg.z;
-            const int64_t e0 = sg.x, e1 = e0 + sg.y;
-            const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hi = lane >> 4, lo = lane & 3;
-            int nb[5][CW];
+    const uint32_t group = m64_group(gridDim.x);
+    if (group < n_segs) {
+        const m64_i4 sg = segs[group];
+        const int c = sg.z;
+        const int64_t e0 = sg.x, e1 = e0 + sg.y;
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hi = lane >> 4, lo = lane & 3;
+        int nb[5][CW];
 #pragma unroll
-            for (int q = 0; q < CW; ++q) {
-                const int64_t e = e0 + 16 * (CW * w + q) + (lane & 15);
-                const bool valid = e < e1;
-                nb[0][q] = valid ? (int)e : -1;
+        for (int q = 0; q < CW; ++q) {
+            const int64_t e = e0 + 16 * (CW * w + q) + (lane & 15);
+            const bool valid = e < e1;
+            nb[0][q] = valid ? (int)e : -1;
 #pragma unroll
-                for (int f = 0; f < 4; ++f) nb[f + 1][q] = valid ? nbr[4 * e + f] : -1;
-            }
-            m64_stage<N, NT>(BT + (int64_t)c * 5 * N * N, A, 5);
-            const __amdgpu_buffer_rsrc_t rx = m64_rsrc(x, (uint32_t)(8 * E * G * N));
-            double acc[NQ][NC];
-#pragma unroll
-            for (int rg = 0; rg < NQ; ++rg)
-#pragma unroll
-                for (int q = 0; q < NC; ++q) acc[rg][q] = 0.0;
-            __syncthreads();
-            auto couple = [&](int k) {
-                double b[NC][NQ];
-#pragma unroll
-                for (int q = 0; q < CW; ++q) {
-                    const int s = k == 0 ? nb[0][q] : (k == 1 ? nb[1][q] : (k == 2 ? nb[2][q] : (k == 3 ? nb[3][q] : nb[4][q])));
-#pragma unroll
-                    for (int a = 0; a < G; ++a)
-                        m64_load<N>(rx, s >= 0 ? (uint32_t)((s * G + a) * N) * 8u : M64_OOB, hi, b[q * G + a]);
-                }
-                m64_block<N, NC>(A + k * N * NP, b, lo, hi, acc);
-            };
-            // large blocks (p = 4) one coupling at a time, so that the rows of
-            // the next are not all held at once
-            if constexpr (NQ * NC > 16) {
-#pragma unroll 1
-                for (int k = 0; k < 5; ++k) couple(k);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 5; ++k) couple(k);
-            }
-            double Cm[G][G];
-#pragma unroll
-            for (int a = 0; a < G; ++a)
-#pragma unroll
-                for (int b = 0; b < G; ++b) Cm[a][b] = C[a * G + b];
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < CW; ++q) {
-                const int64_t first = e0 + 16 * (CW * w + q), left = e1 - first;
-                if (left <= 0) continue;
-                const int count = (int)(left < 16 ? left : 16) * G * N;
-                const int64_t at = first * G * N;
-                m64_flush<N, G>(
-                    A + w * 16 * G * N, lane, hi, count,
-                    [&](int rg, int a) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int b = 0; b < G; ++b) s += Cm[a][b] * acc[rg][q * G + b];
-                        return s;
-                    },
-                    [&](int i, m64_d2u v) {
-                        m64_put(y + at, i, count, v);
-                        if (DOT) {
-                            d += x[at + i] * v.x;
-                            if (i + 1 < count) d += x[at + i + 1] * v.y;
-                        }
-                    });
-            }
+            for (int f = 0; f < 4; ++f) nb[f + 1][q] = valid ? nbr[4 * e + f] : -1;
         }
-    } else {
-        const int t = threadIdx.x, el = t / (5 * N), kr = t - el * (5 * N), k = kr / N, r = kr - k * N;
-        const int64_t item = (int64_t)blockIdx.x * EPB + el;
-        const bool on = el < EPB && item < E;
-        const int64_t i = on ? item : 0;
-        const int64_t s = !on ? -1 : (k == 0 ? i : (int64_t)nbr[4 * i + (k - 1)]);
-        double acc[G];
+        m64_stage<N, NT>(BT + (int64_t)c * 5 * N * N, A, 5);
+        const __amdgpu_buffer_rsrc_t rx = m64_rsrc(x, (uint32_t)(8 * E * G * N));
+        double acc[NQ][NC];
 #pragma unroll
-        for (int b = 0; b < G; ++b) acc[b] = 0.0;
-        if (s >= 0) {
-            const double* Bk = BT + ((int64_t)cls[i] * 5 + k) * N * N + r;
-            const double* xt = x + s * G * N;
-#pragma unroll 10
-            for (int mm = 0; mm < N; ++mm) {
-                const double bv = Bk[mm * N];
+        for (int rg = 0; rg < NQ; ++rg)
 #pragma unroll
-                for (int b = 0; b < G; ++b) acc[b] += bv * xt[b * N + mm];
-            }
-        }
-        if (el < EPB)
-#pragma unroll
-            for (int b = 0; b < G; ++b) A[((el * 5 + k) * G + b) * N + r] = acc[b];
+            for (int q = 0; q < NC; ++q) acc[rg][q] = 0.0;
         __syncthreads();
-        if (on && k == 0) {
-            double z[G];
+        auto couple = [&](int k) {
+            double b[NC][NQ];
 #pragma unroll
-            for (int b = 0; b < G; ++b) {
-                z[b] = 0.0;
+            for (int q = 0; q < CW; ++q) {
+                const int s = k == 0 ? nb[0][q] : (k == 1 ? nb[1][q] : (k == 2 ? nb[2][q] : (k == 3 ? nb[3][q] : nb[4][q])));
 #pragma unroll
-                for (int kk = 0; kk < 5; ++kk) z[b] += A[((el * 5 + kk) * G + b) * N + r];
+                for (int a = 0; a < G; ++a)
+                    m64_load<N>(rx, s >= 0 ? (uint32_t)((s * G + a) * N) * 8u : M64_OOB, hi, b[q * G + a]);
             }
+            m64_block<N, NC>(A + k * N * NP, b, lo, hi, acc);
+        };
+        // large blocks (p = 4) one coupling at a time, so that the rows of
+        // the next are not all held at once
+        if constexpr (NQ * NC > 16) {
+#pragma unroll 1
+            for (int k = 0; k < 5; ++k) couple(k);
+        } else {
 #pragma unroll
-            for (int a = 0; a < G; ++a) {
-                double v = 0.0;
+            for (int k = 0; k < 5; ++k) couple(k);
+        }
+        double Cm[G][G];
 #pragma unroll
-                for (int b = 0; b < G; ++b) v += C[a * G + b] * z[b];
-                y[(i * G + a) * N + r] = v;
-                if (DOT) d += x[(i * G + a) * N + r] * v;
-            }
+        for (int a = 0; a < G; ++a)
+#pragma unroll
+            for (int b = 0; b < G; ++b) Cm[a][b] = C[a * G + b];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < CW; ++q) {
+            const int64_t first = e0 + 16 * (CW * w + q), left = e1 - first;
+            if (left <= 0) continue;
+            const int count = (int)(left < 16 ? left : 16) * G * N;
+            const int64_t at = first * G * N;
+            m64_flush<N, G>(
+                A + w * 16 * G * N, lane, hi, count,
+                [&](int rg, int a) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int b = 0; b < G; ++b) s += Cm[a][b] * acc[rg][q * G + b];
+                    return s;
+                },
+                [&](int i, m64_d2u v) {
+                    m64_put(y + at, i, count, v);
+                    if (DOT) {
+                        d += x[at + i] * v.x;
+                        if (i + 1 < count) d += x[at + i + 1] * v.y;
+                    }
+                });
         }
     }
     if (DOT) {
@@ -265,31 +216,84 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
     }
 }
 
-// The launch's workgroups: groups where they fill (segs_fill), small meshes too
-// (us, groups / one by one: 2,058 elements, p = 3, G = 2 6.5 / 8.5; 48,000,
-// p = 1, G = 2 5.5 / 8.0; 3,072, p = 4, G = 2 14.1 / 25.0; equal at 750 and 1,296,
-// p = 3).
-struct M64Grid {
-    uint32_t seg_blocks, blocks;
-};
-template <int N, int CW> static M64Grid m64_grid(const stdg_mesh* m) {
-    constexpr int EPB = 256 / CW / (5 * N) > 0 ? 256 / CW / (5 * N) : 1;
-    const bool fill = segs_fill(m);
-    return {fill ? m64_blocks(m->d.n_segs) : 0, fill ? m64_blocks(m->d.n_segs) : (uint32_t)((m->E + EPB - 1) / EPB)};
+// y = S x element by element: a thread per coupling and row, EPB elements per
+// workgroup of LT threads, the five couplings in parallel and summed through
+// LDS.  Bound: the blocks, 5 N^2 values per element through L2.
+// With DOT (FP64) the workgroup's share of x.y goes to part[blockIdx.x].
+constexpr int LT = 256;
+template <int N> constexpr int list_epb() { return LT / (5 * N) > 0 ? LT / (5 * N) : 1; }
+template <int N, int G, typename T, bool DOT>
+__global__ void __launch_bounds__(LT) schur_apply_list(const T* __restrict__ BT, const int32_t* __restrict__ cls,
+                                                       const int32_t* __restrict__ nbr, const T* __restrict__ C,
+                                                       const T* x, T* __restrict__ y, int64_t E,
+                                                       double* __restrict__ part) {
+    constexpr int EPB = list_epb<N>();
+    static_assert(5 * N <= LT, "a thread per coupling and row");
+    __shared__ T A[EPB * 5 * G * N];
+    __shared__ double red[LT / 64];
+    double d = 0.0;
+    const int t = threadIdx.x, el = t / (5 * N), kr = t - el * (5 * N), k = kr / N, r = kr - k * N;
+    const int64_t i = (int64_t)blockIdx.x * EPB + el;
+    const bool on = el < EPB && i < E;
+    const int64_t s = !on ? -1 : (k == 0 ? i : (int64_t)nbr[4 * i + (k - 1)]);
+    T acc[G];
+#pragma unroll
+    for (int b = 0; b < G; ++b) acc[b] = T(0);
+    if (s >= 0) {
+        const T* Bk = BT + ((int64_t)cls[i] * 5 + k) * N * N + r;
+        const T* xt = x + s * G * N;
+#pragma unroll 10
+        for (int mm = 0; mm < N; ++mm) {
+            const T bv = Bk[mm * N];
+#pragma unroll
+            for (int b = 0; b < G; ++b) acc[b] += bv * xt[b * N + mm];
+        }
+    }
+    if (el < EPB)
+#pragma unroll
+        for (int b = 0; b < G; ++b) A[((el * 5 + k) * G + b) * N + r] = acc[b];
+    __syncthreads();
+    if (on && k == 0) {
+        T z[G];
+#pragma unroll
+        for (int b = 0; b < G; ++b) {
+            z[b] = T(0);
+#pragma unroll
+            for (int kk = 0; kk < 5; ++kk) z[b] += A[((el * 5 + kk) * G + b) * N + r];
+        }
+#pragma unroll
+        for (int a = 0; a < G; ++a) {
+            T v = T(0);
+#pragma unroll
+            for (int b = 0; b < G; ++b) v += C[a * G + b] * z[b];
+            y[(i * G + a) * N + r] = v;
+            if (DOT) d += (double)x[(i * G + a) * N + r] * (double)v;
+        }
+    }
+    if (DOT) {
+        const double p = tl_reduce<LT>(d, red);
+        if (t == 0) part[blockIdx.x] = p;
+    }
 }
 
-template <int N, int G, int CW>
+// Workgroups of the FP64 operator: groups where they fill (segs_fill), small
+// meshes too (us, groups / one by one: 2,058 elements, p = 3, G = 2 6.5 / 8.5;
+// 48,000, p = 1, G = 2 5.5 / 8.0; 3,072, p = 4, G = 2 14.1 / 25.0; equal at 750 and
+// 1,296, p = 3).
+template <int N> static unsigned apply64_blocks(const stdg_mesh* m) {
+    return segs_fill(m) ? m64_blocks(m->d.n_segs) : (unsigned)((m->E + list_epb<N>() - 1) / list_epb<N>());
+}
+
+template <int N, int G, int CW, bool DOT>
 static hipError_t launch_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
                              hipStream_t s) {
-    const M64Grid g = m64_grid<N, CW>(m);
-    const m64_i4* segs = (const m64_i4*)m->d.segs;
-    const uint32_t ns = (uint32_t)m->d.n_segs;
-    if (part)
-        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, true>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
-                           m->d.cls, segs, m->d.nbr, C, x, y, m->E, g.seg_blocks, ns, part);
+    const dim3 grid(apply64_blocks<N>(m));
+    if (segs_fill(m))
+        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, DOT>), grid, dim3(256 / CW), 0, s, m->d.blocks,
+                           (const m64_i4*)m->d.segs, m->d.nbr, C, x, y, m->E, (uint32_t)m->d.n_segs, part);
     else
-        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, false>), dim3(g.blocks), dim3(256 / CW), 0, s, m->d.blocks,
-                           m->d.cls, segs, m->d.nbr, C, x, y, m->E, g.seg_blocks, ns, part);
+        hipLaunchKernelGGL((schur_apply_list<N, G, double, DOT>), grid, dim3(LT), 0, s, m->d.blocks, m->d.cls,
+                           m->d.nbr, C, x, y, m->E, part);
     return hipGetLastError();
 }
 
@@ -338,11 +342,22 @@ static bool m64_supported(const stdg_mesh* m) {
 static hipError_t apply_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
                             hipStream_t s) {
 #define STDG_NG(n, g) \
-    if (m->N == n && m->G == g) return launch_m64<n, g, m64_cw<n, g>()>(m, C, x, y, part, s);
+    if (m->N == n && m->G == g)                                                       \
+        return part ? launch_m64<n, g, m64_cw<n, g>(), true>(m, C, x, y, part, s)     \
+                    : launch_m64<n, g, m64_cw<n, g>(), false>(m, C, x, y, part, s);
     STDG_ALL_NG
 #undef STDG_NG
     return hipErrorInvalidValue;
 }
+
+// FP32 by schur_apply_list: the thread of schur_apply_tn runs through 5 N^2
+// block values in series, whose latency alone is 15 us at p = 3 and 32 (one
+// class per wavefront) to 115 us (several) at p = 4; the list grows with the
+// elements.  us, thread per element / list: p = 3 1,296 elements with walls,
+// G = 2 21.2 / 8.7, 6,000 15.0 / 8.2, 16,464 17.8 / 15.6, 82,944 16.6 / 70; p = 4
+// with walls 750 115 / 9.4, 10,368 112 / 28.6, periodic 3,072 32.3 / 10.3; p = 2
+// 16,464, G = 2 8.0 / 9.0.
+static bool list32(const stdg_mesh* m) { return m->N >= 20 && m->E <= 12000; }
 
 template <typename T>
 static hipError_t launch_apply(const stdg_mesh* m, const T* BT, const T* C, const T* x, T* y,
@@ -351,6 +366,16 @@ static hipError_t launch_apply(const stdg_mesh* m, const T* BT, const T* C, cons
         // meshes whose elements carry their own blocks: the per-element FP64 tables
         if (elem_apply64_supported(m)) return elem_apply_f64(m, C, x, y, s);
         if (m64_supported(m)) return apply_m64(m, C, x, y, nullptr, s);
+    } else if (list32(m)) {
+#define STDG_NG(n, g)                                                                                       \
+    if constexpr (n >= 20) if (m->N == n && m->G == g) {                                                    \
+        hipLaunchKernelGGL((schur_apply_list<n, g, float, false>),                                          \
+                           dim3((unsigned)((m->E + list_epb<n>() - 1) / list_epb<n>())), dim3(LT), 0, s, BT, \
+                           m->d.cls, m->d.nbr, C, x, y, m->E, (double*)nullptr);                            \
+        return hipGetLastError();                                                                           \
+    }
+        STDG_ALL_NG
+#undef STDG_NG
     }
 #define STDG_NG(n, g) \
     if (m->N == n && m->G == g) return launch_tn<n, g, T>(m, BT, C, x, y, s);
@@ -363,7 +388,7 @@ static hipError_t launch_apply(const stdg_mesh* m, const T* BT, const T* C, cons
 int64_t apply_dot_blocks(const stdg_mesh* m) {
     if (elem_apply64_supported(m) || !m64_supported(m)) return 0;
 #define STDG_NG(n, g) \
-    if (m->N == n && m->G == g) return m64_grid<n, m64_cw<n, g>()>(m).blocks;
+    if (m->N == n && m->G == g) return apply64_blocks<n>(m);
     STDG_ALL_NG
 #undef STDG_NG
     return 0;

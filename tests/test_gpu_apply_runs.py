@@ -52,3 +52,19 @@ def test_apply_matches_blocks(n, p, pg, periodic, reorder):
     m.apply(xd, y)
     err = np.abs(y.cpu().numpy().reshape(ref.shape) - ref).max()
     assert err <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n,p,pg,periodic", [((3, 3, 3), 3, 0, False), ((6, 7, 6), 3, 2, True), ((4, 5, 6), 4, 0, False),
+                                             ((6, 6, 5), 4, 1, True), ((3, 4, 4), 4, 4, False)])
+def test_apply_f32_matches_fp64(n, p, pg, periodic):
+    """The FP32 operator element by element (p >= 3, few elements): 5 N products
+    in FP32, 1e-5 of the largest result."""
+    print(f"apply_f32 n={n} p={p} pg={pg} periodic={periodic}", flush=True)
+    X, T = box_mesh(n, (1.0, 1.0, 1.0))
+    m = P.Mesh(X, T, p, pg, dt=1e-2, periodic=periodic)
+    xf = torch.tensor(np.random.default_rng(3).standard_normal(m.E * m.Nst), dtype=torch.float32, device=DEV)
+    yf = torch.full_like(xf, float("nan"))
+    m.apply_f32(xf, yf)
+    y = torch.empty(m.E * m.Nst, dtype=torch.float64, device=DEV)
+    m.apply(xf.double(), y)
+    assert float((yf.double() - y).abs().max()) <= 1e-5 * float(y.abs().max())
