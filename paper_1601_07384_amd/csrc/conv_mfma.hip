@@ -16,7 +16,8 @@
 // instructions of 256 FMAs per four volume points and 45 per four face points,
 // 0.9 ms of the matrix cores in all; measured 7,204 us for the kernel with a
 // lane per element and scalar tables, 1,803 us here (196,608 elements, p = 2,
-// p_gamma = 1: 785 -> 473 us).
+// p_gamma = 1: 785 -> 473 us; 24,576, p = 3, p_gamma = 2: 1,876 -> 550; 3,072,
+// p = 4, p_gamma = 1: 1,304 -> 499).
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -225,15 +226,15 @@ hipError_t launch_conv(const stdg_mesh* m, const double* vbar, const double* vbc
 
 }  // namespace
 
-// groups that fill, the sums of all time nodes in registers (N G up to 40),
+// groups that fill, the sums of all time nodes in registers (N G up to 80),
 // and buffer offsets below 2 GiB
 hipError_t conv_mfma(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s) {
     if (!segs_fill(m) || 8 * (int64_t)m->faces.size() * m->Nst >= ((int64_t)1 << 31)) return hipErrorNotSupported;
 #define STDG_CV(n, g) \
     if (m->N == n && m->G == g) return launch_conv<n, g>(m, vbar, vbc, ups, s);
     STDG_CV(4, 1) STDG_CV(4, 2) STDG_CV(4, 3) STDG_CV(4, 4) STDG_CV(4, 5)
-    STDG_CV(10, 1) STDG_CV(10, 2) STDG_CV(10, 3) STDG_CV(10, 4)
-    STDG_CV(20, 1) STDG_CV(20, 2)
+    STDG_CV(10, 1) STDG_CV(10, 2) STDG_CV(10, 3) STDG_CV(10, 4) STDG_CV(10, 5)
+    STDG_CV(20, 1) STDG_CV(20, 2) STDG_CV(20, 3) STDG_CV(20, 4) STDG_CV(35, 1) STDG_CV(35, 2)
 #undef STDG_CV
     return hipErrorNotSupported;
 }

@@ -14,7 +14,8 @@
 // 14 N^2 flops a column.  663,552 elements, p = 3, p_gamma = 0: 1,005 us for
 // the operator, the block-Jacobi and the dot kernel with one thread per row,
 // 317 us here (385 with the dot against a third vector); 196,608, p = 2,
-// p_gamma = 1: 281 -> 97 (117) us.
+// p_gamma = 1: 281 -> 97 (117) us; 24,576, p = 3, p_gamma = 2 (N G = 60, one
+// wavefront per SIMD): 320 -> 78 (83); 3,072, p = 4, p_gamma = 1: 178 -> 57 (64).
 
 #include "internal.hpp"
 #include "kernels.hpp"
@@ -36,7 +37,6 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
                                                   double* __restrict__ y, const double* w, double* __restrict__ part,
                                                   int64_t E, uint32_t n_segs, uint32_t xbytes) {
     constexpr int NQ = M64<N>::NQ, NP = M64<N>::NP, NC = 3 * G;
-    static_assert((N * G) % 2 == 0, "rows leave two values at a time");
     __shared__ double A[6 * N * NP > 64 * G * N ? 6 * N * NP : 64 * G * N];
     __shared__ double Dl[PRE ? G * NP * G * NP : 1];
     __shared__ double red[VT / 64];
@@ -148,8 +148,15 @@ __global__ void __launch_bounds__(VT) k_visc_mfma(const double* __restrict__ SVt
                     [&](int i, m64_d2u v) {
                         m64_put(y + at, i, count, v);
                         if (DOTS >= 1) {
-                            // (an even number of values: N G is even)
-                            const m64_d2u u = *reinterpret_cast<const m64_d2u*>((DOTS == 1 ? w : x) + at + i);
+                            const double* from = (DOTS == 1 ? w : x) + at + i;
+                            m64_d2u u;
+                            if ((N * G) % 2 == 0 || i + 1 < count) {
+                                u = *reinterpret_cast<const m64_d2u*>(from);
+                            } else {                    // the last of an odd number of values
+                                u.x = *from;
+                                u.y = 0.0;
+                                v.y = 0.0;
+                            }
                             d0 += u.x * v.x + u.y * v.y;
                             if (DOTS == 2) d1 += v.x * v.x + v.y * v.y;
                         }
@@ -179,10 +186,10 @@ hipError_t launch_visc(const stdg_mesh* m, const double* x, double* y, const dou
 
 int64_t visc_mfma_blocks(const stdg_mesh* m) { return m64_blocks(m->d.n_segs); }
 
-// N G up to 40 (the inverse diagonal block in LDS), groups that fill, and
+// N G up to 80 (the inverse diagonal block in LDS), groups that fill, and
 // offsets within a component below 2 GiB
 bool visc_mfma_supported(const stdg_mesh* m) {
-    return segs_fill(m) && (m->N == 4 || m->N == 10 || m->N == 20) && m->G <= 5 && m->Nst <= 40 &&
+    return segs_fill(m) && (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && m->Nst <= 80 &&
            8 * m->E * m->Nst < ((int64_t)1 << 31);
 }
 
@@ -196,8 +203,8 @@ hipError_t visc_mfma(const stdg_mesh* m, bool pre, int dots, const double* x, do
                          : launch_visc<n, g, true, 2>(m, x, y, w, part, s);                 \
     }
     STDG_NG(4, 1) STDG_NG(4, 2) STDG_NG(4, 3) STDG_NG(4, 4) STDG_NG(4, 5)
-    STDG_NG(10, 1) STDG_NG(10, 2) STDG_NG(10, 3) STDG_NG(10, 4)
-    STDG_NG(20, 1) STDG_NG(20, 2)
+    STDG_NG(10, 1) STDG_NG(10, 2) STDG_NG(10, 3) STDG_NG(10, 4) STDG_NG(10, 5)
+    STDG_NG(20, 1) STDG_NG(20, 2) STDG_NG(20, 3) STDG_NG(20, 4) STDG_NG(35, 1) STDG_NG(35, 2)
 #undef STDG_NG
     return hipErrorInvalidValue;
 }

@@ -24,7 +24,9 @@ def test_transfers(n, p, pg, periodic):
 
 
 @pytest.mark.parametrize("n,p,pg,periodic", [(4, 1, 1, False), (5, 2, 0, False), (5, 2, 1, True), (4, 2, 3, False),
-                                             (4, 3, 0, False), (5, 3, 0, True), (3, 3, 1, False), (3, 4, 0, False)])
+                                             (4, 3, 0, False), (5, 3, 0, True), (3, 3, 1, False), (3, 4, 0, False),
+                                             (4, 2, 4, True), (3, 3, 2, False), (3, 3, 3, True), (4, 4, 0, True),
+                                             (3, 4, 1, False)])
 def test_step(n, p, pg, periodic):
     print(f"small groups n={n} p={p} pg={pg} periodic={periodic}", flush=True)
     X, T = kuhn_mesh(n)
