@@ -97,10 +97,12 @@ constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
 // 4), p = 1 2.02 / 1.34, p = 3 3.77 / 2.24, 3,072 (8^3), p = 2 2.84 / 2.15, p = 3
 // 3.84 / 2.61, 82,944, p = 3, p_gamma = 1 22.5 / 5.8, 663,552 212 / 15.5; walls 384
 // 3.31 / 2.47, 1,296 4.33 / 2.43; scattered vertices (elements with their own
-// operands) 384 4.06 / 3.58, 750 4.83 / 2.90.
+// operands) 384 4.06 / 3.58, 750 4.83 / 2.90; p = 4 (no preconditioner without
+// the second level), 384 7.8 / 3.0, 3,072 12.0 / 4.2, 24,576, p_gamma = 1 34.0 /
+// 5.2, walls (runs of several classes: a pass each) 3,072 108 / 10.7.
 constexpr int64_t TL_MIN_E_PERIODIC = 1000, TL_MIN_E = 384;
 int64_t tl_min_elements(const stdg_mesh* m) {
-    return m->cfg.periodic && !elem_supported(m) ? TL_MIN_E_PERIODIC : TL_MIN_E;
+    return m->cfg.periodic && !elem_supported(m) && m->N != 35 ? TL_MIN_E_PERIODIC : TL_MIN_E;
 }
 
 __device__ inline Rsrc make_rsrc(const void* p, uint32_t bytes) {
@@ -626,16 +628,22 @@ int upload_cg_operands(stdg_mesh* m) {
         case 20: spd = cg_operands<20>(m, t, invs); break;
         default: {
             // no tile kernel for this degree: the own-block inverses for the
-            // element-per-lane operator tables only
+            // element-per-lane tables, and the second level where these serve
             const int N = m->N;
+            spd = true;
             invs.assign((size_t)m->n_classes * N * N, 0.0);
-            for (int c = 0; c < m->n_classes; ++c) {
+            for (int c = 0; c < m->n_classes && spd; ++c) {
                 const double* B0 = m->blocks.data() + (size_t)c * 5 * N * N;
                 std::vector<real> chol(B0, B0 + N * N), inv(B0, B0 + N * N);
-                if (!cholesky(N, chol) || !lu_inverse(N, inv)) { invs.assign(invs.size(), 0.0); break; }
+                spd = cholesky(N, chol) && lu_inverse(N, inv);
                 for (int i = 0; i < N * N; ++i) invs[(size_t)c * N * N + i] = (double)inv[i];
             }
-            return upload_lane_operands(m, invs);
+            if (!spd) std::fill(invs.begin(), invs.end(), 0.0);
+            if (const int e = upload_lane_operands(m, invs)) return e;
+            if (!spd || m->curved || !lane_supported(m) || m->E < tl_min_elements(m) ||
+                4 * m->E * m->G * N >= ((int64_t)1 << 31))
+                return STDG_OK;
+            return upload_coarse(m);
         }
     }
     m->d.cg_precond_ok = spd ? 1 : 0;

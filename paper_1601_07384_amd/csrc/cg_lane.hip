@@ -194,8 +194,8 @@ template <int N> __device__ inline void load_ops(const float* __restrict__ table
 // A run of one class takes a single pass.
 // y = cscale B x (cscale = c for p_gamma = 0, 1 for one time node of B (x) I);
 // the five rows of a pass are loaded one block ahead of their products.  With
-// DOT (runs of one class only) the own row comes last, so that it is still
-// in registers for the workgroup's share of x.y, and the kernel belongs to
+// DOT the own row comes last, so that it is still in registers for the
+// workgroup's share of x.y (after one pass), and the kernel belongs to
 // iteration `it` of the two-level CG.
 template <int N, bool DOT>
 __global__ void __launch_bounds__(64 * LWPB) k_lane_op(const float* __restrict__ table, const int32_t* __restrict__ cls,
@@ -219,10 +219,12 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_op(const float* __restrict__
         float ops[LaneShape<N>::NV];
         float v[2][N];
         constexpr int FIRST = DOT ? 1 : 0;
+        bool several = false;
         for (uint64_t todo = __ballot(lp.valid); todo;) {
             const int c = __builtin_amdgcn_readlane(mc, __builtin_ctzll(todo));
             const bool mine = lp.valid && mc == c;
             todo &= ~__ballot(mine);
+            several = several || todo;
             load_ops<N>(table, c, ops);
             uint32_t off[5];
 #pragma unroll
@@ -243,6 +245,7 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_op(const float* __restrict__
         acc_rows<N>(acc, cscale, o);
         // every lane of the run stores (the slots past the mesh get zeros)
         row_store<N>(make_rsrc(y, vbytes), run_off<N>(lp.e, lp.a, G), o);
+        if (DOT && several) row_load<N>(rx, lp.valid ? run_off<N>(lp.e, lp.a, G) : OOB, v[0]);
         if (DOT)
 #pragma unroll
             for (int r = 0; r < N; ++r) d += (double)v[0][r] * (double)o[r];
@@ -605,13 +608,39 @@ template <int N> __device__ inline void load_inv_ops(const float* __restrict__ t
     }
 }
 
+// acc = B_e^-1 v: one pass per class of the run at p = 4 (the other degrees
+// have runs of one class here)
+template <int N>
+__device__ inline void inv_rows(const float* __restrict__ table, const int32_t* __restrict__ cls, int32_t e0, int32_t E,
+                                const float (&v)[N], f4 (&acc)[LaneShape<N>::NQ]) {
+    float ops[LaneShape<N>::NV];
+    acc_zero<N>(acc);
+    if constexpr (N != 35) {
+        load_inv_ops<N>(table, __builtin_amdgcn_readfirstlane(cls[e0]), ops);
+        lane_block<N, 5>(ops, v, acc);
+    } else {
+        const int32_t e = e0 + (int32_t)(threadIdx.x & 63);
+        const int mc = cls[e < E ? e : E - 1];
+        for (uint64_t todo = ~uint64_t(0); todo;) {
+            const int c = __builtin_amdgcn_readlane(mc, __builtin_ctzll(todo));
+            const bool mine = mc == c;
+            todo &= ~__ballot(mine);
+            load_inv_ops<N>(table, c, ops);
+            float w[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) w[k] = mine ? v[k] : 0.0f;
+            lane_block<N, 5>(ops, w, acc);
+        }
+    }
+}
+
 // r -= alpha q (r = b at iteration 0), its corner sums e4 = P^T r, and the
 // workgroup's shares of r.r and r . B_e^-1 r / c
 template <int N>
 __global__ void __launch_bounds__(64 * LWPB) k_lane_update(
     const float* __restrict__ table, const int32_t* __restrict__ cls, float* r, const float* q, f4* __restrict__ e4,
-    double* scal, int it, const double* __restrict__ part_pq, int n_pq, float minv, int32_t G, uint32_t n_waves,
-    int64_t epad, uint32_t vbytes, double* __restrict__ part_out) {
+    double* scal, int it, const double* __restrict__ part_pq, int n_pq, float minv, int32_t E, int32_t G,
+    uint32_t n_waves, int64_t epad, uint32_t vbytes, double* __restrict__ part_out) {
     __shared__ double sh[LWPB];
     if (tl_done(scal, it)) return;
     const double alpha64 = it > 0 ? tl_alpha(scal, tl_sum<64 * LWPB>(part_pq, n_pq, 1, sh), it) : 0.0;
@@ -636,8 +665,6 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_update(
             for (int k = 0; k < N; ++k) rv[k] -= alpha * qv[k];
             row_store<N>(rr, off, rv);
         }
-        float ops[LaneShape<N>::NV];
-        load_inv_ops<N>(table, __builtin_amdgcn_readfirstlane(cls[run * 64u]), ops);
         f4 c4 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int k = 0; k < N; ++k)
@@ -646,8 +673,7 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_update(
                 if (bary.w[k][v] != 0.0f) c4[v] += bary.w[k][v] * rv[k];
         e4[(int64_t)a * epad + e] = c4;
         f4 acc[LaneShape<N>::NQ];
-        acc_zero<N>(acc);
-        lane_block<N, 5>(ops, rv, acc);
+        inv_rows<N>(table, cls, (int32_t)(run * 64u), E, rv, acc);
         float z[N];
         acc_rows<N>(acc, minv, z);
 #pragma unroll
@@ -702,8 +728,6 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_direction(
         }
         float rv[N];
         row_load<N>(rr, off, rv);
-        float ops[LaneShape<N>::NV];
-        load_inv_ops<N>(table, __builtin_amdgcn_readfirstlane(cls[run * 64u]), ops);
         const float* ya = y + (int64_t)a * ystr;
         f4 yc = {0.0f, 0.0f, 0.0f, 0.0f};     // (the slots past the mesh keep zeros)
         if (e >= E) {
@@ -714,8 +738,7 @@ __global__ void __launch_bounds__(64 * LWPB) k_lane_direction(
             yc = ((const f4*)ya)[e];
         }
         f4 acc[LaneShape<N>::NQ];
-        acc_zero<N>(acc);
-        lane_block<N, 5>(ops, rv, acc);
+        inv_rows<N>(table, cls, (int32_t)(run * 64u), E, rv, acc);
         float z[N];
         acc_rows<N>(acc, 1.0f, z);
 #pragma unroll
@@ -936,6 +959,7 @@ hipError_t lane_apply_f32(const stdg_mesh* m, const float* x, float* y, float cs
         case 4: CALL(4); break;                \
         case 10: CALL(10); break;              \
         case 20: CALL(20); break;              \
+        case 35: CALL(35); break;              \
         default: return hipErrorInvalidValue;  \
     }                                          \
     return hipGetLastError();
@@ -954,8 +978,8 @@ hipError_t lane_tl_update(const stdg_mesh* m, const TwoLevel& t, int it, int blo
     const uint32_t vbytes = (uint32_t)(4 * lane_len(m));
 #define STDG_CALL(n)                                                                                               \
     hipLaunchKernelGGL(k_lane_update<n>, dim3(blocks), dim3(64 * LWPB), 0, s, m->d.lane_ops, m->d.cls, t.r, t.q,    \
-                       (f4*)m->d.coarse.e4, t.scal, it, t.part_pq, tl_op_blocks(m), 1.0f / t.cscale, (int32_t)m->G, \
-                       lane_waves(m), m->d.coarse.epad, vbytes, t.part_up)
+                       (f4*)m->d.coarse.e4, t.scal, it, t.part_pq, tl_op_blocks(m), 1.0f / t.cscale, (int32_t)m->E, \
+                       (int32_t)m->G, lane_waves(m), m->d.coarse.epad, vbytes, t.part_up)
     STDG_TL(STDG_CALL)
 #undef STDG_CALL
 }
