@@ -96,6 +96,7 @@ int64_t visc_mfma_blocks(const stdg_mesh* m);
 inline bool segs_fill(const stdg_mesh* m) { return 4 * m->d.n_segs <= m->E; }
 inline bool face_groups_fill(const stdg_mesh* m) { return 4 * m->pd.n_face_groups <= (int64_t)m->faces.size(); }
 bool visc_mfma_supported(const stdg_mesh* m);
+hipError_t prec_mfma(const stdg_mesh* m, const double* x, double* y, hipStream_t s);
 hipError_t visc_mfma(const stdg_mesh* m, bool pre, int dots, const double* x, double* y, const double* w, double* part,
                      hipStream_t s);
 hipError_t launch_visc_apply(const stdg_mesh* m, const double* x, double* y, hipStream_t s);

@@ -197,6 +197,15 @@ __global__ void k_copy(const T* __restrict__ a, T* __restrict__ b, int64_t n) {
         b[i] = a[i];
 }
 
+template <typename T>
+__global__ void k_copy2(const T* __restrict__ a, T* __restrict__ b, T* __restrict__ c, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const T v = a[i];
+        b[i] = v;
+        c[i] = v;
+    }
+}
+
 // Per-time-node sums of a [E][G][N] vector: partial[g * NBLK + block]
 __global__ void __launch_bounds__(RT) k_time_sums(const double* __restrict__ v, int64_t E, int G, int N,
                                                   double* __restrict__ partial) {
@@ -890,9 +899,8 @@ int bicgstab(Ctx& c, const T* b, T* x, T* r, T* rh, T* p, T* v, T* s, T* t, doub
         }
     }
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(RT), 0, c.s, c.partial, NBLK, c.scal, (int)S_BRR, (int)FIN_STORE);
-    hipLaunchKernelGGL(k_copy<T>, dim3(gb), dim3(256), 0, c.s, r, rh, n);
-    hipLaunchKernelGGL(k_fill<T>, dim3(gb), dim3(256), 0, c.s, p, (T)0, n);
-    hipLaunchKernelGGL(k_fill<T>, dim3(gb), dim3(256), 0, c.s, v, (T)0, n);
+    // (the first direction is the residual itself)
+    hipLaunchKernelGGL(k_copy2<T>, dim3(gb), dim3(256), 0, c.s, r, rh, p, n);
     hipLaunchKernelGGL(k_bcg_init, dim3(1), dim3(1), 0, c.s, c.scal);
     CK(hipGetLastError());
     double rr;
@@ -907,7 +915,7 @@ int bicgstab(Ctx& c, const T* b, T* x, T* r, T* rh, T* p, T* v, T* s, T* t, doub
                       2 * visc_mfma_blocks(c.m) <= NBLK * 208;
     const int nd = dots ? (int)visc_mfma_blocks(c.m) : NBLK;
     while (iters < max_it) {
-        hipLaunchKernelGGL(k_bcg_p<T>, dim3(gb), dim3(256), 0, c.s, p, r, v, c.scal, n);
+        if (iters > 0) hipLaunchKernelGGL(k_bcg_p<T>, dim3(gb), dim3(256), 0, c.s, p, r, v, c.scal, n);
         if constexpr (std::is_same<T, double>::value) {
             if (dots) CK(visc_mfma(c.m, true, 1, p, v, rh, c.partial, c.s));
         }

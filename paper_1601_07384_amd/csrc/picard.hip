@@ -664,6 +664,7 @@ hipError_t launch_visc_apply(const stdg_mesh* m, const double* x, double* y, hip
 }
 
 hipError_t launch_visc_precond(const stdg_mesh* m, const double* x, double* y, hipStream_t s) {
+    if (visc_mfma_supported(m)) return prec_mfma(m, x, y, s);
     if (fast_blockdiag(m, x, y, s) == hipSuccess) return hipSuccess;
     const int NG = m->Nst;
     const int64_t n = 3 * m->E * NG;
@@ -922,8 +923,12 @@ extern "C" int stdg_picard_step(const stdg_mesh* cm, double* vhat, double* vbar,
     for (int k = 0; k < npic; ++k) {
         // step 1
         if (int e = stdg_main_from_dual(m, vk, vbk, s)) return e;
-        STDG_HIP(run_dualgrad(m, pk, dt, wg, s));
-        STDG_HIP(run_average(m, wg, lam, s));
+        if (k == 0 && zero_base && theta == 1.0) {
+            hipLaunchKernelGGL(k_zero, dim3(nblk(nM)), dim3(256), 0, s, lam, nM);   // pk = 0
+        } else {
+            STDG_HIP(run_dualgrad(m, pk, dt, wg, s));
+            STDG_HIP(run_average(m, wg, lam, s));
+        }
         // step 2
         CKP(launch_convection(m, vbk, vbc, ups, s));
         // step 3
