@@ -14,7 +14,7 @@ Krylov initial guess, pressure-correction solve to a 1e-10 relative
 residual, velocity update, inputs resident in HBM.  Before the timed steps
 `--record` steps are recorded and the guess model is trained on them on the
 GPU (reported, not timed).  The timed steps use the chosen form: pressure by
-the time-decoupled CG with FP32 inner solves (block-Jacobi preconditioned) in
+the time-decoupled CG with FP32 inner solves (two-level preconditioned) in
 FP64 refinement, each solve started from the extrapolation of its own
 history (the learned start, extrapolation plus a fitted network term, is
 measured beside it and does not beat it here); viscous solve by block-Jacobi
@@ -30,16 +30,19 @@ chosen (FP32 refinement PCG, extrapolated guess), with ablations that change
 one thing at a time (precision, preconditioner, initial guess, the learned
 guess).
 
-The roofline entry is for the step's dominant kernel, the one-kernel FP32 CG
-iteration (k_lane_chunk<N> on meshes whose 64-element runs share a geometry
-class, k_elem_iter<N, G> on meshes whose elements mostly carry their own
-blocks, k_cg_op<N, true> otherwise), together with the one-block scalar
-kernel k_cg_red that precedes each launch.  Its duration per iteration is the
+The roofline entry is for the step's dominant work, one iteration of the
+two-level preconditioned FP32 CG: the operator (k_lane_op<N, true> on meshes
+whose 64-element runs share a geometry class, k_elem_op<N, G, true> on meshes
+whose elements mostly carry their own blocks, k_cg_op<N, false, true>
+otherwise), the residual update, the second level (k_restrict, k_plane,
+k_columns, k_plane, or k_small) and the direction update.  Its duration is the
 library's own HIP-event measurement on its stream around the back-to-back
-iteration launches of the timed steps (stdg_step_report.pressure_fused_iter_us).
-Algorithmic bytes per iteration: read z, p, w, x and write them once (8 x 4 B
-per DoF) plus 20 B of indices per element, plus, for k_elem_iter, the six
-FP32 N x N blocks of every element (24 N^2 B per element).
+iterations of the timed steps (stdg_step_report.pressure_fused_iter_us).
+Algorithmic bytes per iteration: the operator reads p and writes q, the update
+reads r, q and writes r, the direction update reads r, p, x and writes p, x
+(10 x 4 B per DoF), 36 B of indices and 32 B of corner values per element (and
+time node), plus, for per-element operands, seven FP32 N x N blocks of every
+element (28 N^2 B).
 """
 
 import argparse
@@ -58,12 +61,11 @@ CONFIGS = {
     "c2": dict(n=24, p=3, pg=1, dt=1e-3, nu=1e-3, n_pic=2),
     "c5": dict(n=32, p=2, pg=1, dt=1e-3, nu=1e-3, n_pic=2),
 }
-# HBM bytes per launch of k_lane_chunk<20> on the 663,552-element cube from
-# rocprofv3 FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads
-# for a device copy of known size; valid only for the kernel source they were
-# measured on (sha256 prefix).  None until measured.
-MEASURED_TRAFFIC = {"source": "paper_1601_07384_amd/csrc/cg_lane.hip", "sha256": "7a1a70f3332b4361",
-                    "bytes": 530775654, "config": "c3"}
+# HBM bytes of one iteration on the 663,552-element cube from rocprofv3
+# FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads for a device
+# copy of known size; valid only for the kernel source they were measured on
+# (sha256 prefix).  None until measured.
+MEASURED_TRAFFIC = {"source": "paper_1601_07384_amd/csrc/cg_lane.hip", "sha256": None, "bytes": None, "config": "c3"}
 FP64_PEAK_TFLOPS = 78.6
 FP32_MFMA_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
@@ -228,7 +230,7 @@ def learned_guess_experiment(args, P, torch, m, c, vhat, vbar, p, hist, opts, la
     print(json.dumps({
         "metric": "first pressure-solve iterations and time to 1e-10 on held-out steps, by initial guess",
         "config": {"workload": label, "train_steps": T, "eval_steps": args.eval_steps, "epochs": args.epochs,
-                   "lr": args.lr, "solver": "FP32-inner block-Jacobi PCG in FP64 refinement, rtol 1e-10"},
+                   "lr": args.lr, "solver": "FP32-inner two-level PCG in FP64 refinement, rtol 1e-10"},
         "by_guess": summary,
         "learned_vs_extrapolated_first_iters": le / ex if ex else None,
         "network_beats_extrapolation": le < ex,
@@ -371,7 +373,7 @@ def main():
             ("fp32_pcg_previous", "chosen solver, previous-step guess", P.STDG_KRYLOV_PREVIOUS, press),
             ("fp32_pcg_learned", "chosen solver, learned guess (extrapolation + fitted network term)",
              P.STDG_KRYLOV_LEARNED, press),
-            ("chosen", "FP32-inner block-Jacobi PCG in FP64 refinement, extrapolated guess",
+            ("chosen", "FP32-inner two-level PCG in FP64 refinement, extrapolated guess",
              P.STDG_KRYLOV_EXTRAPOLATE, press),
         ]
         out_state = {}
@@ -398,11 +400,11 @@ def main():
                "p": float((pp_ - pc).abs().max() / pp_.abs().max())}
         del out_state, vp, pp_, vc, pc
 
-    # one-kernel FP32 CG iteration (B (x) I): z, p, w, x read and written once
+    # one iteration of the two-level FP32 CG (B (x) I): ten vector passes
     it_us = sum(r.pressure_fused_iter_us * r.pressure_iters for r in reps) / max(
         sum(r.pressure_iters for r in reps if r.pressure_fused_iter_us > 0), 1)
-    k_bytes = 8.0 * dofs * 4 + 20.0 * E + (24.0 * N * N * E if m.inner_per_element else 0.0)
-    k_flops = 2.0 * N * N * 5 * E * G
+    k_bytes = 10.0 * dofs * 4 + (36.0 + 32.0 * G) * E + (28.0 * N * N * E if m.inner_per_element else 0.0)
+    k_flops = 2.0 * N * N * 7 * E * G
     k_s = it_us * 1e-6 if it_us > 0 else float("nan")
     first = reps[0]
     out = {
@@ -430,15 +432,17 @@ def main():
             "plain": forms.get("plain", {}).get("step_pressure_s"),
             "chosen": forms.get("chosen", {}).get("step_pressure_s"),
             "plain_form": "FP64 CG from zero, every pressure solve of one step",
-            "chosen_form": "FP32-inner block-Jacobi PCG in FP64 refinement, extrapolated guess for the "
+            "chosen_form": "FP32-inner two-level PCG in FP64 refinement, extrapolated guess for the "
                            "first solve of the step",
             "chosen_vs_plain_rel_diff": err, "forms": forms},
         "roofline": {"bound": "hbm", "achieved": k_bytes / k_s / 1e9, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": k_bytes / k_s / 1e9 / HBM_PEAK_GBS,
                      "traffic": measured_traffic(args.config) if args.jitter == 0 else None,
-                     "kernel": (f"k_lane_chunk<{N}> + k_cg_red (one PCG iteration)" if run_layout
-                                else (f"k_elem_iter<{N},{G}> + k_cg_red (one PCG iteration)" if m.inner_per_element
-                                      else f"k_cg_op<{N},true> + k_cg_red (one PCG iteration)")), "kernel_us": it_us,
+                     "kernel": ((f"k_lane_op<{N},true>" if run_layout
+                                 else (f"k_elem_op<{N},{G},true>" if m.inner_per_element
+                                       else f"k_cg_op<{N},false,true>"))
+                                + " + residual update + second level + direction update (one two-level PCG "
+                                  "iteration)"), "kernel_us": it_us,
                      "kernel_launches": sum(r.pressure_iters for r in reps),
                      "bytes_per_launch": k_bytes, "flops_per_launch": k_flops,
                      "mfma_tflops": k_flops / k_s / 1e12,
