@@ -220,7 +220,8 @@ typedef struct {
                            /* every such block is SPD, and on meshes of more   */
                            /* than a few hundred elements that fill their      */
                            /* bounding box a second level for the smooth part  */
-                           /* of the error; other solves ignore it             */
+                           /* of the error (with it p = 4 too, on meshes of    */
+                           /* few classes); other solves ignore it             */
 } stdg_solve_opts;
 
 typedef struct {

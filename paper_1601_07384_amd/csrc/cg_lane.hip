@@ -2,8 +2,9 @@
 // operator y = c B x (B = dt^2 S^sp on one time node) and the block-Jacobi
 // step y = s B_e^-1 x (p = 1, 2, 3, 4), and the one-kernel preconditioned CG
 // iteration whose recurrences are documented with k_cg_op in cg_fused.hip
-// (p = 1, 2, 3).  They serve meshes whose 64-element runs share one geometry
-// class (the operator also takes runs of several classes, one pass each).
+// (p = 1, 2, 3), and the kernels of the two-level CG.  They serve meshes whose
+// 64-element runs share one geometry class; at p = 4 the operator and the
+// two-level kernels also take runs of several classes, one pass each.
 //
 // One wavefront per (64-element run, time node), lane l = element 64 run + l.
 // A lane holds whole rows of its element (the N values, loaded with the
@@ -893,9 +894,6 @@ int upload_lane_operands(stdg_mesh* m, const std::vector<double>& inv) {
     STDG_HIP(hipMemcpy(m->d.lane_ops, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice));
     return m->N == 35 ? STDG_OK : upload_chunk_tables(m);
 }
-
-// the one-kernel CG iteration runs in the run layout (p = 1, 2, 3)
-bool lane_iter_supported(const stdg_mesh* m) { return m->d.lane_ops != nullptr && m->N != 35; }
 
 // workgroups of the per-run kernels (a multiple of the 8 XCDs)
 int64_t lane_run_blocks(const stdg_mesh* m) { return ((int64_t)lane_waves(m) + LWPB - 1) / LWPB / 8 * 8 + 8; }
