@@ -1245,7 +1245,12 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
             // each inner solve reduces the residual by inner_rtol, but never
             // further than the final tolerance needs (a good initial guess
             // then saves inner iterations instead of overshooting)
+            // (the two-level CG stops at the iteration that meets its
+            // tolerance, the others up to two polling intervals, 8 to 16
+            // iterations, later: it aims lower by what those gain, so that
+            // its errors are no larger)
             const double inner_abs = std::max(o.inner_rtol * rn, 0.25 * o.rtol * bnorm);
+            const double two_abs = std::max(0.4 * o.inner_rtol * rn, 0.1 * o.rtol * bnorm);
             if (run_inner) {
                 // element-per-lane kernels: CG on c B (STDG_CG) or on B (x) I
                 // (STDG_CG_TIME, correction (I (x) C^-1) w) in the run layout
@@ -1256,7 +1261,7 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
                 c.run_layout = true;
                 c.op = o.method == STDG_CG ? 0 : 2;
                 status = cg_two_level(c)
-                             ? cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, inner_abs / rn,
+                             ? cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, two_abs / rn,
                                                   o.max_iter - inner_total, o.check_every, it, res)
                              : cg<float>(c, w.b32, w.x32, w.r32, w.p32, w.q32, inner_abs / rn,
                                          o.max_iter - inner_total, o.check_every, it, res);
@@ -1273,7 +1278,7 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
                 if (time) c.op = 2;
                 const bool two = (time || o.method == STDG_CG) && cg_two_level(c);
                 if (two)
-                    status = cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, inner_abs / rn,
+                    status = cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, two_abs / rn,
                                                 o.max_iter - inner_total, o.check_every, it, res);
                 c.op = 0;
                 if (two && time && status >= 0) {
