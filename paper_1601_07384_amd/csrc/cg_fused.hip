@@ -93,13 +93,13 @@ constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
 // eight launches instead of two, 25..33 us instead of 10..17 where latency is
 // all, and saves as many as the mesh is wide; walls double those of block
 // Jacobi.  Solve to 1e-10, ms, block Jacobi against two-level: periodic, 750
-// elements, p = 2 1.80 / 1.90, 1,296 2.14 / 1.96, p = 3 2.86 / 2.44, 1,536 (8 x 8 x
-// 4), p = 1 2.02 / 1.34, p = 3 3.77 / 2.24, 3,072 (8^3), p = 2 2.84 / 2.15, p = 3
-// 3.84 / 2.61, 82,944, p = 3, p_gamma = 1 22.5 / 5.8, 663,552 212 / 15.5; walls 384
-// 3.31 / 2.47, 1,296 4.33 / 2.43; scattered vertices (elements with their own
-// operands) 384 4.06 / 3.58, 750 4.83 / 2.90; p = 4 (no preconditioner without
-// the second level), 384 7.8 / 3.0, 3,072 12.0 / 4.2, 24,576, p_gamma = 1 34.0 /
-// 5.2, walls (runs of several classes: a pass each) 3,072 108 / 10.7.
+// elements, p = 2 1.80 / 1.90, 1,296 2.14 / 2.14, p = 3 2.86 / 2.67, 1,536 (8 x 8 x
+// 4), p = 1 2.02 / 1.33, p = 3 3.77 / 2.42, 3,072 (8^3), p = 2 2.84 / 2.26, p = 3
+// 3.84 / 2.73, 82,944, p = 3, p_gamma = 1 22.5 / 6.2, 663,552 212 / 15.5; walls 384
+// 3.31 / 2.5, 1,296 4.33 / 2.58; scattered vertices (elements with their own
+// operands) 384 4.06 / 3.6, 750 4.83 / 3.05; p = 4 (no preconditioner without the
+// second level), 384 7.8 / 3.2, 3,072 12.0 / 4.0, 24,576, p_gamma = 1 34.0 / 5.7,
+// walls (runs of several classes: a pass each) 3,072 108 / 10.4.
 constexpr int64_t TL_MIN_E_PERIODIC = 1000, TL_MIN_E = 384;
 int64_t tl_min_elements(const stdg_mesh* m) {
     return m->cfg.periodic && !elem_supported(m) && m->N != 35 ? TL_MIN_E_PERIODIC : TL_MIN_E;
