@@ -96,8 +96,8 @@ constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
 // elements, p = 2 1.80 / 1.90, 1,296 2.14 / 2.14, p = 3 2.86 / 2.67, 1,536 (8 x 8 x
 // 4), p = 1 2.02 / 1.33, p = 3 3.77 / 2.42, 3,072 (8^3), p = 2 2.84 / 2.26, p = 3
 // 3.84 / 2.73, 82,944, p = 3, p_gamma = 1 22.5 / 6.2, 663,552 212 / 15.5; walls 384
-// 3.31 / 2.5, 1,296 4.33 / 2.58; scattered vertices (elements with their own
-// operands) 384 4.06 / 3.6, 750 4.83 / 3.05; p = 4 (no preconditioner without the
+// 3.31 / 2.27, 1,296 4.33 / 2.56; scattered vertices (elements with their own
+// operands) 384 4.06 / 2.45, 750 4.83 / 2.69; p = 4 (no preconditioner without the
 // second level), 384 7.8 / 3.2, 3,072 12.0 / 4.0, 24,576, p_gamma = 1 34.0 / 5.7,
 // walls (runs of several classes: a pass each) 3,072 108 / 10.4.
 constexpr int64_t TL_MIN_E_PERIODIC = 1000, TL_MIN_E = 384;
