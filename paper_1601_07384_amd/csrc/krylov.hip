@@ -545,9 +545,10 @@ int cg_fused(Ctx& c, const float* b, float* x, float* r, float* p, float* q, dou
 // level and the direction update; alpha, beta and the convergence test are
 // formed on the device, and once the test holds the kernels still queued
 // return at once, so the host polls without draining the queue.  iters is
-// the iteration that met the tolerance.
-bool cg_two_level(const Ctx& c) {
-    return c.precond && (c.op == 2 || (c.op == 0 && c.m->G == 1)) && coarse_supported(c.m) && c.m->ws.ev[0] &&
+// the iteration that met the tolerance.  Its vectors are in the run layout where
+// lane_supported, element-major otherwise.
+bool cg_two_level(const Ctx& c, int op) {
+    return c.precond && (op == 2 || (op == 0 && c.m->G == 1)) && coarse_supported(c.m) && c.m->ws.ev[0] &&
            tl_op_blocks(c.m) + 2 * tl_upd_blocks(c.m) <= NBLK * 208;
 }
 
@@ -1220,8 +1221,13 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
         if (status == STDG_OK && rel > o.rtol) status = STDG_NOT_CONVERGED;
     } else {
         // FP64 iterative refinement around FP32 Krylov solves
-        const bool run_inner = lane_supported(m) && (o.method == STDG_CG || o.method == STDG_CG_TIME) &&
-                               w.p32b && 2 * cg_partial_len(m) <= (int64_t)NBLK * 208;
+        // The layout follows the solver: on meshes of the element-per-lane
+        // kernels the run layout for the two-level CG (at every size) and for
+        // the one-kernel CG while its partials fit (about 3.4 M, in chunks 5.1 M
+        // elements times time nodes), element-major for all else.
+        const bool time = o.method == STDG_CG_TIME, two = (time || o.method == STDG_CG) && cg_two_level(c, time ? 2 : 0);
+        const bool run_inner = lane_supported(m) && (two || ((time || o.method == STDG_CG) && w.p32b &&
+                                                             2 * cg_partial_len(m) <= (int64_t)NBLK * 208));
         for (outer = 1; outer <= o.max_outer + 1; ++outer) {
             if (int e = check(rel)) return e;
             if (outer == 1) rel0 = rel;
@@ -1259,9 +1265,8 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
                 hipLaunchKernelGGL(k_fill<float>, dim3(grid_for(n32)), dim3(256), 0, c.s, w.x32, 0.0f, n32);
                 c.n = n32;
                 c.run_layout = true;
-                c.op = o.method == STDG_CG ? 0 : 2;
-                status = cg_two_level(c)
-                             ? cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, two_abs / rn,
+                c.op = time ? 2 : 0;
+                status = two ? cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, two_abs / rn,
                                                   o.max_iter - inner_total, o.check_every, it, res)
                              : cg<float>(c, w.b32, w.x32, w.r32, w.p32, w.q32, inner_abs / rn,
                                          o.max_iter - inner_total, o.check_every, it, res);
@@ -1270,13 +1275,11 @@ int solve_with(stdg_mesh* m, const double* b, double* x, const stdg_solve_opts& 
                 c.op = 0;
                 inner_total += it;
                 if (status < 0) return status;
-                CK(lane_unpack(m, w.x32, o.method == STDG_CG ? nullptr : m->d.Cinv, rn, true, x, c.s));
+                CK(lane_unpack(m, w.x32, time ? m->d.Cinv : nullptr, rn, true, x, c.s));
             } else {
                 hipLaunchKernelGGL(k_d2f_scaled, dim3(gb), dim3(256), 0, c.s, w.r, w.b32, 1.0 / rn, n);
                 hipLaunchKernelGGL(k_fill<float>, dim3(gb), dim3(256), 0, c.s, w.x32, 0.0f, n);
-                const bool time = o.method == STDG_CG_TIME;
-                if (time) c.op = 2;
-                const bool two = (time || o.method == STDG_CG) && cg_two_level(c);
+                c.op = two && time ? 2 : 0;
                 if (two)
                     status = cg_two_level_solve(c, w.b32, w.x32, w.p32, w.q32, two_abs / rn,
                                                 o.max_iter - inner_total, o.check_every, it, res);
