@@ -373,29 +373,48 @@ void line_eigen(const std::vector<double>& x, bool periodic, double L, std::vect
     V.swap(W);
 }
 
-// the distinct values of coordinate d of the element corners (within tol;
-// with a period, hi is identified with lo), empty past MAXN of them
-std::vector<double> lines_of(const stdg_mesh* m, int d, double lo, double hi, bool periodic, double tol) {
-    std::vector<double> x;
+// A line of vertices in one direction: the values from lo to hi, no gap
+// between neighbouring ones above tol.  A value joins every line within tol of
+// it, so the outcome is the same in any order of the values, every value lies
+// in its line, and the index found by line_of is that of a line whatever the
+// coordinates' noise.
+struct Line { double lo, hi; };
+void join(std::vector<Line>& l, Line v, double tol) {
+    const auto a = std::lower_bound(l.begin(), l.end(), v.lo - tol, [](const Line& q, double at) { return q.hi < at; });
+    auto b = a;
+    for (; b != l.end() && b->lo <= v.hi + tol; ++b) v = Line{std::min(v.lo, b->lo), std::max(v.hi, b->hi)};
+    if (a == b) {
+        l.insert(a, v);
+    } else {
+        *a = v;
+        l.erase(a + 1, b);
+    }
+}
+int line_of(const std::vector<Line>& l, double v) {
+    const auto a = std::upper_bound(l.begin(), l.end(), v, [](double at, const Line& q) { return at < q.lo; });
+    return std::max((int)(a - l.begin()) - 1, 0);
+}
+
+// the lines of coordinate d of the element corners (with a period, hi is
+// identified with lo), empty past MAXN of them
+std::vector<Line> lines_of(const stdg_mesh* m, int d, double lo, double hi, bool periodic, double tol) {
+    std::vector<Line> x;
     bool many = false;
-    auto insert = [tol](std::vector<double>& l, double v) {
-        const auto it = std::lower_bound(l.begin(), l.end(), v - tol);
-        if (it == l.end() || std::fabs(*it - v) > tol) l.insert(it, v);
-    };
 #pragma omp parallel
     {
-        std::vector<double> own;
+        std::vector<Line> own;
 #pragma omp for schedule(static)
         for (int64_t t = 0; t < m->E; ++t)
             for (int k = 0; k < 4 && (int)own.size() <= MAXN; ++k) {
-                const double v = (double)m->vert[t][k][d];
-                insert(own, periodic && std::fabs(v - hi) < tol ? lo : v);
+                double v = (double)m->vert[t][k][d];
+                if (periodic && std::fabs(v - hi) < tol) v = lo;
+                join(own, Line{v, v}, tol);
             }
 #pragma omp critical
         {
             many = many || (int)own.size() > MAXN;
             for (size_t i = 0; i < own.size() && !many; ++i) {
-                insert(x, own[i]);
+                join(x, own[i], tol);
                 many = (int)x.size() > MAXN;
             }
         }
@@ -447,12 +466,14 @@ int upload_coarse(stdg_mesh* m) {
     const bool per = m->cfg.periodic != 0;
     const double h = std::cbrt(6.0 * vol / (double)E);
     std::vector<double> x[3];
+    std::vector<Line> line[3];
     double tol[3];
     bool tensor = true;
     size_t nodes = 1;
     for (int d = 0; d < 3; ++d) {
         tol[d] = 1e-6 * std::min(h, L[d]);
-        if (tensor) x[d] = lines_of(m, d, lo[d], hi[d], per, tol[d]);
+        if (tensor) line[d] = lines_of(m, d, lo[d], hi[d], per, tol[d]);
+        for (const Line& v : line[d]) x[d].push_back(v.lo + 0.5 * (v.hi - v.lo));
         tensor = tensor && !x[d].empty();
         nodes *= x[d].size();
     }
@@ -501,7 +522,7 @@ int upload_coarse(stdg_mesh* m) {
                 double v = (double)m->vert[t][k][d];
                 if (tensor) {
                     if (per && std::fabs(v - hi[d]) < tol[d]) v = lo[d];
-                    i0[d] = (int)(std::lower_bound(x[d].begin(), x[d].end(), v - tol[d]) - x[d].begin());
+                    i0[d] = line_of(line[d], v);
                 } else {
                     const int cells = per ? n[d] : n[d] - 1;
                     const double s = (v - lo[d]) / L[d] * cells;
