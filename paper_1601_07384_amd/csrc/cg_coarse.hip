@@ -52,10 +52,14 @@ constexpr int RL1 = 8, RLW = 64;
 
 inline int pad16(int n) { return (n + 15) / 16 * 16; }
 
-// g[a][node] = sum over the corners that reach the node, RL lanes per node,
-// entries of a node contiguous (padded with slot -1), summed in a fixed order
+// g[a][node] = sum over the corners that reach the node, RL lanes per node, in a
+// fixed order.  A node of a tensor grid has K entries (padded with slot -1),
+// one between scattered vertices the entries row[node] .. row[node + 1]: there
+// the fullest node has many times the mean (graded meshes, 3,072 elements, 14 to
+// 47 times), and padded rows would be mostly padding, read in every iteration.
 template <bool HASW>
-__global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ slot, const float* __restrict__ w, int K,
+__global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ slot, const float* __restrict__ w,
+                                                  const int64_t* __restrict__ row, int K,
                                                   const float* __restrict__ e4, int64_t estr, float* __restrict__ g,
                                                   int nodes, const double* __restrict__ scal, int it) {
     constexpr int RL = HASW ? RLW : RL1;
@@ -65,10 +69,14 @@ __global__ void __launch_bounds__(256) k_restrict(const int32_t* __restrict__ sl
     float s = 0.0f;
     if (j < nodes) {
         const float* ea = e4 + a * estr;
-        for (int k = l; k < K; k += RL) {
-            const int c = slot[j * K + k];
-            const float v = c >= 0 ? ea[c] : 0.0f;
-            s += HASW ? w[j * K + k] * v : v;
+        if (HASW) {
+            const int64_t end = row[j + 1];
+            for (int64_t k = row[j] + l; k < end; k += RL) s += w[k] * ea[slot[k]];
+        } else {
+            for (int k = l; k < K; k += RL) {
+                const int c = slot[j * K + k];
+                s += c >= 0 ? ea[c] : 0.0f;
+            }
         }
     }
 #pragma unroll
@@ -534,16 +542,27 @@ int upload_coarse(stdg_mesh* m) {
             else tri[4 * t + k] = TriCorner{i0[0] | (i0[1] << 10) | (i0[2] << 20), {f[0], f[1], f[2]}};
         }
     for (int64_t c4 = 0; c4 < 4 * E; ++c4) visit(c4, [&](int j, float) { ++count[j]; });
-    const int RL = tensor ? RL1 : RLW;
-    const int K = (*std::max_element(count.begin(), count.end()) + RL - 1) / RL * RL;
-    if ((int64_t)K * N3 > ((int64_t)1 << 28)) return STDG_OK;     // a few nodes that every corner reaches
-    std::vector<int32_t> slot((size_t)N3 * K, -1);
-    std::vector<float> wgt(tensor ? 0 : (size_t)N3 * K, 0.0f);
+    std::vector<int64_t> row(tensor ? 0 : N3 + 1, 0);
+    int K = 0;
+    size_t entries = 0;
+    if (tensor) {
+        K = (*std::max_element(count.begin(), count.end()) + RL1 - 1) / RL1 * RL1;
+        entries = (size_t)K * N3;
+        // a node that many more corners reach than others (2 on a cube of 4^3
+        // hexahedra with walls)
+        if (entries > 8 * (size_t)(4 * E)) return STDG_OK;
+    } else {
+        for (int j = 0; j < N3; ++j) row[j + 1] = row[j] + count[j];
+        entries = (size_t)row[N3];
+    }
+    std::vector<int32_t> slot(entries, -1);
+    std::vector<float> wgt(tensor ? 0 : entries, 0.0f);
     std::fill(count.begin(), count.end(), 0);
     for (int64_t c4 = 0; c4 < 4 * E; ++c4)
         visit(c4, [&](int j, float w) {
-            slot[(size_t)j * K + count[j]] = (int32_t)c4;
-            if (!tensor) wgt[(size_t)j * K + count[j]] = w;
+            const size_t at = (tensor ? (size_t)j * K : (size_t)row[j]) + count[j];
+            slot[at] = (int32_t)c4;
+            if (!tensor) wgt[at] = w;
             ++count[j];
         });
     // one-dimensional eigenproblems (equal lines share one)
@@ -582,7 +601,7 @@ int upload_coarse(stdg_mesh* m) {
     c.K = K;
     c.epad = epad;
     Pack pk;
-    size_t at[14];
+    size_t at[15];
     for (int d = 0; d < 3; ++d) {
         at[d] = pk.add(mats[d]);
         at[3 + d] = pk.add(matsT[d]);
@@ -591,6 +610,7 @@ int upload_coarse(stdg_mesh* m) {
     at[7] = pk.add(slot);
     at[8] = tensor ? pk.add(corner) : pk.add(tri);
     at[9] = tensor ? 0 : pk.add(wgt);
+    at[14] = tensor ? 0 : pk.add(row);
     const size_t copied = pk.host.size();
     // work vectors after the tables
     size_t end = copied;
@@ -618,6 +638,7 @@ int upload_coarse(stdg_mesh* m) {
     } else {
         c.tri = base + at[8];
         c.wgt = (float*)(base + at[9]);
+        c.row = (int64_t*)(base + at[14]);
         c.yc = (float*)(base + yc);
     }
     c.e4 = (float*)(base + at[10]);
@@ -673,10 +694,10 @@ hipError_t coarse_solve(const stdg_mesh* m, const double* scal, int it, hipStrea
     const bool small = small_grid(c), gather = small && !c.wgt && c.nodes <= SMALL_GATHER;
     const dim3 rgrid((unsigned)(((int64_t)c.nodes * (c.wgt ? RLW : RL1) + 255) / 256), G);
     if (c.wgt)
-        hipLaunchKernelGGL(k_restrict<true>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
+        hipLaunchKernelGGL(k_restrict<true>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.row, c.K, c.e4, estr, c.g, c.nodes,
                            scal, it);
     else if (!gather)
-        hipLaunchKernelGGL(k_restrict<false>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.K, c.e4, estr, c.g, c.nodes,
+        hipLaunchKernelGGL(k_restrict<false>, rgrid, dim3(256), 0, s, c.slot, c.wgt, c.row, c.K, c.e4, estr, c.g, c.nodes,
                            scal, it);
     if (small) {
         // (a thread per node)

@@ -39,13 +39,15 @@ struct CoarseTables {
     float cut = 0.0f;             // eigenvalue sums below it belong to the constant mode
     float scale = 0.0f;           // 1 / dt^2
     void* base = nullptr;         // the one allocation that holds all of the following
-    int K = 0;                    // restriction entries per node
+    int K = 0;                    // restriction entries per node (tensor grid)
     int64_t epad = 0;             // elements, padded to whole 64-element runs
     float* V[3] = {nullptr, nullptr, nullptr};    // [n][n] eigenvectors, padded to multiples of 16
     float* VT[3] = {nullptr, nullptr, nullptr};   // transposed
     float* lam = nullptr;         // eigenvalues, x then y then z
-    int32_t* slot = nullptr;      // [nodes][K] corner (4 element + corner) reaching the node, -1 padding
-    float* wgt = nullptr;         // its weight (null: all one)
+    int32_t* slot = nullptr;      // corners (4 element + corner) reaching a node: [nodes][K], -1 padding,
+                                  // or by row
+    float* wgt = nullptr;         // their weights (null: all one)
+    int64_t* row = nullptr;       // [nodes + 1] first entry of a node (with wgt)
     int32_t* corner = nullptr;    // [epad][4] grid node of each corner (null: interpolated)
     void* tri = nullptr;          // [epad][4] trilinear position of each corner
     float* yc = nullptr;          // [G][epad][4] interpolated corner values
