@@ -49,6 +49,30 @@ constexpr int CC = 32;          // columns per workgroup of the column kernel
 // by about 24 corners, one of a grid between scattered vertices by about 190
 // (4,374 scattered elements: 14.6 us with 8 lanes per node, 5.0 with 64)
 constexpr int RL1 = 8, RLW = 64;
+// Where the second level does not earn its launches and passes (an iteration
+// takes 1.4 to 3 times that of block Jacobi alone) block Jacobi stays alone: on
+// elements many cells wide, which alias the grid functions, and on lines of
+// very different spacing, where the FP32 rounding of the smooth part reaches
+// the rough one.  Periodic meshes need half the iterations of block Jacobi, so
+// small ones earn less.  Solve to 1e-8, time of two-level / block Jacobi, 384 to
+// 7,986 elements, p = 1, 2, 3; spacings graded by the given factor:
+//   scattered, walls, elements 2.8 cells wide (graded 10 in all directions) 0.53
+//   to 0.90, 3.5 (30) 0.90 to 2.5, more (100) 1.3 to 6.1; periodic 2.0 (4) 0.50
+//   to 1.01, 2.8 (10) 0.72 to 1.18, 3.1 (15) 0.85 to 1.22, and 24,576 elements
+//   2.8 0.77;
+//   tensor grid, walls, 100 or 127 0.35 to 0.97, once 1.21 (127), 1,000 0.48 to
+//   1.60, 10^4 0.46 to 1.02 at p = 1, 2 and not converged at p = 3; periodic,
+//   common blocks, 8 0.53 to 0.97, 16 0.76 to 1.23, 100 0.90 to 1.31, from 24,576
+//   elements 100 0.80 to 0.96; periodic, blocks per element, 384 and 1,296
+//   elements 10 0.72 to 0.92, 100 0.85 to 1.35, from 3,072 100 0.73 to 1.03.
+struct Limits {
+    double width;       // cells an element spans in any direction
+    double grading;     // widest spacing / narrowest, all directions together
+};
+Limits limits(const stdg_mesh* m) {
+    const bool small = m->cfg.periodic && m->N != 35 && m->E < 16384;
+    return Limits{small ? 2.25 : 3.25, small && (!elem_supported(m) || m->E < 3000) ? 8.0 : 100.5};
+}
 
 inline int pad16(int n) { return (n + 15) / 16 * 16; }
 
@@ -496,6 +520,15 @@ int upload_coarse(stdg_mesh* m) {
         }
         if (x[d].size() < 2) return STDG_OK;
     }
+    double narrow = 1e300, spread = 0.0;
+    for (int d = 0; d < 3; ++d)
+        for (size_t i = 0; i + 1 < x[d].size() + (per ? 1 : 0); ++i) {
+            const double w = i + 1 < x[d].size() ? x[d][i + 1] - x[d][i] : x[d][0] + L[d] - x[d][i];
+            narrow = std::min(narrow, w);
+            spread = std::max(spread, w);
+        }
+    const Limits lim = limits(m);
+    if (tensor && spread > lim.grading * narrow) return STDG_OK;
     const int n[3] = {(int)x[0].size(), (int)x[1].size(), (int)x[2].size()};
     const int G = m->G;
     const int64_t epad = (E + 63) / 64 * 64;
@@ -521,26 +554,36 @@ int upload_coarse(stdg_mesh* m) {
             if (w != 0.0f) f(node(i[0], i[1], i[2]), w);
         }
     };
-#pragma omp parallel for schedule(static)
-    for (int64_t t = 0; t < E; ++t)
+    double wide = 0.0;
+#pragma omp parallel for schedule(static) reduction(max : wide)
+    for (int64_t t = 0; t < E; ++t) {
+        double first[3], last[3];
         for (int k = 0; k < 4; ++k) {
             int i0[3];
             float f[3];
+            double pos[3];      // in cells, a period not wrapped
             for (int d = 0; d < 3; ++d) {
-                double v = (double)m->vert[t][k][d];
+                const double v = (double)m->vert[t][k][d];
                 if (tensor) {
-                    if (per && std::fabs(v - hi[d]) < tol[d]) v = lo[d];
-                    i0[d] = line_of(line[d], v);
+                    const bool up = per && std::fabs(v - hi[d]) < tol[d];
+                    i0[d] = up ? 0 : line_of(line[d], v);
+                    pos[d] = up ? n[d] : i0[d];
                 } else {
                     const int cells = per ? n[d] : n[d] - 1;
                     const double s = (v - lo[d]) / L[d] * cells;
                     i0[d] = std::min(std::max((int)std::floor(s), 0), cells - 1);
                     f[d] = (float)std::min(std::max(s - i0[d], 0.0), 1.0);
+                    pos[d] = s;
                 }
+                first[d] = k > 0 ? std::min(first[d], pos[d]) : pos[d];
+                last[d] = k > 0 ? std::max(last[d], pos[d]) : pos[d];
             }
             if (tensor) corner[4 * t + k] = node(i0[0], i0[1], i0[2]);
             else tri[4 * t + k] = TriCorner{i0[0] | (i0[1] << 10) | (i0[2] << 20), {f[0], f[1], f[2]}};
         }
+        for (int d = 0; d < 3; ++d) wide = std::max(wide, last[d] - first[d]);
+    }
+    if (wide > lim.width) return STDG_OK;
     for (int64_t c4 = 0; c4 < 4 * E; ++c4) visit(c4, [&](int j, float) { ++count[j]; });
     std::vector<int64_t> row(tensor ? 0 : N3 + 1, 0);
     int K = 0;

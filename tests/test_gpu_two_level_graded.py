@@ -72,3 +72,49 @@ def test_memory_of_the_tables(ratio):
         del m
     print("  bytes per element:", [round(u / len(T)) for u in used], flush=True)
     assert used[2] - used[1] <= 1024 * len(T)
+
+
+CASES = [
+    # name, n per direction, grading per direction (sign: two-sided), jitter, p, p_gamma, periodic, second level
+    ("scattered, 10", (8, 8, 8), (10, 10, 10), 0.2, 2, 0, False, True),
+    ("scattered, 30", (8, 8, 8), (30, 30, 30), 0.2, 1, 0, False, False),
+    ("scattered, 30 both ends", (8, 8, 8), (-30, -30, -30), 0.2, 2, 0, False, False),
+    ("scattered, 100", (8, 8, 8), (100, 100, 100), 0.2, 3, 0, False, False),
+    ("scattered, 100 both ends", (8, 8, 8), (-100, -100, -100), 0.2, 2, 1, False, False),
+    ("scattered, 300", (8, 8, 8), (300, 300, 300), 0.2, 1, 0, False, False),
+    ("scattered periodic, 10", (8, 8, 8), (10, 10, 10), 0.2, 1, 0, True, False),
+    ("tensor, 100 in z", (8, 8, 8), (1, 1, 100), 0.0, 2, 0, False, True),
+    ("tensor, 1e4 in z", (6, 6, 6), (1, 1, 1e4), 0.0, 3, 0, False, False),
+    ("tensor, 1000", (4, 4, 4), (1000, 1000, 1000), 0.0, 1, 0, False, False),
+    ("tensor periodic, 4 in z", (8, 8, 16), (1, 1, 4), 0.0, 2, 1, True, True),
+    ("tensor periodic, 64 in z", (8, 8, 16), (1, 1, 64), 0.0, 2, 1, True, False),
+    ("tensor periodic, p = 4, 64 in z", (8, 8, 8), (1, 1, 64), 0.0, 4, 0, True, True),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_second_level_only_where_it_pays(case):
+    """With the polls 64 iterations apart block Jacobi alone takes a multiple of
+    64, the two-level CG the iterations that it needs.  Where the second level is
+    used it has to halve the iterations, or nearly (an iteration takes about
+    twice as long), of the same mesh with its corners pulled out by a thousandth
+    of a spacing, which no longer fills its box and so has block Jacobi alone."""
+    name, n, grading, jitter, p, pg, periodic, second = case
+    print("two-level,", name, flush=True)
+    X, T = graded_mesh([graded_lines(k, abs(g), g < 0) for k, g in zip(n, grading)], jitter)
+    its = []
+    for pull in (0.0, 1.0) if second else (0.0,):
+        Y = X.copy()
+        corner = np.all((X == 0.0) | (X == 1.0), axis=1)
+        Y[corner if periodic else 0] -= pull * 1e-3 * X[X > 0].min()
+        m = P.Mesh(Y, T, p, pg, dt=1e-2, periodic=periodic)
+        x, b = system(m, Y, T)
+        xs = torch.zeros_like(b)
+        rep = m.solve(b, xs, method=P.STDG_CG_TIME, precision=P.STDG_FP32, rtol=1e-8, inner_rtol=1e-4,
+                      max_iter=64000, check_every=64)
+        assert rep.status == 0 and rep.rel_residual <= 1e-8
+        its.append(rep.inner_iters)
+    print(f"  {m.E} elements, iterations: {its}", flush=True)
+    assert (its[0] % 64 != 0) == second
+    if second:
+        assert its[1] % 64 == 0 and its[0] < 0.55 * its[1]
