@@ -267,6 +267,13 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __re
     put_rows<N, G>(A, l.wave, l.lane, l.hi, out, e0 + 16 * l.wave, e1, acc, 0, [&](int a) { return dt * W[a]; });
 }
 
+// components per workgroup of the viscous right-hand side: beside the sums it
+// holds as many mixed columns, so all three only at p = 1 with few time nodes.
+// One against three, us: 3,072 elements, p = 2, p_gamma = 4 26.5 -> 8.8 (14.6 on
+// the vector units), p = 3, p_gamma = 2 26.1 -> 9.9; 48,000, p = 2, p_gamma = 4
+// 104 -> 61 (94; three spilled 64 registers), p_gamma = 1 23.2 -> 23.1.
+template <int N, int G> constexpr int rhs_comps() { return N == 4 && G <= 3 ? 3 : 1; }
+
 // viscous right-hand side: M (sum_b g0g1[a][b] vprev_b - T[a][b] lam_b) - ups_a - nu dt W_a sum_{bdry f} BB_f vbc
 template <int N, int G>
 __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double* __restrict__ MIt, const double* __restrict__ BBt,
@@ -277,7 +284,7 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double*
                                                   const double* __restrict__ ups, const double* __restrict__ lam,
                                                   const double* __restrict__ vbc, double nu_dt,
                                                   double* __restrict__ rhs, int64_t E, int64_t F, uint32_t n_groups) {
-    constexpr int NQ = M64<N>::NQ, CP = comps<N, G>();
+    constexpr int NQ = M64<N>::NQ, CP = rhs_comps<N, G>();
     __shared__ double A[lds_size<N, G, 1>()];
     const uint32_t gi = m64_group(gridDim.x);
     if (gi >= n_groups) return;
@@ -416,7 +423,7 @@ hipError_t rows_visc_rhs(const stdg_mesh* m, const double* vprev, const double* 
     const PicardDevice& d = m->pd;
     const int64_t E = m->E, F = (int64_t)m->faces.size();
 #define STDG_CALL(n, g)                                                                                            \
-    hipLaunchKernelGGL((kr_visc_rhs<n, g>), dim3(m64_blocks(m->d.n_segs), 3 / comps<n, g>()), dim3(RT), 0, s, d.MIt, d.BBt,       \
+    hipLaunchKernelGGL((kr_visc_rhs<n, g>), dim3(m64_blocks(m->d.n_segs), 3 / rhs_comps<n, g>()), dim3(RT), 0, s, d.MIt, d.BBt,       \
                        (const m64_i4*)m->d.segs, m->d.nbr, d.tet_face, d.g0g1, d.Tm, d.W, vprev, ups, lam, vbc,      \
                        m->cfg.nu * m->cfg.dt, rhs, E, F, (uint32_t)m->d.n_segs)
     STDG_ROWS(STDG_CALL)
