@@ -226,10 +226,10 @@ hipError_t launch_conv(const stdg_mesh* m, const double* vbar, const double* vbc
 
 }  // namespace
 
-// groups that fill, the sums of all time nodes in registers (N G up to 80),
+// groups that pay, the sums of all time nodes in registers (N G up to 80),
 // and buffer offsets below 2 GiB
 hipError_t conv_mfma(const stdg_mesh* m, const double* vbar, const double* vbc, double* ups, hipStream_t s) {
-    if (!segs_fill(m) || 8 * (int64_t)m->faces.size() * m->Nst >= ((int64_t)1 << 31)) return hipErrorNotSupported;
+    if (!groups_pay(m, GroupKernel::CONVECTION) || 8 * (int64_t)m->faces.size() * m->Nst >= ((int64_t)1 << 31)) return hipErrorNotSupported;
 #define STDG_CV(n, g) \
     if (m->N == n && m->G == g) return launch_conv<n, g>(m, vbar, vbc, ups, s);
     STDG_CV(4, 1) STDG_CV(4, 2) STDG_CV(4, 3) STDG_CV(4, 4) STDG_CV(4, 5)

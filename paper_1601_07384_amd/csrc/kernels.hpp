@@ -86,15 +86,14 @@ hipError_t launch_cg_check_f32(const double* part, int64_t n_part, double* scal,
 hipError_t time_mix_f64(const stdg_mesh* m, const double* M, const double* x, double* y, hipStream_t s);
 hipError_t time_mix_f32(const stdg_mesh* m, const float* M, const float* x, float* y, hipStream_t s);
 int64_t visc_mfma_blocks(const stdg_mesh* m);
-// Whether the groups of elements (of faces) with common blocks, stdg_mesh
-// tables `segs` and `face_groups`, hold four and more on average; structured
-// meshes hold 16 (9) from 384 elements on.  Group kernel / general kernel on
-// 1,960 groups of 1.2 (4.8) elements, us: average, p = 3 25 / 122 (27 / 91),
-// pressure operator, p = 4, 55 / 21 (55 / 70); goback, p = 2, 16 / 12 (16 / 10).
-// On many groups the first cost 25 ns per group (average, p = 3, p_gamma = 1),
-// the others 3.3 ns per element.
+// Whether a kernel that takes a workgroup per group of elements (faces) with
+// common blocks, stdg_mesh tables `segs` and `face_groups`, is used; see
+// groups_pay for where the line lies.
+enum class GroupKernel { AVERAGE, FACES, RHS, VISC_RHS, VISCOUS, CONVECTION };
+bool groups_pay(const stdg_mesh* m, GroupKernel k);
+// the FP64 operator's groups: four and more elements on average (1,960 groups of
+// 4.8 elements, p = 4 55 us, by schur_apply_list 70; of 1.2 55 / 21)
 inline bool segs_fill(const stdg_mesh* m) { return 4 * m->d.n_segs <= m->E; }
-inline bool face_groups_fill(const stdg_mesh* m) { return 4 * m->pd.n_face_groups <= (int64_t)m->faces.size(); }
 bool visc_mfma_supported(const stdg_mesh* m);
 hipError_t prec_mfma(const stdg_mesh* m, const double* x, double* y, hipStream_t s);
 hipError_t visc_mfma(const stdg_mesh* m, bool pre, int dots, const double* x, double* y, const double* w, double* part,
@@ -104,7 +103,7 @@ int model_predict(stdg_model* md, const stdg_mesh* m, const double* P, const dou
                   double* x0, hipStream_t s, bool correction_only);
 int device_dots(stdg_mesh* m, int k, const double* const* a, const double* const* b, int64_t n, hipStream_t s,
                 double* out);
-bool rows_mfma_supported(const stdg_mesh* m, bool faces);
+bool rows_mfma_supported(const stdg_mesh* m, GroupKernel k);
 hipError_t rows_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s);
 hipError_t rows_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0, int64_t f1,
                        hipStream_t s);

@@ -584,7 +584,7 @@ int upload(T*& dst, const std::vector<T>& src) {
 // p <= 4, the thread-per-coefficient kernels above otherwise.
 hipError_t run_goback(const stdg_mesh* m, const double* vbar, const double* vbdry, double* out, int64_t f0,
                       int64_t f1, hipStream_t s) {
-    if (rows_mfma_supported(m, true)) return rows_goback(m, vbar, vbdry, out, f0, f1, s);
+    if (rows_mfma_supported(m, GroupKernel::FACES)) return rows_goback(m, vbar, vbdry, out, f0, f1, s);
     if (fast_rows_supported(m)) return fast_goback(m, vbar, vbdry, out, f0, f1, s);
     const PicardDevice& d = m->pd;
     const int64_t n = 3 * (f1 - f0) * m->G * m->N;
@@ -595,7 +595,7 @@ hipError_t run_goback(const stdg_mesh* m, const double* vbar, const double* vbdr
 }
 
 hipError_t run_average(const stdg_mesh* m, const double* vhat, double* vbar, hipStream_t s) {
-    if (rows_mfma_supported(m, false)) return rows_average(m, vhat, vbar, s);
+    if (rows_mfma_supported(m, GroupKernel::AVERAGE)) return rows_average(m, vhat, vbar, s);
     if (fast_rows_supported(m)) return fast_average(m, vhat, vbar, s);
     const int64_t n = 3 * m->E * m->Nst;
     hipLaunchKernelGGL(k_average, dim3(nblk(n)), dim3(256), 0, s, m->pd.A, m->d.cls, m->pd.tet_face, vhat, vbar, m->E,
@@ -604,7 +604,7 @@ hipError_t run_average(const stdg_mesh* m, const double* vhat, double* vbar, hip
 }
 
 hipError_t run_dualgrad(const stdg_mesh* m, const double* p, double dt, double* w, hipStream_t s) {
-    if (rows_mfma_supported(m, true)) return rows_dualgrad(m, p, dt, w, s);
+    if (rows_mfma_supported(m, GroupKernel::FACES)) return rows_dualgrad(m, p, dt, w, s);
     if (fast_rows_supported(m)) return fast_dualgrad(m, p, dt, w, s);
     const PicardDevice& d = m->pd;
     const int64_t F = (int64_t)m->faces.size();
@@ -614,7 +614,7 @@ hipError_t run_dualgrad(const stdg_mesh* m, const double* p, double dt, double* 
 }
 
 hipError_t run_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, double* b, hipStream_t s) {
-    if (rows_mfma_supported(m, false)) return rows_rhs_pressure(m, Fv, dt, b, s);
+    if (rows_mfma_supported(m, GroupKernel::RHS)) return rows_rhs_pressure(m, Fv, dt, b, s);
     if (fast_rows_supported(m)) return fast_rhs_pressure(m, Fv, dt, b, s);
     hipLaunchKernelGGL(k_rhs_pressure, dim3(nblk(m->E * m->Nst)), dim3(256), 0, s, m->pd.QT, m->d.cls, m->pd.tet_face,
                        m->pd.W, Fv, dt, b, m->E, (int64_t)m->faces.size(), m->G, m->N);
@@ -623,7 +623,7 @@ hipError_t run_rhs_pressure(const stdg_mesh* m, const double* Fv, double dt, dou
 
 hipError_t run_visc_rhs(const stdg_mesh* m, const double* vprev, const double* ups, const double* lam,
                         const double* vbc, double* rhs, hipStream_t s) {
-    if (rows_mfma_supported(m, false)) return rows_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
+    if (rows_mfma_supported(m, GroupKernel::VISC_RHS)) return rows_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
     if (fast_rows_supported(m)) return fast_visc_rhs(m, vprev, ups, lam, vbc, rhs, s);
     const PicardDevice& d = m->pd;
     hipLaunchKernelGGL(k_visc_rhs, dim3(nblk(3 * m->E * m->Nst)), dim3(256), 0, s, d.MIT, d.BB, m->d.cls, m->d.nbr,

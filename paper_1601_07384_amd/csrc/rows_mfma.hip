@@ -18,6 +18,8 @@
 // 1,068 -> 273; the three transfers of 1,296 elements with walls, p = 3,
 // p_gamma = 1: 162 -> 37.
 
+#include <algorithm>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 #include "mfma64.hpp"
@@ -357,11 +359,54 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_visc_rhs(const double*
 
 }  // namespace
 
-// groups of elements or of faces that fill, every component within the 2 GiB
-// of a buffer offset
-bool rows_mfma_supported(const stdg_mesh* m, bool faces) {
-    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 &&
-           (faces ? face_groups_fill(m) : segs_fill(m)) &&
+// A group kernel costs a time per group (blocks staged, one workgroup's chain),
+// the kernels on the vector units one per element beside a floor that grows
+// with p.  So groups are used while their number stays below
+//   base + elements / slope,
+// four and more elements each on average: `base` groups take as long as the
+// other kernel's floor, and from `slope` elements per group on the groups are
+// as fast on any mesh.  Fitted to 7 meshes of 4 to 40 elements per group for
+// each of 486, 1,536 and 3,456 groups; us, groups / vector units:
+//   average, p = 2, p_gamma = 1: 486 groups of 4 9 / 14, 1,536 of 4 19 / 17, of
+//   16 22 / 27, 3,456 of 8 38 / 31, of 24 46 / 82;
+//   goback, p = 2, p_gamma = 1: 1,536 of 4 22 / 13, of 16 25 / 28, 3,456 of 8 44 / 33;
+//   p = 1: 1,536 of 8 10 / 7, of 40 16 / 16; p = 3: 1,536 of 4 48 / 47, of 16 52 / 100;
+//   pressure right-hand side, p = 1, p_gamma = 2: 3,456 of 24 26 / 24, of 40 31 / 37;
+//   p >= 2 ahead at every number;
+//   viscous right-hand side, p = 2, p_gamma = 1: 1,536 of 4 14 / 11, of 12 15 / 16;
+//   viscous operator (with D^-1 and the dots, per BiCGStab iteration), p = 1,
+//   p_gamma = 1: 1,536 of 4 27 / 25, 3,456 of 12 56 / 45, of 24 62 / 67;
+//   convection, p = 2, p_gamma = 1: 486 of 4 77 / 124, 1,536 of 8 219 / 141, of 40
+//   243 / 365, 3,456 of 8 510 / 220.
+// Convection of 4, 5 time nodes has a longer chain (p = 1 78 us, p = 2 180) than
+// the lane-per-element kernel on small meshes of whole runs or many classes (51,
+// 140); where runs mix few classes that kernel takes 170 to 800.
+bool groups_pay(const stdg_mesh* m, GroupKernel k) {
+    const bool faces = k == GroupKernel::FACES;
+    const int64_t n = faces ? (int64_t)m->faces.size() : m->E;
+    const int64_t groups = faces ? m->pd.n_face_groups : m->d.n_segs;
+    if (4 * groups > n) return false;
+    // by kernel, p - 1 and time nodes 1, 2, 3, more
+    constexpr int ANY = 1 << 30;
+    static const int base[6][4][4] = {
+        {{500, 64, 64, 64}, {2000, 900, 800, 300}, {1600, 1600, 800, 800}, {1000, 1000, 1000, 1000}},
+        {{1000, 128, 128, 128}, {1000, 660, 660, 400}, {3200, 2400, 1600, 1000}, {2000, 2000, 2000, 500}},
+        {{3500, 1700, 1400, 600}, {ANY, ANY, ANY, ANY}, {ANY, ANY, ANY, ANY}, {ANY, ANY, ANY, ANY}},
+        {{1600, 300, 600, 100}, {1700, 1000, 1000, 400}, {2000, 1150, 1000, 300}, {1000, 1000, 300, 0}},
+        {{3500, 1300, 1000, 900}, {3500, 3200, 2400, 1500}, {2500, 2500, 2500, 2500}, {2500, 2500, 2500, 2500}},
+        {{2100, 650, 420, 50}, {2400, 650, 450, 50}, {3000, 1400, 550, 480}, {400, 450, 0, 0}}};
+    const int deg = m->N == 4 ? 0 : (m->N == 10 ? 1 : (m->N == 20 ? 2 : 3));
+    const bool rows = k != GroupKernel::VISCOUS && k != GroupKernel::CONVECTION;
+    const int slope = rows && deg == 0 ? 48 : (faces ? 20 : 32);
+    if (k == GroupKernel::CONVECTION && deg < 2 && m->G > 3 && m->E < 12000 &&
+        (64 * (int64_t)m->n_classes > m->E || 64 * groups < n + 64))
+        return false;
+    return groups <= base[(int)k][deg][std::min(m->G, 4) - 1] + n / slope;
+}
+
+// every component within the 2 GiB of a buffer offset
+bool rows_mfma_supported(const stdg_mesh* m, GroupKernel k) {
+    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && groups_pay(m, k) &&
            8 * (int64_t)m->faces.size() * m->Nst < ((int64_t)1 << 31);
 }
 

@@ -247,11 +247,11 @@ hipError_t launch_visc(const stdg_mesh* m, const double* x, double* y, const dou
 
 int64_t visc_mfma_blocks(const stdg_mesh* m) { return m64_blocks(m->d.n_segs); }
 
-// N G up to 80 (the inverse diagonal block in LDS), groups that fill, and
+// N G up to 80 (the inverse diagonal block in LDS), groups that pay, and
 // offsets within a component below 2 GiB
 bool visc_mfma_supported(const stdg_mesh* m) {
-    return segs_fill(m) && (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && m->Nst <= 80 &&
-           8 * m->E * m->Nst < ((int64_t)1 << 31);
+    return (m->N == 4 || m->N == 10 || m->N == 20 || m->N == 35) && m->G <= 5 && m->Nst <= 80 &&
+           8 * m->E * m->Nst < ((int64_t)1 << 31) && groups_pay(m, GroupKernel::VISCOUS);
 }
 
 #define STDG_VISC_NG                                                              \
