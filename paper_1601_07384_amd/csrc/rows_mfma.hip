@@ -270,11 +270,12 @@ __global__ void __launch_bounds__(RT, (waves<N, G>())) kr_rhs(const double* __re
 }
 
 // components per workgroup of the viscous right-hand side: beside the sums it
-// holds as many mixed columns, so all three only at p = 1 with few time nodes.
+// holds as many mixed columns, so all three only at p = 1 with one or two time
+// nodes.
 // One against three, us: 3,072 elements, p = 2, p_gamma = 4 26.5 -> 8.8 (14.6 on
 // the vector units), p = 3, p_gamma = 2 26.1 -> 9.9; 48,000, p = 2, p_gamma = 4
 // 104 -> 61 (94; three spilled 64 registers), p_gamma = 1 23.2 -> 23.1.
-template <int N, int G> constexpr int rhs_comps() { return N == 4 && G <= 3 ? 3 : 1; }
+template <int N, int G> constexpr int rhs_comps() { return N == 4 && G <= 2 ? 3 : 1; }
 
 // viscous right-hand side: M (sum_b g0g1[a][b] vprev_b - T[a][b] lam_b) - ups_a - nu dt W_a sum_{bdry f} BB_f vbc
 template <int N, int G>
