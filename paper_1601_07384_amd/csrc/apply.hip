@@ -126,6 +126,13 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
 // G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; no two
 // neighbours of one class (schur_apply_list), 82,944, p = 3, G = 2: 391 -> 198.  The sums' rounding is half as large.
 // With DOT the workgroup's share of x.y goes to part[blockIdx.x].
+// Elements written out at a time: at p = 4 with four and five time nodes the
+// rows of 16 took more LDS than the blocks (90 KB against 50 at five) and left
+// one workgroup per CU.  16 / 8 at a time, us (the kernel before that staged x):
+// 24,576 elements, G = 5 61.7 / 56.4 (59.4), 82,944 193 / 154 (166), 131,712 297 /
+// 246 (266), G = 4 199 / 189 (225); 48,000, whose 750 groups fill three rounds of
+// one per CU but one and a half of two, 102 / 105 (96); G = 3 no difference.
+template <int N, int G> constexpr int m64_part() { return N == 35 && G >= 4 ? 8 : 16; }
 template <int N, int G, int CW, bool DOT>
 __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __restrict__ BT,
                                                            const m64_i4* __restrict__ segs,
@@ -134,7 +141,8 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
                                                            double* __restrict__ y, int64_t E, uint32_t n_segs,
                                                            double* __restrict__ part) {
     constexpr int NT = 256 / CW, NQ = M64<N>::NQ, NP = M64<N>::NP, NC = CW * G;
-    constexpr int LD = 5 * N * NP > 64 * G * N ? 5 * N * NP : 64 * G * N;
+    constexpr int EN = m64_part<N, G>(), OUT = 4 * EN * G * N;
+    constexpr int LD = 5 * N * NP > OUT ? 5 * N * NP : OUT;
     __shared__ double A[LD];
     __shared__ double red[NT / 64];
     double d = 0.0;
@@ -193,8 +201,8 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
             if (left <= 0) continue;
             const int count = (int)(left < 16 ? left : 16) * G * N;
             const int64_t at = first * G * N;
-            m64_flush<N, G>(
-                A + w * 16 * G * N, lane, hi, count,
+            m64_flush<N, G, EN>(
+                A + w * EN * G * N, lane, hi, count,
                 [&](int rg, int a) {
                     double s = 0.0;
 #pragma unroll

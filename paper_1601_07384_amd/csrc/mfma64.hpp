@@ -101,29 +101,36 @@ template <int N, int T> __device__ inline void m64_stage(const double* __restric
 // instruction would touch 16 rows, 32 bytes each (goback, 663,552 elements,
 // p = 3: 465 -> 445 us, the preconditioned viscous operator 340 -> 317).  value(rg, a) is the lane's result row 4 rg + hi at
 // time node a; out(i, v) takes the two values at offset i of the component
-// (relative to the first entity), of which those below `count` exist.
+// (relative to the first entity), of which those below `count` exist.  EN
+// entities pass at a time (buf: EN G N doubles).
 typedef double m64_d2u __attribute__((ext_vector_type(2), aligned(8)));   // rows start at any multiple of 8 bytes
-template <int N, int G, typename V, typename O>
+template <int N, int G, int EN = 16, typename V, typename O>
 __device__ __forceinline__ void m64_flush(double* buf, int lane, int hi, int count, V&& value, O&& out) {
-    constexpr int NQ = M64<N>::NQ, TOT = 16 * G * N;
+    constexpr int NQ = M64<N>::NQ, TOT = EN * G * N;
+    static_assert(EN == 16 || TOT % 2 == 0, "pairs within a part");
     // (lanes of absent entities write too; their values are not read)
-    double* row = buf + (lane & 15) * (G * N);
+    double* row = buf + (lane & (EN - 1)) * (G * N);
 #pragma unroll
-    for (int a = 0; a < G; ++a)
+    for (int part = 0; part < 16 / EN; ++part) {
+        if (EN == 16 || (lane & 15) / EN == part)
 #pragma unroll
-        for (int rg = 0; rg < NQ; ++rg)
-            if (4 * rg + hi < N) row[a * N + 4 * rg + hi] = value(rg, a);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int a = 0; a < G; ++a)
 #pragma unroll
-    for (int i0 = 0; i0 < TOT; i0 += 128) {
-        const int i = i0 + 2 * lane;
-        if (i < count) out(i, m64_d2u{buf[i], buf[i + 1 < TOT ? i + 1 : i]});
+                for (int rg = 0; rg < NQ; ++rg)
+                    if (4 * rg + hi < N) row[a * N + 4 * rg + hi] = value(rg, a);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int left = count - part * TOT;
+#pragma unroll
+        for (int i0 = 0; i0 < TOT; i0 += 128) {
+            const int i = i0 + 2 * lane;
+            if (i < left && i < TOT) out(part * TOT + i, m64_d2u{buf[i], buf[i + 1 < TOT ? i + 1 : i]});
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // store of m64_flush's pair at y + i
