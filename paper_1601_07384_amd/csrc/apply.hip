@@ -10,7 +10,8 @@
 // FP64 (p <= 4, p_gamma <= 4): groups of up to 64 elements of one class on the
 // FP64 matrix cores, meshes without such groups with a thread per (coupling,
 // row) (schur_apply_list); meshes whose elements carry their own blocks stream them
-// (cg_elem.hip).  FP32 vectors and other degrees: one thread per (element,
+// (cg_elem.hip), and at p = 1 large meshes take an element per lane
+// (schur_apply_run).  FP32 vectors and other degrees: one thread per (element,
 // time node), the neighbour column x'_m = sum_b C_ab x_k[b][m] formed on the
 // fly, N outputs in registers; a wavefront of one class reads its blocks
 // through scalar loads (stored transposed, BT[c][k][m][r], so that a column is
@@ -224,6 +225,102 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
     }
 }
 
+// y = S x at p = 1 with one or two time nodes on large meshes of whole runs (64
+// elements of one class): a wavefront per run, lane l = element 64 run + l.  For
+// each coupling the wavefront moves the 64 rows it needs (contiguous in
+// memory) into its LDS with 16-byte loads that walk them in order, then every
+// lane reads its own row back and applies the class block column by column
+// through scalar loads.  The G x G time factor is applied to the result, which
+// leaves through LDS the same way.  Row pieces sit at an odd stride of 16-byte
+// units, so that the 16 lanes of each pass of a 16-byte read hit distinct banks.
+// Bound: HBM.  A row is 4 doubles here, so schur_apply_m64's 64 elements are one
+// 16-byte load per lane and coupling beside staging and two barriers.  us, groups /
+// this: G = 1 48,000 elements 4.5 / 7.5, 384,000 15.1 / 9.0, 663,552 23.7 / 14.9; G = 2
+// 48,000 5.9 / 9.2, 131,712 10.8 / 8.2, 663,552 40.2 / 28.1; G = 3, p = 2 the groups
+// at every size (p = 2, 663,552 39.5 / 47.4).
+template <int N, int G>
+__global__ void __launch_bounds__(64) schur_apply_run(const double* __restrict__ BT, const int32_t* __restrict__ cls,
+                                                      const int32_t* __restrict__ nbr, const double* __restrict__ C,
+                                                      const double* __restrict__ x, double* __restrict__ y,
+                                                      int64_t E, uint32_t n_runs) {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    constexpr int R = N * G, NP = R / 2, STR = NP % 2 == 0 ? NP + 1 : NP;
+    static_assert(R % 2 == 0, "rows of whole 16-byte pieces");
+    __shared__ d2 L[64 * STR];
+    const int lane = threadIdx.x;
+    const uint32_t run = m64_group(gridDim.x);
+    if (run >= n_runs) return;
+    const int64_t e0 = (int64_t)run * 64, e = e0 + lane;
+    const bool valid = e < E;
+    const int c = __builtin_amdgcn_readfirstlane(cls[e0]);
+    int nbk[4] = {-1, -1, -1, -1};
+    if (valid) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) nbk[f] = nbr[4 * e + f];
+    }
+    double z[G][N];
+#pragma unroll
+    for (int b = 0; b < G; ++b)
+#pragma unroll
+        for (int r = 0; r < N; ++r) z[b][r] = 0.0;
+    for (int k = 0; k < 5; ++k) {
+        const int src = k == 0 ? (valid ? (int)e : -1) : nbk[k - 1];
+        if (__builtin_amdgcn_readfirstlane(__ballot(src >= 0) != 0 ? 1 : 0) == 0) continue;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int pc = i * 64 + lane, row = pc / NP, piece = pc - row * NP;
+            const int s = __shfl(src, row, 64);
+            const m64_d2u v = s >= 0 ? reinterpret_cast<const m64_d2u*>(x + (int64_t)s * R)[piece] : m64_d2u{0.0, 0.0};
+            L[row * STR + piece] = d2{v.x, v.y};
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double xr[R];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const d2 t = L[lane * STR + j];
+            xr[2 * j] = t.x;
+            xr[2 * j + 1] = t.y;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const double* Bk = BT + ((int64_t)c * 5 + k) * N * N;
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const double* col = Bk + m * N;
+#pragma unroll
+            for (int r = 0; r < N; ++r) {
+                const double a = col[r];
+#pragma unroll
+                for (int b = 0; b < G; ++b) z[b][r] += a * xr[b * N + m];
+            }
+        }
+    }
+    double yr[R];
+#pragma unroll
+    for (int a = 0; a < G; ++a)
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int b = 0; b < G; ++b) s += C[a * G + b] * z[b][r];
+            yr[a * N + r] = s;
+        }
+#pragma unroll
+    for (int j = 0; j < NP; ++j) L[lane * STR + j] = d2{yr[2 * j], yr[2 * j + 1]};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int pc = i * 64 + lane, row = pc / NP, piece = pc - row * NP;
+        const d2 v = L[row * STR + piece];
+        if (e0 + row < E) reinterpret_cast<m64_d2u*>(y + (e0 + row) * R)[piece] = m64_d2u{v.x, v.y};
+    }
+}
+
 // y = S x element by element: a thread per coupling and row, EPB elements per
 // workgroup of LT threads, the five couplings in parallel and summed through
 // LDS.  Bound: the blocks, 5 N^2 values per element through L2.
@@ -305,6 +402,19 @@ static hipError_t launch_m64(const stdg_mesh* m, const double* C, const double* 
     return hipGetLastError();
 }
 
+// p = 1, one or two time nodes, 100,000 elements and more in whole runs
+static bool run64(const stdg_mesh* m) {
+    return m->N == 4 && m->G <= 2 && m->E >= 100000 && m->d.n_segs == (m->E + 63) / 64;
+}
+
+template <int N, int G>
+static hipError_t launch_run(const stdg_mesh* m, const double* C, const double* x, double* y, hipStream_t s) {
+    const uint32_t runs = (uint32_t)m->d.n_segs;
+    hipLaunchKernelGGL((schur_apply_run<N, G>), dim3(m64_blocks(runs)), dim3(64), 0, s, m->d.blocks, m->d.cls,
+                       m->d.nbr, C, x, y, m->E, runs);
+    return hipGetLastError();
+}
+
 template <int N, int G, typename T>
 static hipError_t launch_tn(const stdg_mesh* m, const T* BT, const T* C, const T* x, T* y, hipStream_t s) {
     const int64_t blocks = (m->E + 255) / 256 * G;
@@ -373,6 +483,7 @@ static hipError_t launch_apply(const stdg_mesh* m, const T* BT, const T* C, cons
     if constexpr (sizeof(T) == 8) {
         // meshes whose elements carry their own blocks: the per-element FP64 tables
         if (elem_apply64_supported(m)) return elem_apply_f64(m, C, x, y, s);
+        if (run64(m)) return m->G == 1 ? launch_run<4, 1>(m, C, x, y, s) : launch_run<4, 2>(m, C, x, y, s);
         if (m64_supported(m)) return apply_m64(m, C, x, y, nullptr, s);
     } else if (list32(m)) {
 #define STDG_NG(n, g)                                                                                       \

@@ -1,0 +1,17 @@
+"""FP64 pressure operator at p = 1 on both sides of the size from which meshes
+of whole 64-element runs take an element per lane (100,000 elements), and a mesh
+that large whose last runs mix classes; against the product with the mesh's own
+blocks, as in the tests of smaller meshes.
+"""
+
+import pytest
+
+import test_gpu_apply_runs as runs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,pg", [((28, 26, 24), 0), ((28, 26, 24), 1), ((27, 26, 24), 1), ((28, 26, 20), 0),
+                                  ((28, 26, 24), 2)])
+def test_apply_matches_blocks(n, pg):
+    runs.test_apply_matches_blocks(n, 1, pg, True, True)
