@@ -100,9 +100,15 @@ constexpr int PSTRIDE = 8;              // ... stored with this stride (doubles)
 // operands) 384 4.06 / 2.45, 750 4.83 / 2.69; p = 4 (no preconditioner without the
 // second level), 384 7.8 / 3.2, 3,072 12.0 / 4.0, 24,576, p_gamma = 1 34.0 / 5.7,
 // walls (runs of several classes: a pass each) 3,072 108 / 10.4.
-constexpr int64_t TL_MIN_E_PERIODIC = 1000, TL_MIN_E = 384;
+// Periodic meshes whose runs mix classes keep element-major vectors, where more
+// time nodes lengthen each item of the residual and direction kernels: p_gamma =
+// 0 1,296, p = 2 2.10 / 2.24, 2,058 2.32 / 2.22; p_gamma = 1 1,296 2.02 / 2.55, 2,058
+// 2.33 / 2.61, 4,374 2.77 / 2.72; p_gamma = 2 2,058 2.35 / 2.88, 4,374 2.81 / 2.98, 6,000
+// 3.17 / 3.10.
+constexpr int64_t TL_MIN_E_RUNS = 1000, TL_MIN_E = 384, TL_MIN_E_MIXED = 2000;
 int64_t tl_min_elements(const stdg_mesh* m) {
-    return m->cfg.periodic && !elem_supported(m) && m->N != 35 ? TL_MIN_E_PERIODIC : TL_MIN_E;
+    if (!m->cfg.periodic || elem_supported(m) || m->N == 35) return TL_MIN_E;
+    return lane_supported(m) ? TL_MIN_E_RUNS : TL_MIN_E_MIXED * m->G;
 }
 
 __device__ inline Rsrc make_rsrc(const void* p, uint32_t bytes) {

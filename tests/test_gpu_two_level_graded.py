@@ -118,3 +118,18 @@ def test_second_level_only_where_it_pays(case):
     assert (its[0] % 64 != 0) == second
     if second:
         assert its[1] % 64 == 0 and its[0] < 0.55 * its[1]
+
+
+@pytest.mark.parametrize("n,p,pg,second", [(6, 2, 0, False), (7, 2, 0, True), (7, 2, 1, False), (9, 2, 1, True),
+                                           (9, 1, 2, False), (8, 3, 2, True)])
+def test_least_elements_of_periodic_meshes(n, p, pg, second):
+    """Runs that mix classes (all but n = 8): from 2,000 elements per time node."""
+    print(f"two-level, periodic n={n} p={p} pg={pg}", flush=True)
+    X, T = graded_mesh([graded_lines(n, 1.0)] * 3)
+    m = P.Mesh(X, T, p, pg, dt=1e-2, periodic=True)
+    x, b = system(m, X, T)
+    xs = torch.zeros_like(b)
+    rep = m.solve(b, xs, method=P.STDG_CG_TIME, precision=P.STDG_FP32, rtol=1e-8, inner_rtol=1e-4, check_every=64)
+    assert rep.status == 0 and rep.rel_residual <= 1e-8
+    print("  iterations:", rep.inner_iters, flush=True)
+    assert (rep.inner_iters % 64 != 0) == second
