@@ -1333,7 +1333,11 @@ extern "C" int stdg_pressure_solve(const stdg_mesh* cm, const double* b, double*
     int mres = 0;
     if (int e = check_solve_opts(m, o, mres)) return e;
     if (int e = ensure_workspace(m, mres, o.precision == STDG_FP32)) return e;
-    return solve_with(m, b, x, o, mres, rep, stream, m->ws, t0);
+    const int e = solve_with(m, b, x, o, mres, rep, stream, m->ws, t0);
+    // a solve that ends on an error read behind its queue: the iterations still
+    // queued write x and the mesh's work vectors
+    if (e < 0) (void)hipStreamSynchronize((hipStream_t)stream);
+    return e;
 }
 
 // ------------------------------------------------------------------ no-allocation solve
