@@ -11,7 +11,8 @@
 // left out), which is spectrally equivalent to P^T B P: on structured cubes
 // 34..38 iterations per 1e-5 at p = 2, 3 whatever the size, as many as with
 // the exact P^T B P, against 103 (8^3), 150 (12^3) and about 420 (48^3) with
-// block Jacobi alone (CPU emulation; GPU times at launch_two_level).
+// block Jacobi alone (CPU emulation; solve times at tl_min_elements in
+// cg_fused.hip and at limits below).
 //
 // K is applied exactly, by fast diagonalisation: with the generalised
 // eigenvectors V_d of the one-dimensional stiffness and lumped mass matrices
@@ -26,7 +27,8 @@
 // grid (then a corner is a grid node), otherwise uniform lines with as many
 // cells as hexahedra of six elements fill the box, corners interpolated
 // trilinearly.  It needs a mesh that fills its bounding box (the elements'
-// volumes add up to it); other meshes keep the block-Jacobi step.
+// volumes add up to it), elements a few cells wide and spacings within bounds
+// (limits); other meshes keep the block-Jacobi step.
 
 #include <algorithm>
 #include <cmath>

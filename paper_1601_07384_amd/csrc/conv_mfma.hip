@@ -29,8 +29,8 @@ namespace {
 constexpr int CT = 256;
 constexpr int QC = 36;      // points per chunk: a face of p = 3 whole, its 125 volume points in four
 
-// rows of `row` doubles [point][N] from src (points q0 .. q0 + n) into LDS
-// [QC][NP], zero where point or column is padding
+// n points' rows of N doubles, `stride` apart, from src into LDS [QC][NP], zero
+// where point or column is padding
 template <int N> __device__ inline void stage_points(const double* __restrict__ src, int n, int stride, double* L) {
     constexpr int NP = M64<N>::NP;
     for (int t = threadIdx.x; t < QC * NP; t += CT) {

@@ -38,3 +38,24 @@ def test_error_behind_the_queue(precision):
     assert torch.cuda.current_stream().query()
     m.solve(b, after, **opts)
     assert torch.equal(before, after)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_right_hand_side(bad):
+    """An error at once, and nothing left behind for the two-level CG's next solve."""
+    print("solve, right-hand side with", bad, flush=True)
+    X, T = kuhn_mesh(12)
+    m = P.Mesh(X, T, 2, 1, dt=1e-2, periodic=True)
+    x = torch.randn(m.E * m.Nst, generator=torch.Generator(device=DEV).manual_seed(1), dtype=torch.float64, device=DEV)
+    b = torch.empty_like(x)
+    m.apply(x, b)
+    opts = dict(method=P.STDG_CG_TIME, precision=P.STDG_FP32, rtol=1e-10, inner_rtol=1e-5)
+    before, after = torch.zeros_like(b), torch.zeros_like(b)
+    m.solve(b, before, **opts)
+    wrong = b.clone()
+    wrong[b.numel() // 2] = bad
+    with pytest.raises(P.StdgError, match="non-finite"):
+        m.solve(wrong, torch.zeros_like(b), **opts)
+    assert torch.cuda.current_stream().query()
+    m.solve(b, after, **opts)
+    assert torch.equal(before, after)
