@@ -127,14 +127,11 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
 // G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; no two
 // neighbours of one class (schur_apply_list), 82,944, p = 3, G = 2: 391 -> 198.  The sums' rounding is half as large.
 // With DOT the workgroup's share of x.y goes to part[blockIdx.x].
-// Elements written out at a time: at p = 4 with four and five time nodes the
-// rows of 16 took more LDS than the blocks (90 KB against 50 at five) and left
-// one workgroup per CU.  16 / 8 at a time, us (the kernel before that staged x):
-// 24,576 elements, G = 5 61.7 / 56.4 (59.4), 82,944 193 / 154 (166), 131,712 297 /
-// 246 (266), G = 4 199 / 189 (225); 48,000, whose 750 groups fill three rounds of
-// one per CU but one and a half of two, 102 / 105 (96); G = 3 no difference.
-template <int N, int G> constexpr int m64_part() { return N == 35 && G >= 4 ? 8 : 16; }
-template <int N, int G, int CW, bool DOT>
+// EN: elements whose rows pass through LDS at a time.  At p = 4 with four and
+// five time nodes the rows of 16 take more LDS than the blocks (72 and 90 KB
+// against 50), which leaves two and one workgroups per CU instead of three and
+// two; m64_narrow() says where 8 pay.
+template <int N, int G, int CW, bool DOT, int EN>
 __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __restrict__ BT,
                                                            const m64_i4* __restrict__ segs,
                                                            const int32_t* __restrict__ nbr,
@@ -142,7 +139,7 @@ __global__ void __launch_bounds__(256 / CW) schur_apply_m64(const double* __rest
                                                            double* __restrict__ y, int64_t E, uint32_t n_segs,
                                                            double* __restrict__ part) {
     constexpr int NT = 256 / CW, NQ = M64<N>::NQ, NP = M64<N>::NP, NC = CW * G;
-    constexpr int EN = m64_part<N, G>(), OUT = 4 * EN * G * N;
+    constexpr int OUT = 4 * EN * G * N;
     constexpr int LD = 5 * N * NP > OUT ? 5 * N * NP : OUT;
     __shared__ double A[LD];
     __shared__ double red[NT / 64];
@@ -389,14 +386,32 @@ template <int N> static unsigned apply64_blocks(const stdg_mesh* m) {
     return segs_fill(m) ? m64_blocks(m->d.n_segs) : (unsigned)((m->E + list_epb<N>() - 1) / list_epb<N>());
 }
 
+// Rows leave schur_apply_m64 eight elements at a time (p = 4, G = 4, 5): where
+// there are more groups than CUs.  Up to one group per CU the second pass
+// through LDS is all that the smaller slices bring; at G = 5 three rounds of one
+// workgroup per CU are faster than one and a half of two.  16 / 8 (the kernel
+// before both, which staged x), us: G = 4 192 groups 29.4 / 33.0 (30.5), 384 46.5 /
+// 46.2 (48.0), 528 70.1 / 71.2 (70.8), 720 84.7 / 72.7 (78.5), 1,248 122 / 111 (128);
+// G = 5 192 groups 34.5 / 34.9 (35.0), 264 60.5 / 52.6 (57.9), 504 69.8 / 59.9
+// (67.2), 576 93.9 / 84.1 (88.0), 624 94.7 / 97.5 (88.1), 768 101 / 104 (94), 792 126 /
+// 105 (115), 1,536 200 / 163 (175).  G = 3 no difference.
+template <int N, int G> static bool m64_narrow(int64_t groups) {
+    constexpr int CUS = 256;
+    if (N != 35 || G < 4 || groups <= CUS) return false;
+    return G < 5 || groups <= 600 || groups > 3 * CUS;
+}
+
 template <int N, int G, int CW, bool DOT>
 static hipError_t launch_m64(const stdg_mesh* m, const double* C, const double* x, double* y, double* part,
                              hipStream_t s) {
+    constexpr int NARROW = N == 35 && G >= 4 ? 8 : 16;
     const dim3 grid(apply64_blocks<N>(m));
-    if (segs_fill(m))
-        hipLaunchKernelGGL((schur_apply_m64<N, G, CW, DOT>), grid, dim3(256 / CW), 0, s, m->d.blocks,
-                           (const m64_i4*)m->d.segs, m->d.nbr, C, x, y, m->E, (uint32_t)m->d.n_segs, part);
-    else
+    if (segs_fill(m)) {
+        const auto kernel = m64_narrow<N, G>(m->d.n_segs) ? schur_apply_m64<N, G, CW, DOT, NARROW>
+                                                          : schur_apply_m64<N, G, CW, DOT, 16>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256 / CW), 0, s, m->d.blocks, (const m64_i4*)m->d.segs, m->d.nbr, C, x,
+                           y, m->E, (uint32_t)m->d.n_segs, part);
+    } else
         hipLaunchKernelGGL((schur_apply_list<N, G, double, DOT>), grid, dim3(LT), 0, s, m->d.blocks, m->d.cls,
                            m->d.nbr, C, x, y, m->E, part);
     return hipGetLastError();
