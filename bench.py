@@ -61,11 +61,13 @@ CONFIGS = {
     "c2": dict(n=24, p=3, pg=1, dt=1e-3, nu=1e-3, n_pic=2),
     "c5": dict(n=32, p=2, pg=1, dt=1e-3, nu=1e-3, n_pic=2),
 }
-# HBM bytes of one iteration on the 663,552-element cube from rocprofv3
-# FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads for a device
-# copy of known size; valid only for the kernel source they were measured on
-# (sha256 prefix).  None until measured.
-MEASURED_TRAFFIC = {"source": "paper_1601_07384_amd/csrc/cg_lane.hip", "sha256": None, "bytes": None, "config": "c3"}
+# HBM bytes of one two-level iteration on the 663,552-element cube (operator,
+# residual update, restriction, the grid's planes twice and its columns,
+# direction update) from rocprofv3 FETCH_SIZE and WRITE_SIZE, each scaled by
+# what the counter reads for a device copy of known size (2.0 and 1.0); valid
+# only for the kernel source they were measured on (sha256 prefix).
+MEASURED_TRAFFIC = {"source": "paper_1601_07384_amd/csrc/cg_lane.hip", "sha256": "1adedd7fa6841697",
+                    "bytes": 647759872, "config": "c3"}
 FP64_PEAK_TFLOPS = 78.6
 FP32_MFMA_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0

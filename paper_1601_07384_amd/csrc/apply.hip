@@ -121,11 +121,12 @@ __global__ void __launch_bounds__(256) schur_apply_rows(
 // and written in whole lines).  Bound: HBM at p <= 2, the matrix cores and the
 // operand reads at p = 3, 4, the launch (7.8 us in a loop from the host)
 // below 10^4 elements.  MI355X, kernels per entry on the vector units before
-// -> this one, us: 663,552 elements, p = 3, G = 1: 123 -> 102 (2.1 TB/s of x
-// and y); 196,608, p = 2: G = 1 19.9 -> 14.8, G = 2 29.7 -> 24.5; 82,944, p = 3,
-// G = 2: 33.0 -> 24.9; 48,000, p = 2, G = 3: 41 -> 11.5; with walls 10,368, p = 4,
-// G = 5: 50 -> 35 and 1,296, p = 3: 35 -> 7.7; no two
-// neighbours of one class (schur_apply_list), 82,944, p = 3, G = 2: 391 -> 198.  The sums' rounding is half as large.
+// -> this one, us: 663,552 elements, p = 3, G = 1: 92.5 -> 77.3 in a row of 50
+// launches (2.7 TB/s of x and y; 105 -> 81 one by one); 196,608, p = 2: G = 1
+// 19.9 -> 14.8, G = 2 29.7 -> 24.5; 82,944, p = 3, G = 2: 33.0 -> 24.9; 48,000,
+// p = 2, G = 3: 41 -> 11.5; with walls 10,368, p = 4, G = 5: 50 -> 34 and 1,296,
+// p = 3: 35 -> 7.7; no two neighbours of one class (schur_apply_list), 82,944,
+// p = 3, G = 2: 391 -> 198.  The sums' rounding is half as large.
 // With DOT the workgroup's share of x.y goes to part[blockIdx.x].
 // EN: elements whose rows pass through LDS at a time.  At p = 4 with four and
 // five time nodes the rows of 16 take more LDS than the blocks (72 and 90 KB
